@@ -372,6 +372,19 @@ void fill_model(fsmp_ctx *c) {
     md.logC = -md.log_tau2;
     md.den12 = 1.0;
   }
+  const double ts = md.kind == FSMP_PHI_BIEXP ? std::max(std::max(md.inv_tau1, md.inv_tau12), md.inv_tau2) : md.inv_tau2;
+  md.small_dt = md.dt * ts <= 0.25;
+  md.Cd2 = md.C / md.den2;
+  md.Cd12 = md.kind == FSMP_PHI_BIEXP ? md.C / md.den12 : 0.0;
+  md.ga = (float)(md.dt * md.inv_tau2);
+  md.ga_inv = 1.0f / md.ga;
+  md.gb = (float)(md.dt * md.inv_tau1);
+  // the rise factors reach 1 to the last bit at e^{-n dt / tau_rise} < 2^-54
+  md.rise_n = 0;
+  if (md.kind == FSMP_PHI_BIEXP) {
+    const double nr = std::ceil(54.0 * std::log(2.0) / (md.dt * md.inv_tau1)) + 1.0;
+    if (nr <= kMaxRise) md.rise_n = (int)nr;
+  }
   md.sub_shift = -1;
   for (int k = 0; k < 31; ++k)
     if ((1 << k) == md.sub) md.sub_shift = k;
@@ -384,21 +397,23 @@ void fill_model(fsmp_ctx *c) {
 }
 
 // Table of 1 - e^{-k dt / tau} (tau2, then tau12; 0 for EXP) for k = 0 .. n - 1, n >= need:
-// the count-dependent factors of the light curve's partial sums.  Grown (never shrunk) when
+// the count-dependent factors of the light curve's partial sums; then the rise factors at
+// whole grid steps (ModelDev::rtab).  Grown (never shrunk) when
 // a batch has a longer solution space; earlier launches of this context are waited for
 // before the old table is released.
 hipError_t ensure_ptab(fsmp_ctx *c, int64_t need) {
   if (c->md.ptab && c->md.ptab_n >= need) return hipSuccess;
   const int64_t n = std::max<int64_t>(need, 4 * 4096 + 1);
-  std::vector<double> h(2 * (size_t)n);
+  std::vector<double> h(2 * (size_t)n + c->md.rise_n);
   for (int64_t k = 0; k < n; ++k) {
     const double kdt = (double)k * c->md.dt;
     h[2 * k] = -std::expm1(-kdt * c->md.inv_tau2) / c->md.den2;
     h[2 * k + 1] = c->md.kind == FSMP_PHI_EXP ? 0.0 : -std::expm1(-kdt * c->md.inv_tau12) / c->md.den12;
   }
+  for (int k = 0; k < c->md.rise_n; ++k) h[2 * (size_t)n + k] = -std::expm1(-(double)k * c->md.dt * c->md.inv_tau1);
   (void)hipDeviceSynchronize();
   c->ptab.release();
-  hipError_t e = c->ptab.ensure(2 * (size_t)n);
+  hipError_t e = c->ptab.ensure(h.size());
   if (e == hipSuccess) e = hipMemcpy(c->ptab.p, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     c->md.ptab = nullptr;
@@ -407,6 +422,7 @@ hipError_t ensure_ptab(fsmp_ctx *c, int64_t need) {
   }
   c->md.ptab = c->ptab.p;
   c->md.ptab_n = n;
+  c->md.rtab = c->ptab.p + 2 * n;
   return hipSuccess;
 }
 

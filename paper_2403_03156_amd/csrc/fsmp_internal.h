@@ -28,6 +28,14 @@ struct ModelDev {
   // (device; the geometric series' denominators divided out on the host)
   const double *ptab;
   int64_t ptab_n;
+  // BIEXP: 1 - e^{-n dt / tau_rise} for n = 0 .. rise_n - 1, the last entry 1 to the last bit
+  // (device, behind ptab); rise_n = 0 (EXP, or a rise over too many grid points): no table
+  const double *rtab;
+  int32_t rise_n;
+  int32_t small_dt;    // dt / tau <= 1/4 for every tau of the light curve (t0_terms)
+  double Cd2, Cd12;    // C / den2, C / den12 (0 for EXP): the two series summed to infinity
+  // birth search's first guess, FP32: dt / tau2, its inverse, dt / tau_rise (0 for EXP)
+  float ga, ga_inv, gb;
   // MCP-PMT mixture (n_mix > 0): cumulative weights (accumulated in index order) and, per
   // component, rho_e = s / sigma_e^2, log rho_e, rho_e mu_e, rho_e mu_e^2
   int32_t n_mix, pad2;
@@ -172,6 +180,7 @@ size_t lane_ws_doubles(int kcap, int64_t n_list);
 size_t lane_ws_ints(int kcap, int64_t n_list);
 // PE capacities of the chain kernels; a waveform runs in the smallest one >= its kmax
 constexpr int kNumCaps = 8;
+constexpr int kMaxRise = 1024;  // longest rise table (8 KB of LDS beside the overlap tables)
 constexpr int kCaps[kNumCaps] = {16, 32, 48, 64, 96, 128, 160, 192};
 bool chain_kcap_supported(int kcap, int M, int sub);  // lane-group (LDS) instance exists and fits
 // lane groups with H in device memory (FP64, or FP32 in the precision form; `wide`: the

@@ -103,6 +103,18 @@ __device__ inline double dpp_move(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// log2, 2^x and 1 / x in FP32 to an ulp by the hardware's own instructions (first guesses only;
+// the library's functions where the source is compiled for the host)
+#if defined(__AMDGCN__)
+__device__ inline float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
+__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ inline float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+#else
+inline float fast_log2(float x) { return log2f(x); }
+inline float fast_exp2(float x) { return exp2f(x); }
+inline float fast_rcp(float x) { return 1.0f / x; }
+#endif
+
 // v of lane L of the wavefront, in scalar registers
 __device__ inline double lane_value(double v, int L) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), L);
@@ -196,18 +208,65 @@ __device__ inline double phi_total(const ModelDev &md, double t0, int glo, int g
   return p.n > 0 ? phi_partial(md, xs_exp(md, p.xs), p.n) : 0.0;
 }
 
-// phi_total for a chain's lane group (t0, glo, ghi the same in all its lanes, every lane
-// active): the two exponentials are one evaluation (the group's first lane e2, its second
-// e12)
+// 1 - e^{-y} for 0 <= y <= 1/4 by its Taylor series (thirteen terms: the rest is below
+// 2^-56 of the value), all terms in one chain of multiply-adds
+__device__ inline double one_minus_exp_small(double y) {
+  const double x = -y;
+  double p = 1.0 / 6227020800.0;
+  p = fma(p, x, 1.0 / 479001600.0);
+  p = fma(p, x, 1.0 / 39916800.0);
+  p = fma(p, x, 1.0 / 3628800.0);
+  p = fma(p, x, 1.0 / 362880.0);
+  p = fma(p, x, 1.0 / 40320.0);
+  p = fma(p, x, 1.0 / 5040.0);
+  p = fma(p, x, 1.0 / 720.0);
+  p = fma(p, x, 1.0 / 120.0);
+  p = fma(p, x, 1.0 / 24.0);
+  p = fma(p, x, 1.0 / 6.0);
+  p = fma(p, x, 0.5);
+  p = fma(p, x, 1.0);
+  return y * p;
+}
+
+// What a light-curve start t0 contributes to a sweep, the same in all lanes of a chain's group:
+// the factors of the partial sums from the first grid point of T at or after t0 (xs_exp), its
+// index gs, the number n of points from there on, the sum over them, and for the rise factors
+// of the PEs (rise_at) the first grid point g0 at or after t0 (not clipped to T) with
+// q1 = 1 - e^{-(g0 dt - t0) / tau_rise}.
+struct T0Terms {
+  double e2, e12, q1, Phi;
+  int g0, gs, n;
+};
+
+// T0Terms for a chain's lane group (t0, glo <= ghi the same in all its lanes, every lane
+// active).  The distance g0 dt - t0 is below one grid step, so with dt / tau <= 1/4 all three
+// exponentials are one short series (lane 0 tau2, lane 1 tau12, the others tau_rise): 13
+// multiply-adds where the library's exp and expm1 take about 70 instructions.  Other light
+// curves, and a T that starts after t0 (the two sums then start at its first point), take the
+// library functions.
 template <int W>
-__device__ inline double phi_total_group(const ModelDev &md, double t0, int glo, int ghi, int lane, int base) {
-  const GridPos p = grid_pos(md, t0, glo, ghi);
-  const double v = exp(-p.xs * (lane == 0 ? md.inv_tau2 : md.inv_tau12));
-  XsExp x;
-  x.e2 = group_bcast<W, 0>(v, base);
-  const double v12 = group_bcast<W, 1>(v, base);
-  x.e12 = md.kind == FSMP_PHI_EXP ? 0.0 : v12;
-  return p.n > 0 ? phi_partial(md, x, p.n) : 0.0;
+__device__ inline T0Terms t0_terms(const ModelDev &md, double t0, int glo, int ghi, int lane, int base) {
+  T0Terms t;
+  const double gd = ceil(md.sub_shift >= 0 ? t0 * md.sub : t0 / md.dt);
+  t.g0 = (int)fmin(fmax(gd, -1073741824.0), 1073741824.0);
+  t.gs = t.g0 < glo ? glo : t.g0;
+  t.n = ghi - t.gs + 1;
+  const double f = (double)t.g0 * md.dt - t0;
+  const double y = f * (lane == 0 ? md.inv_tau2 : lane == 1 ? md.inv_tau12 : md.inv_tau1);
+  double v, e;
+  if (md.small_dt && f <= md.dt) {
+    v = one_minus_exp_small(y);
+    e = 1.0 - v;
+  } else {
+    v = -expm1(-y);
+    e = exp(-y);
+  }
+  if (t.g0 < glo) e = exp(-((double)glo * md.dt - t0) * (lane == 0 ? md.inv_tau2 : md.inv_tau12));
+  t.e2 = group_bcast<W, 0>(e, base);
+  t.e12 = md.kind == FSMP_PHI_EXP ? 0.0 : group_bcast<W, 1>(e, base);
+  t.q1 = group_bcast<W, 2>(v, base);
+  t.Phi = t.n > 0 ? phi_partial(md, XsExp{t.e2, t.e12}, t.n) : 0.0;
+  return t;
 }
 
 // Sum over a group of W lanes (W a power of two, groups aligned to W): a butterfly over lane
@@ -270,15 +329,33 @@ __device__ inline void group_log2(double x0, double x1, int lane, int base, doub
   l1 = group_bcast<W, 1>(v, base);
 }
 
-// BIEXP part of log phi that depends on t0: log(1 - e^{-(t - t0) / tau_rise})
-__device__ inline double rise_term(const ModelDev &md, int g, double t0) {
-  return log(-expm1(-((double)g * md.dt - t0) * md.inv_tau1));
+// the same for three values (the group's lanes 0, 1 and 2 on)
+template <int W>
+__device__ inline void group_log3(double x0, double x1, double x2, int lane, int base, double &l0, double &l1,
+                                  double &l2) {
+  const double v = log(lane == 0 ? x0 : lane == 1 ? x1 : x2);
+  l0 = group_bcast<W, 0>(v, base);
+  l1 = group_bcast<W, 1>(v, base);
+  l2 = group_bcast<W, 2>(v, base);
 }
 
-// its factor 1 - e^{-(t - t0) / tau_rise}, in (0, 1) for t > t0; t - t0 is at least an ulp
+// BIEXP rise factor 1 - e^{-(t - t0) / tau_rise}, in (0, 1) for t > t0; t - t0 is at least an ulp
 // of t0, so a product of eight factors stays far above the FP64 underflow threshold
 __device__ inline double rise_factor(const ModelDev &md, int g, double t0) {
   return -expm1(-((double)g * md.dt - t0) * md.inv_tau1);
+}
+
+// The rise factor of the PE at grid point g from the table rt of md.rise_n entries (LDS):
+// with n = g - g0 >= 0 and r_n = 1 - e^{-n dt / tau_rise},
+//   1 - e^{-(g dt - t0) / tau_rise} = r_n + (1 - r_n) q1
+// (every term positive: no cancellation, however close the PE is to t0).  One LDS read and two
+// multiply-adds instead of an expm1 (about 45 instructions) per PE and sweep.
+__device__ inline double rise_at(const ModelDev &md, const double *rt, const T0Terms &t, double t0, int g) {
+  const int n = g - t.g0;
+  // no table; or the rounding of g dt and ceil(t0 / dt) (dt not a power of two) disagrees
+  if (md.rise_n == 0 || n < 0) return rise_factor(md, g, t0);
+  const double r = rt[n < md.rise_n ? n : md.rise_n - 1];
+  return fma(t.q1, 1.0 - r, r);
 }
 
 // v / sub and v % sub for v >= 0 (grid indices): shifts when sub is a power of two
@@ -301,58 +378,74 @@ __device__ inline double overlap(const ModelDev &md, const double *vt, const dou
   return s;
 }
 
-// birth position: smallest g in T with sum_{g' <= g} phi(g' dt - t0) > target
+// Birth position: smallest g in T with sum_{g' <= g} phi(g' dt - t0) > target.  The partial sum
+// over the first k points is Cd2 e2 (1 - a^k) - Cd12 e12 (1 - b^k), a = e^{-dt / tau2},
+// b = e^{-dt / tau12}; with R the whole series less the target, it reaches the target where
+//   k dt / tau2 = log(Cd2 e2 / R) + log(1 - w0 e^{-k dt / tau_rise}),   w0 = Cd12 e12 / (Cd2 e2).
+// Two Newton steps in FP32 from the large-k solution land on the point or the one after it
+// (measured: 99.7% on it, the rest one off, over the light curves of the workloads and rises
+// from 0.3 to 20 ns); the group's lanes then evaluate the exact FP64 partial sums at that many
+// neighbours and pick the first above the target, so the result is the search's own.  A guess
+// outside the neighbourhood falls back to an LPC-ary search of the side it lies on.  One
+// round trip to the table instead of log_LPC(points): 1 against 6 for 4-lane groups on
+// 1,024-sample windows.
 template <int LPC>
-__device__ inline int birth_draw(const ModelDev &md, double t0, int glo, int ghi, double target, int lane, int grp) {
-  const GridPos p = grid_pos(md, t0, glo, ghi);
-  XsExp xe;
+__device__ inline int birth_draw(const ModelDev &md, const T0Terms &t, double target, int lane, int grp) {
+  const XsExp xe{t.e2, t.e12};
+  const uint64_t gmask = (LPC == 64) ? ~0ull : ((1ull << (LPC & 63)) - 1ull);
+  const int last = t.n - 1;
+  int lo = 0, hi = last;
   {
-    // the two exponentials in one evaluation (the group's first lane e2, its second e12)
-    const double v = exp(-p.xs * (lane == 0 ? md.inv_tau2 : md.inv_tau12));
-    xe.e2 = group_bcast<LPC, 0>(v, grp * LPC);
-    const double v12 = group_bcast<LPC, 1>(v, grp * LPC);
-    xe.e12 = md.kind == FSMP_PHI_EXP ? 0.0 : v12;
-  }
-  int64_t k;
-  if (md.kind == FSMP_PHI_EXP) {
-    // closed-form inverse of the truncated geometric law
-    const double c = target * exp(p.xs * md.inv_tau2) * md.den2 / md.inv_tau2;
-    if (c >= 1.0) {
-      k = p.n - 1;
-    } else {
-      const double L = -log1p(-c) / (md.dt * md.inv_tau2);
-      k = (int64_t)floor(L);
-      if (k < 0) k = 0;
-      if (k > p.n - 1) k = p.n - 1;
-      // settle rounding at the boundary against the partial sums
-      if (k > 0 && phi_partial(md, xe, k) > target) k -= 1;
-      else if (k < p.n - 1 && !(phi_partial(md, xe, k + 1) > target)) k += 1;
-    }
-  } else {
-    // LPC-ary search on the closed-form partial sums
-    int64_t lo = 0, hi = p.n - 1;
-    const uint64_t gmask = (LPC == 64) ? ~0ull : ((1ull << LPC) - 1ull);
-    while (hi > lo) {
-      const int64_t span = hi - lo + 1;
-      const int64_t step = (span + LPC - 1) / LPC;
-      int64_t kl = lo + (int64_t)(lane + 1) * step - 1;
-      if (kl > hi) kl = hi;
-      const bool pred = phi_partial(md, xe, kl + 1) > target;
-      const uint64_t bal = (__ballot(pred) >> (grp * LPC)) & gmask;
-      if (bal == 0) {
-        lo = hi;
-        break;
+    const double a2 = md.Cd2 * t.e2, a12 = md.Cd12 * t.e12;
+    const double R = (a2 - a12) - target;
+    const float L = 0.69314718f * (fast_log2((float)a2) - fast_log2((float)R));
+    const float w0 = (float)a12 * fast_rcp((float)a2);
+    float k = L * md.ga_inv;
+    if (md.kind != FSMP_PHI_EXP) {
+#pragma unroll
+      for (int it = 0; it < 2; ++it) {
+        const float w = w0 * fast_exp2(-1.44269504f * md.gb * k);
+        const float u = fmaxf(1.0f - w, 1e-6f);
+        const float g = k * md.ga - L - 0.69314718f * fast_log2(u);
+        const float gp = fmaxf(md.ga - w * md.gb * fast_rcp(u), 0.02f * md.ga);
+        k = fmaxf(k - g * fast_rcp(gp), 0.0f);
       }
-      const int l = __ffsll((unsigned long long)bal) - 1;
-      int64_t khi = lo + (int64_t)(l + 1) * step - 1;
-      if (khi > hi) khi = hi;
-      const int64_t klo = (l == 0) ? lo : lo + (int64_t)l * step;
-      lo = klo;
-      hi = khi;
     }
-    k = lo;
+    // R <= 0 (rounding, the last point), an overflow or a NaN: the guess is the last point
+    int kg = R > 0.0 && k < (float)last ? (int)k : last;
+    // the neighbours kg - LPC/2 .. kg + LPC/2 - 1, moved inside [0, last]
+    int k0 = kg - LPC / 2;
+    k0 = k0 > last - (LPC - 1) ? last - (LPC - 1) : k0;
+    k0 = k0 < 0 ? 0 : k0;
+    const int kl = k0 + lane > last ? last : k0 + lane;
+    const bool pred = phi_partial(md, xe, kl + 1) > target;
+    const uint64_t bal = (__ballot(pred) >> (grp * LPC)) & gmask;
+    if (bal == 0) {
+      lo = k0 + LPC > last ? last : k0 + LPC;  // past the neighbourhood (or the last point)
+    } else {
+      const int l = __ffsll((unsigned long long)bal) - 1;
+      hi = k0 + l > last ? last : k0 + l;
+      lo = l > 0 || k0 == 0 ? hi : 0;
+    }
   }
-  return (int)(p.gs + k);
+  while (hi > lo) {
+    const int span = hi - lo + 1;
+    const int step = (span + LPC - 1) / LPC;
+    int kl = lo + (lane + 1) * step - 1;
+    if (kl > hi) kl = hi;
+    const bool pred = phi_partial(md, xe, kl + 1) > target;
+    const uint64_t bal = (__ballot(pred) >> (grp * LPC)) & gmask;
+    if (bal == 0) {
+      lo = hi;
+      break;
+    }
+    const int l = __ffsll((unsigned long long)bal) - 1;
+    int khi = lo + (l + 1) * step - 1;
+    if (khi > hi) khi = hi;
+    lo = (l == 0) ? lo : lo + l * step;
+    hi = khi;
+  }
+  return t.gs + lo;
 }
 
 // ------------------------------------------------------------------ grid occupancy
@@ -652,6 +745,8 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
   for (int i = threadIdx.x; i < md.sub * md.M; i += blockDim.x) ov[i] = a.ovl[i];
   double *lgn = ov + md.sub * md.M;  // log k, k = 0..KCAP + 1
   for (int i = threadIdx.x; i < KCAP + 2; i += blockDim.x) lgn[i] = log((double)i);
+  double *rt = lgn + KCAP + 2;  // rise factors at whole grid steps (rise_at)
+  for (int i = threadIdx.x; i < md.rise_n; i += blockDim.x) rt[i] = md.rtab[i];
   __syncthreads();
 
   // the wavefront's index is the same in all its lanes: taken from the first, it and what
@@ -664,7 +759,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
   const int64_t slot = tile * CPW + grp;
   if (slot >= a.n_list) return;
 
-  double *cb = smem + md.M * (1 + md.sub) + (KCAP + 2) + (int64_t)(wv * CPW + grp) * CL::kDoubles;
+  double *cb = smem + md.M * (1 + md.sub) + (KCAP + 2) + md.rise_n + (int64_t)(wv * CPW + grp) * CL::kDoubles;
   // device memory of a tile (the wavefront's chains interleaved element by element): H in its
   // storage type; in the FP32 form then the FP64 refresh matrix W and the exact G (FP64), in
   // the corrected FP64 form the exact G
@@ -724,13 +819,12 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
 
   double t0 = a.t0init[w];
   int N = 0;
-  double Phi = (glo <= ghi) ? phi_total_group<LPC>(md, t0, glo, ghi, lane, gbase) : 0.0;
-  // Lambda_T changes only with t0 (its log is taken with the jump's own log); S_cur = sum
-  // over PEs of the BIEXP rise term at the current t0 and gmin = the smallest PE grid index
-  // (phi must stay positive at every PE) make the t0 step one term per PE
-  double Lam = lam * md.dt * Phi;
+  // the light curve's terms at t0; Lambda_T changes only with t0 (its log is taken with the
+  // jump's own log); gmin = the smallest PE grid index (phi must stay positive at every PE)
+  T0Terms tc{0.0, 0.0, 0.0, 0.0, 0, 0, 0};
+  if (glo <= ghi) tc = t0_terms<LPC>(md, t0, glo, ghi, lane, gbase);
+  double Lam = lam * md.dt * tc.Phi;
   const bool biexp = md.kind == FSMP_PHI_BIEXP;
-  double S_cur = 0.0;
   int gmin = INT32_MAX;
   if (lane == 0) {
     for (int i = 0; i < 20; ++i) acc[i] = 0.0;
@@ -765,14 +859,11 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
           gram_resid_b<LPC, LD, HS>(Gm, bv, xv, rs, n0, lane);
         }
         N = n0;
-        double sn = 0.0;
         int m = INT32_MAX;
         for (int i = lane; i < N; i += LPC) {
-          if (biexp) sn += rise_term(md, zg[i], t0);
           m = zg[i] < m ? zg[i] : m;
           occ_edit(a, c, 1, -1, zg[i], 0, burn, n_steps);
         }
-        S_cur = group_sum<LPC>(sn);
         gmin = group_min<LPC>(m);
       } else {
         st |= FSMP_ST_FACTOR;
@@ -879,41 +970,39 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       t0acc = (rec.flags & 4) != 0;
       if (rec.t0 != t0) {
         t0 = rec.t0;
-        Phi = (glo <= ghi) ? phi_total_group<LPC>(md, t0, glo, ghi, lane, gbase) : 0.0;
-        Lam = lam * md.dt * Phi;
-        if (biexp) {
-          double sn = 0.0;
-          for (int i = lane; i < N; i += LPC) sn += rise_term(md, zg[i], t0);
-          S_cur = group_sum<LPC>(sn);
-        }
+        if (glo <= ghi) tc = t0_terms<LPC>(md, t0, glo, ghi, lane, gbase);
+        Lam = lam * md.dt * tc.Phi;
       }
     } else if (t0p >= md.t0_min && t0p <= md.t0_max) {
       const double xmin = (N > 0) ? (double)gmin * md.dt - t0p : 1.0;
       if (biexp ? (xmin > 0.0) : (xmin >= 0.0)) {
-        double S_new = 0.0;
-        if (biexp) {
-          // the rise factors of a lane's PEs multiplied in runs of up to eight, one log per run
-          double pr = 1.0;
+        T0Terms tp = tc;
+        if (glo <= ghi) tp = t0_terms<LPC>(md, t0p, glo, ghi, lane, gbase);
+        double S = 0.0;  // sum over the PEs of log r(t0p) / r(t0), r the rise factor
+        if (biexp && N > 0) {
+          // the rise factors of a lane's PEs at both t0 multiplied in runs of up to eight (each
+          // at least an ulp of t0 over tau_rise: far from underflow), one log per run
+          double pn = 1.0, pc = 1.0;
           int m = 0;
           for (int i = lane; i < N; i += LPC) {
-            pr *= rise_factor(md, zg[i], t0p);
+            const int g = zg[i];
+            pn *= rise_at(md, rt, tp, t0p, g);
+            pc *= rise_at(md, rt, tc, t0, g);
             if (++m == 8) {
-              S_new += log(pr);
-              pr = 1.0;
+              S += log(pn / pc);
+              pn = pc = 1.0;
               m = 0;
             }
           }
-          S_new += log(pr);
-          S_new = group_sum<LPC>(S_new);
+          S += log(pn / pc);
+          S = group_sum<LPC>(S);
         }
-        const double part = (double)N * (t0p - t0) * md.inv_tau2 + (S_new - S_cur);
-        const double Phip = (glo <= ghi) ? phi_total_group<LPC>(md, t0p, glo, ghi, lane, gbase) : 0.0;
-        const double la0 = part - (lam * md.dt * Phip - lam * md.dt * Phi);
+        const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
+        const double la0 = part - (lam * md.dt * tp.Phi - lam * md.dt * tc.Phi);
         if (lg2 < la0) {
           t0 = t0p;
-          Phi = Phip;
-          Lam = lam * md.dt * Phi;
-          S_cur = S_new;
+          tc = tp;
+          Lam = lam * md.dt * tc.Phi;
           t0acc = true;
           if (lane == 0) cnt[1]++;
         }
@@ -934,7 +1023,9 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
     // need_mv: a birth part (births, shifts); need_dp: in the FP32 form, a death part
     // (deaths, shifts) evaluated with the residual correction
     bool valid = false, need_mv = false, need_dp = false;
-    double dnu = 0.0, la = -INFINITY, lpn = 0.0, lpo = 0.0;
+    // lpd: log phi at a shift's new position less that at its old one; pr_sh: the ratio of their
+    // rise factors, whose log is part of it
+    double dnu = 0.0, la = -INFINITY, lpd = 0.0, pr_sh = 1.0;
     // xjp: x_j as stored (the corrected FP64 form evaluates with xj = x_j + h^T s and edits x
     // with the stored value, which keeps x = H b along the edits)
     double delta2 = 1.0, up = 0.0, om = 1.0, xj = 0.0, xjp = 0.0, ej = 0.0, beta = 0.0;
@@ -957,8 +1048,8 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       if (lane == 0) cnt[2]++;
       if (N >= kmax) {
         st |= FSMP_ST_KMAX;
-      } else if (Phi > 0.0 && consider) {
-        gnew = FORCE ? rec.g : birth_draw<LPC>(md, t0, glo, ghi, u53(r[4], r[5]) * Phi, lane, grp);
+      } else if (tc.Phi > 0.0 && consider) {
+        gnew = FORCE ? rec.g : birth_draw<LPC>(md, tc, u53(r[4], r[5]) * tc.Phi, lane, grp);
         need_mv = Lam > 0.0;
       }
     } else {
@@ -996,12 +1087,16 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         sh = FORCE ? rec.g - zg[j] : (int)rint(xi_sh * md.shift_sd / md.dt);
         gnew = zg[j] + sh;
         if (gnew >= glo && gnew <= ghi) {
-          // log phi at the new and at the old position, one evaluation for both
-          const double lv = log_phi(md, (double)(lane == 0 ? gnew : zg[j]) * md.dt - t0);
-          lpn = group_bcast<LPC, 0>(lv, gbase);
-          const double lpo_v = group_bcast<LPC, 1>(lv, gbase);
-          if (lpn > -INFINITY) {
-            lpo = lpo_v;
+          const double xnew = (double)gnew * md.dt - t0;
+          if (biexp ? xnew > 0.0 : xnew >= 0.0) {
+            if constexpr (FORCE) {
+              // a recorded t0 may lie after the old position (log phi = -inf there)
+              lpd = log_phi(md, xnew) - log_phi(md, (double)zg[j] * md.dt - t0);
+            } else {
+              lpd = (double)(zg[j] - gnew) * md.dt * md.inv_tau2;
+              if (biexp && sh != 0) pr_sh = rise_at(md, rt, tc, t0, gnew) / rise_at(md, rt, tc, t0, zg[j]);
+              if constexpr (F32) lpd += log(pr_sh);
+            }
             if constexpr (MCP) {
               lro = md.mix_lrho[ek[j]];
               rm2o = md.mix_rhom2[ek[j]];
@@ -1009,7 +1104,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
             if (sh == 0 && (!MCP || enew == ek[j])) {
               valid = true;
               dnu = 0.0;
-              la = lpn - lpo;
+              la = 0.0;
             } else {
               need_mv = true;
               need_dp = F32;
@@ -1066,12 +1161,12 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         delta2 = d - (q - ej * ej / om);
         up = beta - (p - ej * xj / om);
         if (delta2 > 0.0 && om > 0.0) {
-          double lom, ld2;
-          group_log2<LPC>(om, delta2, lane, gbase, lom, ld2);
+          double lom, ld2, lpr;
+          group_log3<LPC>(om, delta2, pr_sh, lane, gbase, lom, ld2, lpr);
           dnu = 0.5 * (-lom - ld2 + (up * up / delta2 - xj * xj / om) * md.inv_s);
           // mixture form: the removed and the added PE carry their own rho and rho mu^2
           if constexpr (MCP) dnu += 0.5 * (lrn - lro + (rm2o - rm2n) * md.inv_s);
-          la = dnu + lpn - lpo;
+          la = dnu + (lpd + lpr);
           valid = true;
         } else {
           st |= FSMP_ST_FACTOR;
@@ -1113,7 +1208,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         double lom, ld2;
         group_log2<LPC>(om, delta2, lane, gbase, lom, ld2);
         dnu = 0.5 * (-lom - ld2 + (up * up / delta2 - xj * xj / om) * md.inv_s);
-        la = dnu + lpn - lpo;
+        la = dnu + lpd;
       }
       double b = 0.0;
       if (move != 2) b += 0.5 * fabs(1.0 / delta2 + up * up / (delta2 * delta2 * s)) * Bq + fabs(up) / (delta2 * s) * Bp;
@@ -1407,7 +1502,6 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
             if (KEEPG) bv[N] = beta;
           }
           N++;
-          if (biexp) S_cur += rise_term(md, gnew, t0);
           gmin = gnew < gmin ? gnew : gmin;
         } else if (move == 2) {
           const int last = N - 1;
@@ -1431,7 +1525,6 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
             }
           }
           N--;
-          if (biexp) S_cur -= rise_term(md, gj, t0);
         } else {
           for (int i = lane; i < N; i += LPC) {
             if (i == j) {
@@ -1447,7 +1540,6 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
             if constexpr (MCP) ek[j] = enew;
             if (KEEPG) bv[j] = beta;
           }
-          if (biexp) S_cur += rise_term(md, gnew, t0) - rise_term(md, gj, t0);
         }
         WAVE_SYNC();
         // the corrected FP64 form: the residual of the new x against the new G
@@ -2431,11 +2523,15 @@ __global__ void __launch_bounds__(256) posterior_extra_kernel(PosteriorArgs a) {
 }
 
 template <int KCAP, int LPC, int WPB, bool HG, bool FORCE = false, bool F32 = false, bool MCP = false>
-hipError_t launch_chain_t(const ChainArgs &a, hipStream_t st, int32_t *lanes, int64_t *blocks) {
+hipError_t launch_chain_t(const ChainArgs &args, hipStream_t st, int32_t *lanes, int64_t *blocks) {
   constexpr int CPB = WPB * (kWave / LPC);
+  ChainArgs a = args;
   const int64_t nb = (a.n_list + CPB - 1) / CPB;
-  const size_t lds = sizeof(double) * ((size_t)a.md.M * (1 + a.md.sub) + (KCAP + 2) +
-                                       (size_t)CPB * ChainLayout<KCAP, HG, F32, MCP>::kDoubles);
+  size_t lds = sizeof(double) * ((size_t)a.md.M * (1 + a.md.sub) + (KCAP + 2) +
+                                 (size_t)CPB * ChainLayout<KCAP, HG, F32, MCP>::kDoubles);
+  // the rise table where it fits beside what the host has checked
+  if (lds + sizeof(double) * a.md.rise_n > 160 * 1024) a.md.rise_n = 0;
+  lds += sizeof(double) * a.md.rise_n;
   *lanes = LPC;
   *blocks = nb;
   if (nb == 0) return hipSuccess;
