@@ -18,6 +18,10 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed-FP32 instructions anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # The sweep loops are long and use hundreds of FP64 constants (polynomials of log, exp, sin):
+    # hoisted out of the loop they fill the 256 registers and spill; left in place they are
+    # scalar moves beside the vector work.
+    "-mllvm", "-disable-machine-licm",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

@@ -203,6 +203,7 @@ struct fsmp_ctx {
   DevBuf<double> lane_d;
   DevBuf<int32_t> lane_i;
   DevBuf<double> draw_scr;  // charge draws: KCAP (KCAP + 1) FP64 words per chain
+  DevBuf<double> ovp;       // partial overlap sums (ModelDev::ovp)
   DevBuf<double> ptab;      // light-curve partial-sum factors (ModelDev::ptab)
   // per PE capacity (kCaps), FSMP_DESIGN_*: 0 = lane group per chain, H in LDS
   // (capacities up to 64); 1 = one lane per chain, state in device memory; 2 = lane group
@@ -210,6 +211,7 @@ struct fsmp_ctx {
   // one lane per chain wins at capacity 16 (few PEs, the serial work shared by 64 chains),
   // the device-memory groups everywhere above.
   int design[kNumCaps] = {1, 2, 2, 2, 2, 2, 2, 2};
+  bool design_set[kNumCaps] = {};  // set by fsmp_set_design, the autotuner or the environment
   PinBuf stage;
   hipEvent_t stage_done = nullptr;
   bool stage_pending = false;
@@ -254,11 +256,18 @@ bool finite(double v) { return std::isfinite(v); }
 // with G^-1 in device memory (the FP32 form without capacity 48, which it runs at 64); one
 // lane per chain exists at capacities 16 and 32 (FP64); the wide device-memory groups from
 // capacity 32 up (FP64, single charge law)
+// The LDS kernels in the form of the device-memory ones (corrected from capacity 48 up, to
+// capacity 160): not a design a caller sets, but where routed_design sends a bucket.
+constexpr int kDesignLds = 4;
+static const int64_t kLdsChains[kNumCaps] = {1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30};
+
 bool design_available(const fsmp_ctx *c, int kcap, int design) {
   const bool fp32 = c->cfg.precision == FSMP_FP32_REFRESH;
   const bool mcp = c->cfg.n_mix > 0;
   switch (design) {
-    case FSMP_DESIGN_GROUP: return !fp32 && !mcp && chain_kcap_supported(kcap, c->tab.M, c->cfg.grid_sub);
+    case FSMP_DESIGN_GROUP: return !fp32 && !mcp && chain_lds_supported(kcap, false, c->tab.M, c->cfg.grid_sub);
+    case kDesignLds:
+      return !fp32 && !mcp && chain_lds_supported(kcap, kcap >= 48, c->tab.M, c->cfg.grid_sub);
     case FSMP_DESIGN_LANE: return !fp32 && !mcp && (kcap == 16 || kcap == 32);
     case FSMP_DESIGN_GROUP_DEVMEM: return chain_dm_supported(kcap, c->tab.M, c->cfg.grid_sub, fp32, mcp);
     case FSMP_DESIGN_GROUP_DEVMEM_WIDE:
@@ -272,6 +281,28 @@ bool design_available(const fsmp_ctx *c, int kcap, int design) {
 int effective_design(const fsmp_ctx *c, int kcap, int design) {
   if (design_available(c, kcap, design)) return design;
   return FSMP_DESIGN_GROUP_DEVMEM;
+}
+
+// The kernels a bucket of `cnt` chains runs: the effective design; but where the caller has not
+// set one, or has set the wide device-memory groups, the LDS kernels for as many chains as
+// kLdsChains.
+int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
+  const int dz = effective_design(c, kCaps[q], c->design[q]);
+  if ((!c->design_set[q] || dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE) && cnt <= kLdsChains[q] &&
+      design_available(c, kCaps[q], kDesignLds))
+    return kDesignLds;
+  return dz;
+}
+
+// device-memory doubles of a bucket's chain state in a design
+size_t design_ws_doubles(int kcap, int design, int64_t cnt, bool fp32) {
+  switch (design) {
+    case FSMP_DESIGN_LANE: return lane_ws_doubles(kcap, cnt);
+    case FSMP_DESIGN_GROUP_DEVMEM: return group_dm_ws_doubles(kcap, cnt, fp32);
+    case FSMP_DESIGN_GROUP_DEVMEM_WIDE: return group_dm_ws_doubles(kcap, cnt, fp32, true);
+    case kDesignLds: return lds_ws_doubles(kcap, kcap >= 48, cnt);
+    default: return 0;
+  }
 }
 
 fsmp_status validate_model(const fsmp_ser *ser, const fsmp_intensity *phi, const fsmp_config *cfg, std::string &m) {
@@ -480,7 +511,10 @@ fsmp_status fsmp_create(fsmp_ctx **out, const fsmp_ser *ser, const fsmp_intensit
     for (int q = 0; q < kNumCaps && q < (int)L; ++q) {
       const int want = d[q] == 'g' ? FSMP_DESIGN_GROUP : d[q] == 'l' ? FSMP_DESIGN_LANE
                        : d[q] == 'd' ? FSMP_DESIGN_GROUP_DEVMEM : d[q] == 'w' ? FSMP_DESIGN_GROUP_DEVMEM_WIDE : -1;
-      if (want >= 0 && design_available(c, kCaps[q], want)) c->design[q] = want;
+      if (want >= 0 && design_available(c, kCaps[q], want)) {
+        c->design[q] = want;
+        c->design_set[q] = true;
+      }
     }
   }
   int prev = 0;
@@ -492,7 +526,13 @@ fsmp_status fsmp_create(fsmp_ctx **out, const fsmp_ser *ser, const fsmp_intensit
   if (e == hipSuccess)
     e = hipMemcpy(c->d_ovl, c->tab.ovl.data(), sizeof(double) * c->tab.ovl.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage_done, hipEventDisableTiming);
-  if (e == hipSuccess) e = ensure_ptab(c, 0);
+  const size_t n_ovp = c->tab.ovl.size() * (size_t)(c->tab.LV + 1);
+  if (e == hipSuccess && n_ovp * sizeof(double) <= kMaxOvp) {
+    e = c->ovp.ensure(n_ovp);
+    if (e == hipSuccess) e = launch_overlap_partial(c->d_vtab, c->ovp.p, c->tab.sub, c->tab.M, c->tab.LV, nullptr);
+    c->md.ovp = c->ovp.p;
+  }
+  if (e == hipSuccess) e = ensure_ptab(c, 0);  // (synchronises the device)
   if (e == hipSuccess) {
     // set-up of the allocation-free variant: the device address of its scratch array
     void *sp = nullptr;
@@ -548,6 +588,7 @@ void fsmp_destroy(fsmp_ctx *c) {
   c->lane_d.release();
   c->draw_scr.release();
   c->ptab.release();
+  c->ovp.release();
   c->lane_i.release();
   c->stage.release();
   (void)hipSetDevice(prev);
@@ -579,11 +620,9 @@ size_t fsmp_workspace_bytes(const fsmp_ctx *c, const fsmp_batch *b) {
   // chain state of each bucket in its design; charge-draw scratch; partial-sum table
   for (int q = 0; q < kNumCaps; ++q) {
     if (!cnt[q]) continue;
-    const int dz = effective_design(c, kCaps[q], c->design[q]);
-    if (dz == FSMP_DESIGN_LANE)
-      bytes += lane_ws_doubles(kCaps[q], cnt[q]) * 8 + lane_ws_ints(kCaps[q], cnt[q]) * 4;
-    else if (dz == FSMP_DESIGN_GROUP_DEVMEM || dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE)
-      bytes += group_dm_ws_doubles(kCaps[q], cnt[q], fp32, dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE) * 8;
+    const int dz = routed_design(c, q, cnt[q]);
+    bytes += design_ws_doubles(kCaps[q], dz, cnt[q], fp32) * 8;
+    if (dz == FSMP_DESIGN_LANE) bytes += lane_ws_ints(kCaps[q], cnt[q]) * 4;
     if (cf.record_flags & FSMP_REC_CHARGE) bytes += (size_t)((cnt[q] + 63) / 64 * 64) * kCaps[q] * (kCaps[q] + 1) * 8;
   }
   bytes += (size_t)std::max<int64_t>(tmax + 1, 4 * 4096 + 1) * 16;
@@ -741,11 +780,13 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   int64_t bucket_start[kNumCaps + 1] = {0};
   const bool fp32 = cf.precision == FSMP_FP32_REFRESH;
   auto design_of = [&](int bi) {
-    const int dz = effective_design(c, caps[bi], c->design[bi]);
     // a replay runs the device-memory groups: the wide ones where the context has chosen them
     // at capacity 64 and up, else the narrow ones
-    if (force) return dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE && caps[bi] >= 64 ? dz : FSMP_DESIGN_GROUP_DEVMEM;
-    return dz;
+    if (force) {
+      const int dz = effective_design(c, caps[bi], c->design[bi]);
+      return dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE && caps[bi] >= 64 ? dz : (int)FSMP_DESIGN_GROUP_DEVMEM;
+    }
+    return routed_design(c, bi, bucket_start[bi + 1] - bucket_start[bi]);
   };
   // within a bucket, waveforms with per-waveform sweep counts in 16 bins of the batch's
   // largest count, the longest first, so that the chains of a workgroup end together and the
@@ -824,11 +865,7 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   for (int bi = 0; bi < kNumCaps; ++bi) {
     const int64_t cnt = bucket_start[bi + 1] - bucket_start[bi];
     const int dz = design_of(bi);
-    const size_t dd = dz == FSMP_DESIGN_LANE ? lane_ws_doubles(caps[bi], cnt)
-                      : dz == FSMP_DESIGN_GROUP_DEVMEM ? group_dm_ws_doubles(caps[bi], cnt, fp32)
-                      : dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE ? group_dm_ws_doubles(caps[bi], cnt, fp32, true)
-                                                       : 0;
-    lane_doff[bi + 1] = lane_doff[bi] + dd;
+    lane_doff[bi + 1] = lane_doff[bi] + design_ws_doubles(caps[bi], dz, cnt, fp32);
     lane_ioff[bi + 1] = lane_ioff[bi] + (dz == FSMP_DESIGN_LANE ? lane_ws_ints(caps[bi], cnt) : 0);
   }
   double *d_lane = lane_doff[kNumCaps] > 0 ? carve(c->lane_d, lane_doff[kNumCaps]) : nullptr;
@@ -1035,7 +1072,7 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     bool tuned = true;
     for (int bi = 0; bi < kNumCaps; ++bi)
       if (bucket_start[bi + 1] > bucket_start[bi] &&
-          !(c->tuned_ms[bi] > 0.0 && c->tuned_design[bi] == design_of(bi)))
+          !(c->tuned_ms[bi] > 0.0 && c->tuned_design[bi] == c->design[bi]))
         tuned = false;
     for (int bi = 0; bi < kNumCaps; ++bi) {
       if (tuned) {
@@ -1085,15 +1122,18 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     char name[32];
     const int dz = design_of(bi);
     std::snprintf(name, sizeof name, "%s%s_k%d",
-                  dz == FSMP_DESIGN_LANE ? "chain_lane" : dz == FSMP_DESIGN_GROUP ? "chain_group" : "chain_group_dm",
+                  dz == FSMP_DESIGN_LANE                              ? "chain_lane"
+                  : dz == FSMP_DESIGN_GROUP || dz == kDesignLds ? "chain_group"
+                                                                      : "chain_group_dm",
                   fp32 ? "_fp32" : "", caps[bi]);
-    ca.dws = dz != FSMP_DESIGN_GROUP ? d_lane + lane_doff[bi] : nullptr;
+    ca.dws = lane_doff[bi + 1] > lane_doff[bi] ? d_lane + lane_doff[bi] : nullptr;
     ca.iws = dz == FSMP_DESIGN_LANE ? d_lanei + lane_ioff[bi] : nullptr;
     ca.dscr = ca.qdraw ? d_draw + draw_off[bi] : nullptr;
     e = timed(name, caps[bi], ks, [&](fsmp_timing &t) {
       t.chains = cnt;
       return dz == FSMP_DESIGN_LANE    ? launch_chain_lane(caps[bi], ca, ks, &t.lanes, &t.blocks)
-             : dz == FSMP_DESIGN_GROUP ? launch_chain(caps[bi], ca, ks, &t.lanes, &t.blocks)
+             : dz == FSMP_DESIGN_GROUP ? launch_chain_lds(caps[bi], false, ca, ks, &t.lanes, &t.blocks)
+             : dz == kDesignLds        ? launch_chain_lds(caps[bi], caps[bi] >= 48, ca, ks, &t.lanes, &t.blocks)
                                        : launch_chain_dm(caps[bi], fp32, dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE, ca, ks,
                                                          &t.lanes, &t.blocks);
     });
@@ -1152,6 +1192,7 @@ fsmp_status fsmp_set_design(fsmp_ctx *c, int32_t capacity, int32_t design) {
       continue;
     }
     c->design[q] = design;
+    c->design_set[q] = true;
   }
   if (!any) return fail(c, FSMP_EINVAL, "capacity %d is not one of the kernel capacities", capacity);
   return FSMP_OK;
@@ -1226,7 +1267,10 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   // (side by side, each would also carry what the others take from it)
   c->serial = true;
   int saved_design[kNumCaps];
+  bool saved_set[kNumCaps];
   std::memcpy(saved_design, c->design, sizeof saved_design);
+  std::memcpy(saved_set, c->design_set, sizeof saved_set);
+  for (bool &v : c->design_set) v = true;  // the trials run the designs themselves
   c->cfg.n_steps = tmax;
   c->cfg.burn_in = 0;
   c->cfg.record_flags = 0;
@@ -1251,13 +1295,17 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   c->timing = saved_timing;
   c->serial = false;
   std::memcpy(c->design, saved_design, sizeof saved_design);
+  std::memcpy(c->design_set, saved_set, sizeof saved_set);
   // per capacity the fastest of the designs that ran it
   if (st == FSMP_OK)
     for (int q = 0; q < kNumCaps; ++q) {
       int best = -1;
       for (int d = 0; d < kDesigns; ++d)
         if (ms[d][q] >= 0.0 && (best < 0 || ms[d][q] < ms[best][q])) best = d;
-      if (best >= 0) c->design[q] = best;
+      if (best >= 0) {
+        c->design[q] = best;
+        c->design_set[q] = true;
+      }
       c->tuned_design[q] = best;
       c->tuned_ms[q] = best >= 0 ? ms[best][q] : -1.0;
     }
@@ -1398,6 +1446,7 @@ fsmp_status fsmp_graph_create(fsmp_ctx *c, const fsmp_batch *b, const fsmp_sampl
     return fail(c, st, "graph context: %s", fsmp_last_error(nullptr));
   }
   std::memcpy(g->own->design, c->design, sizeof c->design);
+  std::memcpy(g->own->design_set, c->design_set, sizeof c->design_set);
   hipError_t e = hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
     fsmp_graph_destroy(g);

@@ -34,6 +34,9 @@ struct ModelDev {
   int32_t rise_n;
   int32_t small_dt;    // dt / tau <= 1/4 for every tau of the light curve (t0_terms)
   double Cd2, Cd12;    // C / den2, C / den12 (0 for EXP): the two series summed to infinity
+  // partial sums of the stationary overlaps over the first m samples, [sub][M][LV + 1] (device,
+  // for windows that end inside both columns), or null where the table would exceed kMaxOvp
+  const double *ovp;
   // birth search's first guess, FP32: dt / tau2, its inverse, dt / tau_rise (0 for EXP)
   float ga, ga_inv, gb;
   // MCP-PMT mixture (n_mix > 0): cumulative weights (accumulated in index order) and, per
@@ -171,8 +174,12 @@ hipError_t launch_lucy(const LucyArgs &a, int64_t max_len, hipStream_t st);
 // Launchers (fsmp_kernels.hip).  Each returns hipSuccess or the launch error.
 hipError_t launch_prologue(const PrologueArgs &a, hipStream_t st);
 hipError_t launch_posterior(const PosteriorArgs &a, hipStream_t st);
-// lane-group instances for kcap in {16, 32, 48, 64}; fills lanes per chain and blocks
-hipError_t launch_chain(int kcap, const ChainArgs &a, hipStream_t st, int32_t *lanes, int64_t *blocks);
+// lane groups with H in LDS (FP64, single charge law, no replay); `corr`: the corrected form,
+// capacities 48 and up, whose exact G is in dws (lds_ws_doubles); without it capacities up to 64
+hipError_t launch_chain_lds(int kcap, bool corr, const ChainArgs &a, hipStream_t st, int32_t *lanes,
+                            int64_t *blocks);
+size_t lds_ws_doubles(int kcap, bool corr, int64_t n_list);
+hipError_t launch_overlap_partial(const double *vtab, double *out, int sub, int M, int LV, hipStream_t st);
 // lane-per-chain variant (FP64, capacities 16 and 32); dws / iws must hold lane_ws_doubles /
 // lane_ws_ints(kcap, n_list)
 hipError_t launch_chain_lane(int kcap, const ChainArgs &a, hipStream_t st, int32_t *lanes, int64_t *blocks);
@@ -180,9 +187,10 @@ size_t lane_ws_doubles(int kcap, int64_t n_list);
 size_t lane_ws_ints(int kcap, int64_t n_list);
 // PE capacities of the chain kernels; a waveform runs in the smallest one >= its kmax
 constexpr int kNumCaps = 8;
+constexpr size_t kMaxOvp = 8u << 20;  // bytes of the table of partial overlap sums
 constexpr int kMaxRise = 1024;  // longest rise table (8 KB of LDS beside the overlap tables)
 constexpr int kCaps[kNumCaps] = {16, 32, 48, 64, 96, 128, 160, 192};
-bool chain_kcap_supported(int kcap, int M, int sub);  // lane-group (LDS) instance exists and fits
+bool chain_lds_supported(int kcap, bool corr, int M, int sub);  // the LDS instance exists and fits
 // lane groups with H in device memory (FP64, or FP32 in the precision form; `wide`: the
 // wider groups, FP64 sampling with the single charge law only): dws must hold
 // group_dm_ws_doubles(kcap, n_list, fp32, wide)

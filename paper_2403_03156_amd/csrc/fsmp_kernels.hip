@@ -235,8 +235,17 @@ __device__ inline double one_minus_exp_small(double y) {
 // q1 = 1 - e^{-(g0 dt - t0) / tau_rise}.
 struct T0Terms {
   double e2, e12, q1, Phi;
+  double p2, p12;  // the count-dependent factors at n (md.ptab), loaded before Phi is formed
   int g0, gs, n;
 };
+
+// Phi of a t0's terms: apart from them, so that the loads of its two factors overlap with the
+// work in between
+__device__ inline void t0_phi(const ModelDev &md, T0Terms &t) {
+  const double a = t.e2 * t.p2;
+  const double v = md.kind == FSMP_PHI_EXP ? a * md.inv_tau2 : md.C * (a - t.e12 * t.p12);
+  t.Phi = t.n > 0 ? v : 0.0;
+}
 
 // T0Terms for a chain's lane group (t0, glo <= ghi the same in all its lanes, every lane
 // active).  The distance g0 dt - t0 is below one grid step, so with dt / tau <= 1/4 all three
@@ -251,6 +260,9 @@ __device__ inline T0Terms t0_terms(const ModelDev &md, double t0, int glo, int g
   t.g0 = (int)fmin(fmax(gd, -1073741824.0), 1073741824.0);
   t.gs = t.g0 < glo ? glo : t.g0;
   t.n = ghi - t.gs + 1;
+  const double *pt = md.ptab + 2 * (t.n > 0 ? t.n : 0);
+  t.p2 = pt[0];
+  t.p12 = pt[1];
   const double f = (double)t.g0 * md.dt - t0;
   const double y = f * (lane == 0 ? md.inv_tau2 : lane == 1 ? md.inv_tau12 : md.inv_tau1);
   double v, e;
@@ -265,7 +277,6 @@ __device__ inline T0Terms t0_terms(const ModelDev &md, double t0, int glo, int g
   t.e2 = group_bcast<W, 0>(e, base);
   t.e12 = md.kind == FSMP_PHI_EXP ? 0.0 : group_bcast<W, 1>(e, base);
   t.q1 = group_bcast<W, 2>(v, base);
-  t.Phi = t.n > 0 ? phi_partial(md, XsExp{t.e2, t.e12}, t.n) : 0.0;
   return t;
 }
 
@@ -821,8 +832,11 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
   int N = 0;
   // the light curve's terms at t0; Lambda_T changes only with t0 (its log is taken with the
   // jump's own log); gmin = the smallest PE grid index (phi must stay positive at every PE)
-  T0Terms tc{0.0, 0.0, 0.0, 0.0, 0, 0, 0};
-  if (glo <= ghi) tc = t0_terms<LPC>(md, t0, glo, ghi, lane, gbase);
+  T0Terms tc{};
+  if (glo <= ghi) {
+    tc = t0_terms<LPC>(md, t0, glo, ghi, lane, gbase);
+    t0_phi(md, tc);
+  }
   double Lam = lam * md.dt * tc.Phi;
   const bool biexp = md.kind == FSMP_PHI_BIEXP;
   int gmin = INT32_MAX;
@@ -970,7 +984,10 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       t0acc = (rec.flags & 4) != 0;
       if (rec.t0 != t0) {
         t0 = rec.t0;
-        if (glo <= ghi) tc = t0_terms<LPC>(md, t0, glo, ghi, lane, gbase);
+        if (glo <= ghi) {
+          tc = t0_terms<LPC>(md, t0, glo, ghi, lane, gbase);
+          t0_phi(md, tc);
+        }
         Lam = lam * md.dt * tc.Phi;
       }
     } else if (t0p >= md.t0_min && t0p <= md.t0_max) {
@@ -997,6 +1014,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
           S += log(pn / pc);
           S = group_sum<LPC>(S);
         }
+        if (glo <= ghi) t0_phi(md, tp);
         const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
         const double la0 = part - (lam * md.dt * tp.Phi - lam * md.dt * tc.Phi);
         if (lg2 < la0) {
@@ -1690,6 +1708,868 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
   }
 }
 
+
+// ------------------------------------------------------------------ chains, G^-1 in LDS
+// The LDS design: one chain per group of LPC lanes, each lane one element of the vectors (a
+// whole wavefront at capacities 48 and 64, a workgroup of two or three above), with G^-1, the
+// vectors and the PE list in LDS.  A sweep of the device-memory groups waits for
+// 10-40 dependent memory round trips (the columns of G^-1 in chunks, then their edits); here an
+// element costs an LDS read, and no more chains than the LDS holds are in flight, so this is the
+// design for batches that do not fill the chip with the other ones: a sweep's latency, not the
+// chip's throughput, then sets the time.
+//
+// Capacities up to 48 keep G^-1 full.  From 64 up the symmetric matrix is kept once, by wrapped
+// diagonals: row d (0 .. KCAP / 2) holds the elements (i, (i + d) mod KCAP) at column i, so that
+// consecutive lanes read consecutive words whichever triangle an element is in (a packed
+// triangle would scatter them over the banks); the last row holds every element twice.  That
+// halves the LDS a chain takes (the chains in flight) and the words an edit writes.
+//
+// Elements at and past N of the vectors are kept zero and the matrices start zeroed, so products
+// run over whole chunks without selects.
+//
+// CORR, the corrected FP64 form (capacities from 48 up, see ChainLayout), keeps its exact G in
+// device memory and reads it once per accepted move, for the residual.  (Taking its elements
+// from the overlap table in LDS instead was slower: 27.7 -> 36.5 ms for 873 chains of 500 sweeps
+// at capacity 128; the lanes' gathers conflict.)
+constexpr int kLdsWaves = 8;  // wavefronts of a workgroup at most
+template <int KCAP, int LPC, bool CORR>
+struct LdsLayout {
+  static constexpr bool kSym = KCAP >= 64;
+  static constexpr int kW = LPC > kWave ? LPC / kWave : 1;  // wavefronts of a chain
+  static constexpr int kMat = kSym ? (KCAP / 2 + 1) * KCAP : KCAP * KCAP;
+  static constexpr int kVec = kSym ? 2 * KCAP : KCAP;  // the two scratch vectors (twice in a row when wrapped)
+  static constexpr int kStash = LPC >= kWave ? 0 : 6;  // random values per lane (registers from a wavefront up)
+  static constexpr int kRed = LPC > kWave ? 2 * (3 * kW + 1) : 0;  // partial sums of the wavefronts, two sets
+  // matrix, two scratch vectors, x (b and the residual too in the corrected form), the PE list,
+  // the random values of the next LPC sweeps, the wavefronts' partial sums
+  static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 + kStash * LPC + kRed;
+};
+
+// the overlap of two columns, as overlap(), with the window-edge sums from the table of partial
+// sums ovp where the model has one (else from the response in device memory)
+__device__ inline double overlap_edge(const ModelDev &md, const double *vtab, const double *ov, int g1, int g2,
+                                      int Lw) {
+  const int lo = g1 < g2 ? g1 : g2, hi = g1 < g2 ? g2 : g1;
+  const int d = hi - lo;
+  if (d >= md.M) return 0.0;
+  const int nhi = sub_div(md, lo + md.M - 1);  // last sample of the earlier column
+  const int p = sub_mod(md, lo);
+  if (nhi < Lw) return ov[p * md.M + d];
+  const int n0 = sub_div(md, hi + md.sub - 1);
+  if (md.ovp) {
+    const int m = Lw - n0;
+    return m > 0 ? md.ovp[((int64_t)p * md.M + d) * (md.LV + 1) + m] : 0.0;
+  }
+  double s = 0.0;
+  for (int n = n0; n < Lw; ++n) s += vtab[md.sub * n - lo] * vtab[md.sub * n - hi];
+  return s;
+}
+
+// partial sums of the stationary overlaps, [sub][M][LV + 1]: entry m sums the first m samples
+// that both columns see (in increasing order, as the direct sum)
+__global__ void __launch_bounds__(256) overlap_partial_kernel(const double *vtab, double *out, int sub, int M, int LV) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= sub * M) return;
+  const int p = t / M, d = t % M;
+  const int n0 = (p + d + sub - 1) / sub, n1 = (p + M - 1) / sub;
+  double *row = out + (int64_t)t * (LV + 1);
+  double s = 0.0;
+  row[0] = 0.0;
+  for (int m = 1; m <= LV; ++m) {
+    const int n = n0 + m - 1;
+    if (n <= n1) s += vtab[sub * n - p] * vtab[sub * n - (p + d)];
+    row[m] = s;
+  }
+}
+
+// element (a, b) of the matrix at D
+template <int KCAP, bool SYM>
+__device__ inline int lds_at(int a, int b) {
+  if constexpr (SYM) {
+    int d = b - a;
+    d = d < 0 ? d + KCAP : d;
+    return d <= KCAP / 2 ? d * KCAP + a : (KCAP - d) * KCAP + b;
+  } else {
+    return a * KCAP + b;
+  }
+}
+template <int KCAP, bool SYM>
+__device__ inline void lds_set(double *D, int a, int b, double v) {
+  if constexpr (SYM) {
+    D[lds_at<KCAP, true>(a, b)] = v;
+    const int d = b - a;
+    if (d == KCAP / 2 || d == -KCAP / 2) D[KCAP / 2 * KCAP + b] = v;
+    if (d == KCAP / 2 || d == -KCAP / 2) D[KCAP / 2 * KCAP + a] = v;
+  } else {
+    D[a * KCAP + b] = v;
+    D[b * KCAP + a] = v;
+  }
+}
+
+// element i of a scratch vector (both copies when wrapped)
+template <int KCAP, bool SYM>
+__device__ inline void lds_vec(double *v, int i, double x) {
+  v[i] = x;
+  if constexpr (SYM) v[i + KCAP] = x;
+}
+
+// element i (< KCAP) of H v for the leading N x N block; v zero from N on
+template <int KCAP, bool SYM>
+__device__ inline double lds_dot(const double *D, const double *v, int i, int N) {
+  double e = 0.0;
+  if constexpr (SYM) {
+    const int dm = N - 1 < KCAP / 2 - 1 ? N - 1 : KCAP / 2 - 1;
+    e = D[i] * v[i];  // the diagonal; then the two triangles, each a chain of its own
+    double e1 = 0.0;
+    for (int d0 = 0; d0 <= dm; d0 += 8) {
+      double h0[8], h1[8], v0[8], v1[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int d = d0 + u;
+        h0[u] = D[d * KCAP + i];
+        v0[u] = v[i + d];
+        h1[u] = D[d * KCAP + i - d + (d > i ? KCAP : 0)];
+        v1[u] = v[i - d + KCAP];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (u > 0) e = fma(h0[u], v0[u], e);
+        else e = d0 > 0 ? fma(h0[u], v0[u], e) : e;
+        if (u > 0) e1 = fma(h1[u], v1[u], e1);
+        else e1 = d0 > 0 ? fma(h1[u], v1[u], e1) : e1;
+      }
+    }
+    e += e1;
+    if (N > KCAP / 2) e = fma(D[KCAP / 2 * KCAP + i], v[i + KCAP / 2], e);
+  } else {
+    for (int k0 = 0; k0 < N; k0 += 8) {
+      double h[8], g[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        h[u] = D[(k0 + u) * KCAP + i];
+        g[u] = v[k0 + u];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) e = fma(h[u], g[u], e);
+    }
+  }
+  return e;
+}
+
+// H += cui u u^T row i [+ cvi v v^T], element i's share (i < N; u, v zero from N on)
+template <int KCAP, bool SYM, bool TWO>
+__device__ inline void lds_edit(double *D, const double *u, const double *v, double cui, double cvi, int i, int N) {
+  if constexpr (SYM) {
+    const int dm = N - 1 < KCAP / 2 - 1 ? N - 1 : KCAP / 2 - 1;
+    for (int d0 = 0; d0 <= dm; d0 += 8) {
+      double h[8], a[8], b[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        h[q] = D[(d0 + q) * KCAP + i];
+        a[q] = u[i + d0 + q];
+        if (TWO) b[q] = v[i + d0 + q];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        double x = fma(cui, a[q], h[q]);
+        if (TWO) x = fma(cvi, b[q], x);
+        D[(d0 + q) * KCAP + i] = x;
+      }
+    }
+    if (N > KCAP / 2) {
+      double x = fma(cui, u[i + KCAP / 2], D[KCAP / 2 * KCAP + i]);
+      if (TWO) x = fma(cvi, v[i + KCAP / 2], x);
+      D[KCAP / 2 * KCAP + i] = x;
+    }
+  } else {
+    for (int k0 = 0; k0 < N; k0 += 8) {
+      double h[8], a[8], b[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        h[q] = D[(k0 + q) * KCAP + i];
+        a[q] = u[k0 + q];
+        if (TWO) b[q] = v[k0 + q];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        double x = fma(cui, a[q], h[q]);
+        if (TWO) x = fma(cvi, b[q], x);
+        D[(k0 + q) * KCAP + i] = x;
+      }
+    }
+  }
+}
+
+// a value that is the same in the lanes of a chain's group, as a scalar where the group is a
+// whole wavefront (branches on it then are scalar branches)
+template <int LPC>
+__device__ inline int group_uniform(int v) {
+  if constexpr (LPC >= kWave) return __builtin_amdgcn_readfirstlane(v);
+  else return v;
+}
+
+// LDS written by a chain's lanes becomes visible to all of them (one wavefront or less: the LDS
+// runs its instructions in order; several: a barrier that waits for LDS traffic only, so that
+// loads from device memory stay in flight across it)
+template <int LPC>
+__device__ inline void chain_sync() {
+  if constexpr (LPC > kWave) {
+#if defined(__AMDGCN__)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+#else
+    __syncthreads();
+#endif
+  } else {
+    WAVE_SYNC();
+  }
+}
+
+// the same for device memory too
+template <int LPC>
+__device__ inline void chain_sync_mem() {
+  if constexpr (LPC > kWave) __syncthreads();
+  else WAVE_SYNC();
+}
+
+// Sums of NV values over a chain's lanes, and the value x of lane j (j < 0: none).  Over several
+// wavefronts: each wavefront's sums and x go to one of two sets in `red` (used in turn, so one
+// barrier per use is enough), which every lane adds up in the same order.  All LDS written
+// before the call is visible after it.
+template <int LPC, int NV>
+__device__ inline void chain_sums(double (&v)[NV], double &x, int j, int lane, int base, double *red, int &turn) {
+  if constexpr (LPC > kWave) {
+    constexpr int W = LPC / kWave;
+    double *r = red + turn * (3 * W + 1);
+    turn ^= 1;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = group_sum<kWave>(v[q]);
+    if ((lane & (kWave - 1)) == 0)
+#pragma unroll
+      for (int q = 0; q < NV; ++q) r[3 * (lane / kWave) + q] = v[q];
+    if (lane == j) r[3 * W] = x;
+    chain_sync<LPC>();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      double t = r[q];
+#pragma unroll
+      for (int w = 1; w < W; ++w) t += r[3 * w + q];
+      v[q] = t;
+    }
+    x = r[3 * W];
+  } else {
+    WAVE_SYNC();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = group_sum<LPC>(v[q]);
+    if constexpr (LPC == kWave) x = lane_value(x, j < 0 ? 0 : j);
+    else x = __shfl(x, base + (j < 0 ? 0 : j), kWave);
+  }
+}
+
+// G^-1 of the PE list zl[0..N) by bordering into the (finite) matrix D, each step the birth
+// update of the inverse of the leading block; va, vb: the scratch vectors.  False if a Schur
+// complement is not positive.
+template <int KCAP, int LPC, bool SYM>
+__device__ bool lds_build(const ModelDev &md, const double *vtab, const double *ov, int Lw, double *D, double *va,
+                          double *vb, const int *zl, int N, int lane, int base, double *red, int &turn) {
+  for (int k = 0; k < N; ++k) {
+    const int gk = zl[k];
+    for (int i = lane; i < KCAP; i += LPC)
+      lds_vec<KCAP, SYM>(va, i, i < k ? overlap_edge(md, vtab, ov, gk, zl[i], Lw) : 0.0);
+    const double d = overlap_edge(md, vtab, ov, gk, gk, Lw) + md.rho;
+    chain_sync<LPC>();
+    double q[1] = {0.0}, none = 0.0;
+    for (int i = lane; i < KCAP; i += LPC) {
+      const double e = i < k ? lds_dot<KCAP, SYM>(D, va, i, k) : 0.0;
+      q[0] += va[i] * e;
+      lds_vec<KCAP, SYM>(vb, i, e);
+    }
+    chain_sums<LPC, 1>(q, none, -1, lane, base, red, turn);
+    const double delta2 = d - q[0];
+    if (!(delta2 > 0.0)) return false;
+    const double inv = 1.0 / delta2;
+    for (int i = lane; i < k; i += LPC) lds_edit<KCAP, SYM, false>(D, vb, vb, vb[i] * inv, 0.0, i, k);
+    chain_sync<LPC>();
+    for (int i = lane; i < k; i += LPC) lds_set<KCAP, SYM>(D, k, i, -vb[i] * inv);
+    if (lane == 0) lds_set<KCAP, SYM>(D, k, k, inv);
+    chain_sync<LPC>();
+  }
+  return true;
+}
+
+// The Gibbs / RJMCMC chains of chain_kernel (the same moves, acceptances and random numbers;
+// FP64, single charge law) with G^-1 in LDS.
+template <int KCAP, int LPC, bool CORR>
+__global__ void __launch_bounds__(kLdsWaves *kWave) __attribute__((amdgpu_waves_per_eu(2)))
+chain_lds_kernel(ChainArgs a) {
+  using CL = LdsLayout<KCAP, LPC, CORR>;
+  constexpr bool SYM = CL::kSym;
+  constexpr int W = CL::kW, CPW = LPC < kWave ? kWave / LPC : 1;
+  static_assert(LPC >= 16 && LPC >= KCAP, "one element of the vectors per lane");
+  extern __shared__ double smem[];
+  const ModelDev &md = a.md;
+  // the overlap table in LDS where the wavefronts of a workgroup share it, in device memory (a
+  // few reads per sweep, from the caches) where a workgroup is one chain: the LDS then holds
+  // two chains of capacity 128 per CU
+  constexpr bool OVL = W == 1;
+  double *ovl = smem;
+  double *rt = smem + (OVL ? md.sub * md.M : 0);
+  double *lgn = rt + md.rise_n;
+  if constexpr (OVL)
+    for (int i = threadIdx.x; i < md.sub * md.M; i += blockDim.x) ovl[i] = a.ovl[i];
+  const double *ov = OVL ? ovl : a.ovl;
+  for (int i = threadIdx.x; i < md.rise_n; i += blockDim.x) rt[i] = md.rtab[i];
+  for (int i = threadIdx.x; i < KCAP + 2; i += blockDim.x) lgn[i] = log((double)i);
+  __syncthreads();
+  // lane: the index in the chain's group (its element of the vectors); l64 in the wavefront
+  // (gl in the part of a wavefront that the group is)
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), l64 = threadIdx.x % kWave;
+  const int grp = LPC < kWave ? l64 / LPC : 0, gbase = grp * LPC;
+  const int lane = W > 1 ? (int)threadIdx.x : l64 % LPC, gl = W > 1 ? l64 : lane;
+  constexpr int GW = LPC < kWave ? LPC : kWave;  // lanes that share the per-chain scalars' work
+  const int64_t slot = W > 1 ? (int64_t)blockIdx.x : ((int64_t)blockIdx.x * (blockDim.x / kWave) + wv) * CPW + grp;
+  if (slot >= a.n_list) return;
+  double *D = lgn + (KCAP + 2) + (W > 1 ? 0 : (int64_t)(wv * CPW + grp) * CL::kDoubles);
+  double *va = D + CL::kMat, *vb = va + CL::kVec, *xl = vb + CL::kVec;
+  double *bl = CORR ? xl + KCAP : nullptr, *sl = CORR ? bl + KCAP : nullptr;
+  int *zl = (int *)(xl + (CORR ? 3 : 1) * KCAP);
+  double *stash = (double *)(zl + 2 * ((KCAP + 1) / 2));
+  double *red = stash;  // (the groups wider than a wavefront have no stash)
+  int turn = 0;
+  double *Gm = CORR ? a.dws + slot * (int64_t)(KCAP * KCAP) : nullptr;
+
+  const int64_t c = a.chains[slot];
+  const int64_t w = c / a.n_chains;
+  const int Lw = (int)(a.woff[w + 1] - a.woff[w]);
+  const double lam = a.lam[w];
+  const int kmax = a.kmax[w];
+  const int glo = a.grange[2 * w], ghi = a.grange[2 * w + 1];
+  const double *mf = a.mf + a.mfoff[w];
+  const uint64_t uid = a.wid[w] * (uint64_t)a.n_chains + (uint64_t)(c % a.n_chains);
+  const uint32_t uid0 = (uint32_t)uid, uid1 = (uint32_t)(uid >> 32);
+  uint32_t st = a.wflags[w];
+  if (glo > ghi) st |= FSMP_ST_EMPTY_T;
+  const int steps_w = a.wsteps ? a.wsteps[w] : a.n_steps;
+  const int burn = a.wsteps ? (int)((int64_t)steps_w * a.burn_in / a.n_steps) : a.burn_in;
+  const int n_steps = (st & FSMP_ST_NONFINITE) ? 0 : steps_w;
+  const int S_rec = n_steps > burn ? n_steps - burn : 0;
+  const int nb = S_rec > 0 ? (int)floor(sqrt((double)S_rec)) : 0;
+  const int lb = nb > 0 ? S_rec / nb : 0;
+
+  for (int k = lane; k <= a.kz; k += LPC) a.nhist[c * (a.kz + 1) + k] = 0;
+  for (int k = lane; k < CL::kMat + 2 * CL::kVec + (CORR ? 3 : 1) * KCAP; k += LPC) D[k] = 0.0;
+  for (int k = lane; k < KCAP; k += LPC) zl[k] = 0;
+  if constexpr (CORR)
+    for (int k = lane; k < KCAP * KCAP; k += LPC) Gm[k] = 0.0;
+  chain_sync_mem<LPC>();
+
+  double t0 = a.t0init[w];
+  int N = 0;
+  T0Terms tc{};
+  if (glo <= ghi) {
+    tc = t0_terms<GW>(md, t0, glo, ghi, gl, gbase);
+    t0_phi(md, tc);
+  }
+  double Lam = lam * md.dt * tc.Phi;
+  const bool biexp = md.kind == FSMP_PHI_BIEXP;
+  int gmin = INT32_MAX;  // smallest PE grid index
+  double Q = 0.0;        // sum of the charge means, changes with accepted moves only
+
+  // s = b - G x against the exact G (corrected form), and Q: rows in chunks of 16, the loads of a
+  // chunk in flight together (rows and elements past N are zero or meet a zero x)
+  auto residual = [&]() {
+    double r = 0.0;
+    if constexpr (CORR) {
+      const double *gp = Gm + (KCAP % LPC && lane >= KCAP ? KCAP - 1 : lane);
+      for (int k0 = 0; k0 < N; k0 += 16) {
+        double g[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) g[u] = gp[(k0 + u) * KCAP];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) r = fma(g[u], xl[k0 + u], r);
+      }
+      if (KCAP % LPC == 0 || lane < KCAP) sl[lane] = lane < N ? bl[lane] - r : 0.0;
+    }
+    double qs[1] = {lane < N ? xl[lane] : 0.0}, none = 0.0;
+    chain_sums<LPC, 1>(qs, none, -1, lane, gbase, red, turn);
+    Q = qs[0];
+  };
+
+  // a caller-supplied initial PE list: G^-1 and x = G^-1 b of the list before the first sweep
+  if (a.zinit && n_steps > 0) {
+    const int n0 = (int)(a.zinit_off[c + 1] - a.zinit_off[c]);
+    if (n0 > 0) {
+      const int32_t *z0 = a.zinit + a.zinit_off[c];
+      if (lane < n0) zl[lane] = z0[lane];
+      chain_sync<LPC>();
+      if (lds_build<KCAP, LPC, SYM>(md, a.vtab, ov, Lw, D, va, vb, zl, n0, lane, gbase, red, turn)) {
+        const double b = lane < n0 ? mf[zl[lane] - glo] + md.rhom : 0.0;
+        if (KCAP % LPC == 0 || lane < KCAP) lds_vec<KCAP, SYM>(va, lane, b);
+        chain_sync<LPC>();
+        if (lane < n0) {
+          xl[lane] = lds_dot<KCAP, SYM>(D, va, lane, n0);
+          if constexpr (CORR) {
+            bl[lane] = b;
+            for (int k = 0; k < n0; ++k)
+              Gm[k * KCAP + lane] = overlap_edge(md, a.vtab, ov, zl[k], zl[lane], Lw) + (k == lane ? md.rho : 0.0);
+          }
+          occ_edit(a, c, 1, -1, zl[lane], 0, burn, n_steps);
+        }
+        N = n0;
+        for (int k = 0; k < n0; ++k) gmin = zl[k] < gmin ? zl[k] : gmin;
+        chain_sync<LPC>();
+        residual();
+      } else {
+        st |= FSMP_ST_FACTOR;
+      }
+      chain_sync<LPC>();
+    }
+  }
+
+  // the accumulators live in the group's first lanes: lanes 0, 1, 2 the sums of N, Q, t0 (sum,
+  // sum of squares, open batch sum, sum and sum of squares of the closed ones); lanes 0 .. 3 the
+  // proposals and accepts of t0, birth, death, update.  work: the counters, LDS-free, lane 0
+  double a_s = 0.0, a_q = 0.0, a_b = 0.0, a_bs = 0.0, a_bq = 0.0;
+  int c_p = 0, c_a = 0;
+  double wk0 = 0.0, wk1 = 0.0, wk2 = 0.0, wk3 = 0.0;
+  int run_n = -1, run_s = 0;  // N of the current run among the recorded steps, its first step
+  int b_left = lb, in_batch = nb * lb;
+  int ref_left = a.refresh_M;
+  uint32_t st_r3 = 0, st_r4 = 0, st_r5 = 0;
+  double st_l2 = 0.0, st_l6 = 0.0, st_xt = 0.0, st_xs = 0.0;
+
+  for (int step = 0; step < n_steps; ++step) {
+    if constexpr (!CORR) {
+      // G^-1 rebuilt and x = G^-1 b recomputed every refresh_M sweeps, against the rounding the
+      // edits accumulate (the corrected form needs none)
+      if (a.refresh_M > 0) {
+        if (ref_left == 0) {
+          ref_left = a.refresh_M;
+          if (N > 0) {
+            if (lds_build<KCAP, LPC, SYM>(md, a.vtab, ov, Lw, D, va, vb, zl, N, lane, gbase, red, turn)) {
+              if (KCAP % LPC == 0 || lane < KCAP)
+                lds_vec<KCAP, SYM>(va, lane, lane < N ? mf[zl[lane] - glo] + md.rhom : 0.0);
+              chain_sync<LPC>();
+              if (lane < N) xl[lane] = lds_dot<KCAP, SYM>(D, va, lane, N);
+              residual();
+            } else {
+              st |= FSMP_ST_FACTOR;
+            }
+          }
+        }
+        --ref_left;
+      }
+    }
+    // ---- random values: every GW sweeps each lane makes those of one of the next GW (both
+    // Philox blocks, the three logs, the Box-Muller pair); a sweep reads its own, from lane
+    // registers from a wavefront per chain up, else from LDS
+    const int sl_ = step & (GW - 1);
+    if (sl_ == 0) {
+      uint32_t q0[4], q1[4];
+      philox4x32_10((uint32_t)(step + gl), 0u, uid0, uid1, a.key0, a.key1, q0);
+      philox4x32_10((uint32_t)(step + gl), 1u, uid0, uid1, a.key0, a.key1, q1);
+      const double R = sqrt(-2.0 * log(u01(q0[0])));
+      const double th = 2.0 * M_PI * u01(q0[1]);
+      st_xt = R * cos(th);
+      st_xs = R * sin(th);
+      st_l2 = log(u01(q0[2]));
+      st_l6 = log(u01(q1[2]));
+      st_r3 = q0[3];
+      st_r4 = q1[0];
+      st_r5 = q1[1];
+      if constexpr (LPC < kWave) {
+        WAVE_SYNC();
+        double *q = stash + lane * 6;
+        q[0] = st_xt;
+        q[1] = st_xs;
+        q[2] = st_l2;
+        q[3] = st_l6;
+        ((uint32_t *)q)[8] = st_r3;
+        ((uint32_t *)q)[9] = st_r4;
+        ((uint32_t *)q)[10] = st_r5;
+        WAVE_SYNC();
+      }
+    }
+    uint32_t r3, r4, r5;
+    double lg2, lg6, xi_t0, xi_sh;
+    if constexpr (LPC >= kWave) {
+      r3 = (uint32_t)__builtin_amdgcn_readlane((int)st_r3, sl_);
+      r4 = (uint32_t)__builtin_amdgcn_readlane((int)st_r4, sl_);
+      r5 = (uint32_t)__builtin_amdgcn_readlane((int)st_r5, sl_);
+      lg2 = lane_value(st_l2, sl_);
+      lg6 = lane_value(st_l6, sl_);
+      xi_t0 = lane_value(st_xt, sl_);
+      xi_sh = lane_value(st_xs, sl_);
+    } else {
+      const double *q = stash + sl_ * 6;
+      xi_t0 = q[0];
+      xi_sh = q[1];
+      lg2 = q[2];
+      lg6 = q[3];
+      r3 = ((const uint32_t *)q)[8];
+      r4 = ((const uint32_t *)q)[9];
+      r5 = ((const uint32_t *)q)[10];
+    }
+
+    // ---- Gibbs half-step 1: t0 by Metropolis-Hastings
+    const double t0p = t0 + md.t0_sd * xi_t0;
+    bool t0acc = false;
+    if (t0p >= md.t0_min && t0p <= md.t0_max) {
+      const double xmin = (N > 0) ? (double)gmin * md.dt - t0p : 1.0;
+      if (biexp ? (xmin > 0.0) : (xmin >= 0.0)) {
+        T0Terms tp = tc;
+        if (glo <= ghi) tp = t0_terms<GW>(md, t0p, glo, ghi, gl, gbase);
+        double S = 0.0;  // sum over the PEs of log r(t0p) / r(t0), r the rise factor
+        if (biexp && N > 0) {
+          double ratio = 1.0;
+          if (lane < N) {
+            const int g = zl[lane];
+            ratio = rise_at(md, rt, tp, t0p, g) / rise_at(md, rt, tc, t0, g);
+          }
+          double v[1] = {log(ratio)}, none = 0.0;
+          chain_sums<LPC, 1>(v, none, -1, lane, gbase, red, turn);
+          S = v[0];
+        }
+        if (glo <= ghi) t0_phi(md, tp);
+        const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
+        const double la0 = part - (lam * md.dt * tp.Phi - lam * md.dt * tc.Phi);
+        if (lg2 < la0) {
+          t0 = t0p;
+          tc = tp;
+          Lam = lam * md.dt * tc.Phi;
+          t0acc = true;
+        }
+      }
+    }
+
+    // ---- Gibbs half-step 2: one RJMCMC jump
+    const double um = u01(r3);
+    const int move = group_uniform<LPC>((N == 0 || um < md.J) ? 1 : (um < 2.0 * md.J ? 2 : 3));
+    int j = -1, gnew = -1, sh = 0;
+    bool valid = false, need_mv = false;
+    double dnu = 0.0, la = -INFINITY, lpd = 0.0, pr_sh = 1.0;
+    if (move == 1) {
+      if (N >= kmax) {
+        st |= FSMP_ST_KMAX;
+      } else if (tc.Phi > 0.0) {
+        gnew = birth_draw<GW>(md, tc, u53(r4, r5) * tc.Phi, gl, grp);
+        need_mv = Lam > 0.0;
+      }
+    } else {
+      j = group_uniform<LPC>((int)(((uint64_t)r4 * (uint64_t)N) >> 32));
+      if (move == 3) {
+        const int gj = zl[j];
+        sh = (int)rint(xi_sh * md.shift_sd / md.dt);
+        gnew = gj + sh;
+        const double xnew = (double)gnew * md.dt - t0;
+        if (gnew >= glo && gnew <= ghi && (biexp ? xnew > 0.0 : xnew >= 0.0)) {
+          if (sh == 0) {
+            valid = true;
+            la = 0.0;
+          } else {
+            lpd = (double)(gj - gnew) * md.dt * md.inv_tau2;
+            if (biexp) pr_sh = rise_at(md, rt, tc, t0, gnew) / rise_at(md, rt, tc, t0, gj);
+            need_mv = true;
+          }
+        }
+      }
+    }
+    // birth or shift: gamma = overlaps of the new position with the PEs (zero at the shifted one)
+    // in va, eta = H gamma; death or shift: h = row j of H
+    double eta = 0.0, hj = 0.0;
+    double delta2 = 1.0, up = 0.0, om = 1.0, xj = 0.0, xjp = 0.0, ej = 0.0, beta = 0.0;
+    double inv_om = 0.0, inv_d2 = 0.0;
+    const bool removes = move == 2 || (move == 3 && need_mv);
+    double mfv = 0.0, gam = 0.0;
+    if (need_mv) {
+      mfv = mf[gnew - glo];
+      if (lane < N && lane != j) gam = overlap_edge(md, a.vtab, ov, gnew, zl[lane], Lw);
+      if (KCAP % LPC == 0 || lane < KCAP) lds_vec<KCAP, SYM>(va, lane, gam);
+    }
+    if (removes) {
+      if (lane < N) hj = D[lds_at<KCAP, SYM>(j, lane)];
+      xj = xjp = xl[j];
+      double xc[1] = {0.0};
+      om = hj;
+      if constexpr (CORR) {
+        if (lane < N) xc[0] = hj * sl[lane];
+      }
+      chain_sums<LPC, 1>(xc, om, j, lane, gbase, red, turn);
+      if constexpr (CORR) xj += xc[0];
+      inv_om = 1.0 / om;
+    } else if (need_mv) {
+      chain_sync<LPC>();
+    }
+    if (need_mv) {
+      const double d = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + md.rho;
+      double v[2] = {0.0, 0.0};
+      if (lane < N) {
+        eta = lds_dot<KCAP, SYM>(D, va, lane, N);
+        v[0] = gam * eta;
+        v[1] = gam * xl[lane];
+        if constexpr (CORR) v[1] += eta * sl[lane];
+      }
+      ej = eta;
+      chain_sums<LPC, 2>(v, ej, j, lane, gbase, red, turn);
+      if (move == 3) {
+        v[0] -= ej * ej * inv_om;
+        v[1] -= ej * xj * inv_om;
+      }
+      beta = mfv + md.rhom;
+      delta2 = d - v[0];
+      up = beta - v[1];
+      inv_d2 = 1.0 / delta2;
+    }
+    if (need_mv || move == 2) {
+      if (delta2 > 0.0 && om > 0.0) {
+        // birth: log delta^2, log Lambda; death: log omega, log Lambda; shift: log omega, log
+        // delta^2 and the log of the rise factors' ratio
+        double l0, l1, l2;
+        group_log3<GW>(move == 1 ? delta2 : om, move == 3 ? delta2 : Lam, pr_sh, gl, gbase, l0, l1, l2);
+        if (move == 1) {
+          dnu = -0.5 * (-md.log_rho + l0 + (md.rhom2 - up * up * inv_d2) * md.inv_s);
+          la = dnu + l1 - lgn[N + 1] + (N == 0 ? md.logJ : 0.0);
+        } else if (move == 2) {
+          dnu = 0.5 * (-md.log_rho - l0 + (md.rhom2 - xj * xj * inv_om) * md.inv_s);
+          la = dnu - l1 + lgn[N] - (N == 1 ? md.logJ : 0.0);
+        } else {
+          dnu = 0.5 * (-l0 - l1 + (up * up * inv_d2 - xj * xj * inv_om) * md.inv_s);
+          la = dnu + (lpd + l2);
+        }
+        valid = true;
+      } else {
+        st |= FSMP_ST_FACTOR;
+      }
+    }
+    const bool accepted = group_uniform<LPC>(valid && lg6 < la) != 0;
+    const bool edits = accepted && (move != 3 || sh != 0);
+    c_p += (lane == 0) | (lane == move);
+    c_a += (lane == 0 && t0acc) | (lane == move && accepted);
+    if (a.work) {
+      // the word counts in a packed Cholesky factor of the proposal (birth K(K+1)/2 + 2K + 3,
+      // death (K - j)(K - j + 1)/2 + 1, update both, the birth on K - 1 PEs) and of the edit (birth
+      // K + 3, death (K - 1 - j)(K - j) + K(K + 1)/2, update both); the elements of G^-1 read by the
+      // proposal; the elements of G^-1 and G the edit reads and writes
+      const double K = N, r = N - j;
+      const double wb = move == 1 ? K * (K + 1) / 2 + 2 * K + 3 : (K - 1) * K / 2 + 2 * (K - 1) + 3;
+      const double wd = r * (r + 1) / 2 + 1;
+      if (valid || need_mv) wk0 += move == 1 ? wb : move == 2 ? wd : (need_mv ? wd + wb : 0.0);
+      if (need_mv) wk2 += K * K + (CORR && move == 3 ? K : 0.0);
+      else if (move == 2 && valid) wk2 += CORR ? K : 1.0;
+      if (edits) {
+        const double eb = move == 1 ? K + 3 : (K - 1) + 3, ed = (r - 1) * r + K * (K + 1) / 2;
+        wk1 += move == 1 ? eb : move == 2 ? ed : ed + eb;
+        const double Kn = move == 1 ? K + 1 : move == 2 ? K - 1 : K;
+        wk3 += 2.0 * K * K + (CORR ? Kn * Kn : 0.0);
+      }
+    }
+    if (edits) {
+      // H += cu u u^T + cv v v^T: birth u = eta, cu = 1 / delta^2; death u = h, cu = -1 / omega;
+      // shift both, v = eta - h ej / omega (zero at j) with cv = 1 / delta^2
+      const double xn = up * inv_d2;
+      const int gj = move == 1 ? -1 : zl[j];
+      const bool two = move == 3;
+      const double cu = move == 1 ? inv_d2 : -inv_om, cv = two ? inv_d2 : 0.0;
+      const int last = N - 1;
+      const double uu = move == 1 ? eta : hj;
+      const double vv = two && lane != j ? eta - hj * (ej * inv_om) : 0.0;
+      WAVE_SYNC();
+      if (KCAP % LPC == 0 || lane < KCAP) {
+        lds_vec<KCAP, SYM>(va, lane, uu);
+        if (two || LPC < kWave) lds_vec<KCAP, SYM>(vb, lane, vv);
+      }
+      chain_sync<LPC>();
+      if (lane < N) {
+        // one edit code for the groups that share a wavefront, a shorter one for a single vector
+        if (LPC < kWave || two) lds_edit<KCAP, SYM, true>(D, va, vb, cu * uu, cv * vv, lane, N);
+        else lds_edit<KCAP, SYM, false>(D, va, vb, cu * uu, 0.0, lane, N);
+        const double xe = CORR ? xjp : xj;
+        if (move == 1) xl[lane] -= uu * xn;
+        else if (move == 2) xl[lane] -= uu * xe * inv_om;
+        else xl[lane] = (lane == j) ? xn : xl[lane] - uu * xe * inv_om - vv * xn;
+      }
+      chain_sync<LPC>();
+      if (move != 2) {
+        // the new PE's row: -w / delta^2 with w = eta or v, 1 / delta^2 on the diagonal
+        const int r = move == 1 ? N : j;
+        if (lane < N && lane != r) {
+          lds_set<KCAP, SYM>(D, r, lane, -(move == 1 ? uu : vv) * inv_d2);
+          if constexpr (CORR) {
+            Gm[r * KCAP + lane] = gam;
+            Gm[lane * KCAP + r] = gam;
+          }
+        }
+        if (lane == r) {
+          lds_set<KCAP, SYM>(D, r, r, inv_d2);
+          if (move == 1) xl[r] = xn;
+          zl[r] = gnew;
+          if constexpr (CORR) {
+            bl[r] = beta;
+            Gm[r * KCAP + r] = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + md.rho;
+          }
+        }
+        if (move == 1) N++;
+      } else {
+        // the last PE moves into the freed slot
+        double hl = 0.0, gv = 0.0, xlast = 0.0, blast = 0.0;
+        int zlast = 0;
+        if (lane < N) {
+          hl = D[lds_at<KCAP, SYM>(last, lane)];
+          if constexpr (CORR) gv = Gm[last * KCAP + lane];
+        }
+        zlast = zl[last];
+        xlast = xl[last];
+        if constexpr (CORR) blast = bl[last];
+        chain_sync<LPC>();
+        if (j != last) {
+          // row `last` in place of row j: its element at j is the one at the diagonal
+          const int at = lane == last ? j : lane;
+          if (lane < N && lane != j) {
+            lds_set<KCAP, SYM>(D, j, at, hl);
+            if constexpr (CORR) {
+              Gm[j * KCAP + at] = gv;
+              Gm[at * KCAP + j] = gv;
+            }
+          }
+          if (lane == j) {
+            zl[j] = zlast;
+            xl[j] = xlast;
+            if constexpr (CORR) bl[j] = blast;
+          }
+        }
+        if (lane == last) xl[last] = 0.0;
+        N--;
+      }
+      N = group_uniform<LPC>(N);
+      chain_sync_mem<LPC>();  // (the edits of G too)
+      residual();
+      if (move != 2 && gnew < gmin) {
+        gmin = gnew;
+      } else if (move != 1 && gj == gmin) {
+        gmin = INT32_MAX;
+        for (int i = gl; i < N; i += GW) gmin = zl[i] < gmin ? zl[i] : gmin;
+        gmin = group_min<GW>(gmin);
+      }
+      if (lane == 0) occ_edit(a, c, move, gj, gnew, step, burn, n_steps);
+    }
+
+    if (a.log && lane == 0) {
+      fsmp_logrec *lr = a.log + c * (int64_t)a.n_steps + step;
+      lr->move = move;
+      lr->flags = (valid ? 1 : 0) | (accepted ? 2 : 0) | (t0acc ? 4 : 0);
+      lr->j = j;
+      lr->g = gnew;
+      lr->t0 = t0;
+      lr->dnu = valid ? dnu : 0.0;
+      lr->log_alpha = valid ? la : -INFINITY;
+    }
+
+    // ---- record after burn-in
+    if (step >= burn) {
+      const double v = lane == 0 ? (double)N : lane == 1 ? Q : t0;
+      a_s += v;
+      a_q += v * v;
+      if (in_batch > 0) {
+        --in_batch;
+        a_b += v;
+        if (--b_left == 0) {
+          b_left = lb;
+          a_bs += a_b;
+          a_bq += a_b * a_b;
+          a_b = 0.0;
+        }
+      }
+      if (N != run_n) {
+        if (run_n >= 0 && lane == 0) atomicAdd(a.nhist + c * (a.kz + 1) + run_n, step - run_s);
+        run_n = N;
+        run_s = step;
+      }
+      const int i = step - burn;
+      if (a.trace && a.thin > 0 && (i % a.thin) == 0 && lane == 0) {
+        double *tr = a.trace + (c * a.n_rec + i / a.thin) * 3;
+        tr[0] = (double)N;
+        tr[1] = t0;
+        tr[2] = Q;
+      }
+      if (a.qdraw && a.thin > 0 && (i % a.thin) == 0) {
+        // charge draw q = x + sigma_eps R xi, H = R R^T with R upper triangular: the
+        // factorisation runs from the last PE backwards on a copy of H's lower triangle in the
+        // chain's device-memory scratch; y = R xi accumulates column by column
+        const int64_t rec = c * a.n_rec + i / a.thin;
+        double *Ad = a.dscr + slot * (int64_t)(KCAP * KCAP + KCAP);
+        double *Av = Ad + KCAP * KCAP;  // the column being eliminated
+        chain_sync_mem<LPC>();
+        bool ok = true;
+        for (int r = lane; r < N; r += LPC) {
+          for (int k = 0; k <= r; ++k) Ad[r * KCAP + k] = D[lds_at<KCAP, SYM>(k, r)];
+          va[r] = charge_normal(step, r, uid0, uid1, a.key0, a.key1);
+          vb[r] = 0.0;
+        }
+        chain_sync_mem<LPC>();
+        for (int jj = N - 1; jj >= 0 && ok; --jj) {
+          const double ajj = Ad[jj * KCAP + jj];
+          if (!(ajj > 0.0)) {
+            ok = false;
+            break;
+          }
+          const double dd = sqrt(ajj), xij = va[jj];
+          for (int r = lane; r < jj; r += LPC) {
+            const double x = Ad[jj * KCAP + r] / dd;
+            Av[r] = x;
+            vb[r] += x * xij;
+          }
+          if (lane == 0) vb[jj] += dd * xij;
+          chain_sync_mem<LPC>();
+          for (int r = lane; r < jj; r += LPC) {
+            const double vr = Av[r];
+            for (int k = 0; k <= r; ++k) Ad[r * KCAP + k] -= vr * Av[k];
+          }
+          chain_sync_mem<LPC>();
+        }
+        if (!ok) st |= FSMP_ST_FACTOR;
+        for (int r = lane; r < a.kz; r += LPC) {
+          a.zdraw[rec * a.kz + r] = r < N ? zl[r] : -1;
+          a.qdraw[rec * a.kz + r] = r < N ? (ok ? xl[r] + a.sigma_eps * vb[r] : NAN) : 0.0;
+        }
+        chain_sync_mem<LPC>();
+      }
+    }
+  }
+
+  chain_sync_mem<LPC>();
+  const int kz = a.kz;
+  for (int k = lane; k < kz; k += LPC) {
+    a.z[c * kz + k] = k < N ? zl[k] : -1;
+    a.charge[c * kz + k] = k < N ? xl[k] : 0.0;
+  }
+  if (lane < 3) {
+    double *ac = a.acc + c * 12;
+    ac[2 * lane] = a_s;
+    ac[2 * lane + 1] = a_q;
+    ac[6 + 2 * lane] = a_bs;
+    ac[7 + 2 * lane] = a_bq;
+  }
+  if (lane < 4) {
+    a.counts[c * 8 + 2 * lane] = c_p;
+    a.counts[c * 8 + 2 * lane + 1] = c_a;
+  }
+  if (lane == 0) {
+    if (run_n >= 0) atomicAdd(a.nhist + c * (a.kz + 1) + run_n, n_steps - run_s);
+    a.n_pe[c] = N;
+    a.t0[c] = t0;
+    if (a.rec_steps) a.rec_steps[c] = S_rec;
+    a.status[c] = st;
+    if (a.work) {
+      double *wk = a.work + c * 5;
+      wk[0] = wk0;
+      wk[1] = wk1;
+      wk[2] = wk2;
+      wk[3] = wk3;
+      wk[4] = 0.0;
+    }
+  }
+}
 
 // ------------------------------------------------------------------ chains, one lane each
 // birth position for one lane: EXP by the closed-form inverse, BIEXP by bisection on the
@@ -2828,7 +3708,6 @@ int chain_kcap_for(int kmax) {
 struct GroupCfg {
   int kcap, lpc, wpb;
 };
-static const GroupCfg kGroup[] = {{16, 16, 4}, {32, 32, 4}, {48, 64, 3}, {64, 64, 4}};
 static const GroupCfg kGroupDM[] = {{16, 4, 4},  {32, 4, 4},   {48, 16, 2},  {64, 32, 4},
                                     {96, 16, 2}, {128, 32, 4}, {160, 32, 4}, {192, 32, 2}};
 static const GroupCfg kGroupDMWide[] = {{32, 16, 4}, {48, 32, 4},  {64, 64, 4},  {96, 64, 4},
@@ -2859,10 +3738,93 @@ static size_t chain_lds_bytes(const GroupCfg &g, int M, int sub, bool hg, bool f
   return sizeof(double) * ((size_t)M * (1 + sub) + (size_t)g.kcap + 2 + (size_t)cpb * per);
 }
 
-bool chain_kcap_supported(int kcap, int M, int sub) {
-  for (const GroupCfg &g : kGroup)
-    if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, false) <= 160 * 1024;
-  return false;
+// lanes per chain and LDS doubles of one chain of the LDS instances (0: no such instance)
+static int lds_chain_doubles(int kcap, bool corr, int *lpc) {
+  *lpc = kcap <= 32 ? kcap : kcap <= 64 ? 64 : kcap <= 128 ? 128 : 192;
+  switch (kcap) {
+    case 16: return corr ? 0 : LdsLayout<16, 16, false>::kDoubles;
+    case 32: return corr ? 0 : LdsLayout<32, 32, false>::kDoubles;
+    case 48: return corr ? LdsLayout<48, 64, true>::kDoubles : LdsLayout<48, 64, false>::kDoubles;
+    case 64: return corr ? LdsLayout<64, 64, true>::kDoubles : LdsLayout<64, 64, false>::kDoubles;
+    case 96: return corr ? LdsLayout<96, 128, true>::kDoubles : 0;
+    case 128: return corr ? LdsLayout<128, 128, true>::kDoubles : 0;
+    case 160: return corr ? LdsLayout<160, 192, true>::kDoubles : 0;
+    case 192: return corr ? LdsLayout<192, 192, true>::kDoubles : 0;
+    default: return 0;
+  }
+}
+
+// LDS bytes of a workgroup of `waves` wavefronts (one chain in the groups wider than a
+// wavefront) without the rise table
+static size_t lds_block_bytes(int kcap, bool corr, int M, int sub, int waves) {
+  int lpc;
+  const int per = lds_chain_doubles(kcap, corr, &lpc);
+  if (lpc > kWave) return sizeof(double) * ((size_t)kcap + 2 + per);
+  return sizeof(double) * ((size_t)M * sub + (size_t)kcap + 2 + (size_t)waves * (kWave / lpc) * per);
+}
+
+size_t lds_ws_doubles(int kcap, bool corr, int64_t n_list) { return corr ? (size_t)n_list * kcap * kcap : 0; }
+
+bool chain_lds_supported(int kcap, bool corr, int M, int sub) {
+  int lpc;
+  return lds_chain_doubles(kcap, corr, &lpc) > 0 && lds_block_bytes(kcap, corr, M, sub, 1) <= 160 * 1024;
+}
+
+template <int KCAP, int LPC, bool CORR>
+static hipError_t launch_chain_lds_t(const ChainArgs &args, hipStream_t st, int32_t *lanes, int64_t *blocks) {
+  ChainArgs a = args;
+  constexpr int W = LdsLayout<KCAP, LPC, CORR>::kW, CPW = LPC < kWave ? kWave / LPC : 1;
+  const int64_t units = (a.n_list + CPW - 1) / CPW;  // wavefronts, or chains of several
+  *lanes = LPC;
+  *blocks = 0;
+  if (units == 0) return hipSuccess;
+  if (CORR && a.dws == nullptr) return hipErrorInvalidValue;
+  // As many wavefronts per workgroup as share one copy of the tables: what the LDS holds when the
+  // chains fill the chip, fewer (down to one) so that a small launch spreads over the 256 CUs.
+  // The rise table only where it fits beside one wavefront.
+  const size_t kLds = 160 * 1024, rise = sizeof(double) * a.md.rise_n;
+  if (lds_block_bytes(KCAP, CORR, a.md.M, a.md.sub, 1) + rise > kLds) a.md.rise_n = 0;
+  const size_t extra = sizeof(double) * a.md.rise_n;
+  int w = W > 1 ? 1 : (int)std::min<int64_t>(kLdsWaves, (units + 255) / 256);
+  while (w > 1 && lds_block_bytes(KCAP, CORR, a.md.M, a.md.sub, w) + extra > kLds) --w;
+  const size_t lds = lds_block_bytes(KCAP, CORR, a.md.M, a.md.sub, w) + extra;
+  if (lds > kLds) return hipErrorInvalidValue;  // the host checks the configurations against this
+  if (lds > 64 * 1024) {
+    (void)hipFuncSetAttribute((const void *)chain_lds_kernel<KCAP, LPC, CORR>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipGetLastError();
+  }
+  *blocks = (units + w - 1) / w;
+  hipLaunchKernelGGL((chain_lds_kernel<KCAP, LPC, CORR>), dim3((unsigned)*blocks), dim3(kWave * W * w), lds, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_chain_lds(int kcap, bool corr, const ChainArgs &a, hipStream_t st, int32_t *lanes,
+                            int64_t *blocks) {
+  if (corr) {
+    switch (kcap) {
+      case 48: return launch_chain_lds_t<48, 64, true>(a, st, lanes, blocks);
+      case 64: return launch_chain_lds_t<64, 64, true>(a, st, lanes, blocks);
+      case 96: return launch_chain_lds_t<96, 128, true>(a, st, lanes, blocks);
+      case 128: return launch_chain_lds_t<128, 128, true>(a, st, lanes, blocks);
+      case 160: return launch_chain_lds_t<160, 192, true>(a, st, lanes, blocks);
+      case 192: return launch_chain_lds_t<192, 192, true>(a, st, lanes, blocks);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (kcap) {
+    case 16: return launch_chain_lds_t<16, 16, false>(a, st, lanes, blocks);
+    case 32: return launch_chain_lds_t<32, 32, false>(a, st, lanes, blocks);
+    case 48: return launch_chain_lds_t<48, 64, false>(a, st, lanes, blocks);
+    case 64: return launch_chain_lds_t<64, 64, false>(a, st, lanes, blocks);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_overlap_partial(const double *vtab, double *out, int sub, int M, int LV, hipStream_t st) {
+  hipLaunchKernelGGL(overlap_partial_kernel, dim3((unsigned)((sub * M + 255) / 256)), dim3(256), 0, st, vtab, out, sub,
+                     M, LV);
+  return hipGetLastError();
 }
 
 bool chain_dm_supported(int kcap, int M, int sub, bool f32, bool mcp, bool wide) {
@@ -2921,16 +3883,6 @@ hipError_t launch_chain_lane(int kcap, const ChainArgs &a, hipStream_t st, int32
   switch (kcap) {
     case 16: return launch_chain_lane_t<16>(a, st, lanes, blocks);
     case 32: return launch_chain_lane_t<32>(a, st, lanes, blocks);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t launch_chain(int kcap, const ChainArgs &a, hipStream_t st, int32_t *lanes, int64_t *blocks) {
-  switch (kcap) {
-    case 16: return launch_chain_t<16, 16, 4, false>(a, st, lanes, blocks);
-    case 32: return launch_chain_t<32, 32, 4, false>(a, st, lanes, blocks);
-    case 48: return launch_chain_t<48, 64, 3, false>(a, st, lanes, blocks);
-    case 64: return launch_chain_t<64, 64, 4, false>(a, st, lanes, blocks);
     default: return hipErrorInvalidValue;
   }
 }
