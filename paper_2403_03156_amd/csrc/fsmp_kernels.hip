@@ -1718,7 +1718,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
 // design for batches that do not fill the chip with the other ones: a sweep's latency, not the
 // chip's throughput, then sets the time.
 //
-// Capacities up to 48 keep G^-1 full.  From 64 up the symmetric matrix is kept once, by wrapped
+// Capacities up to 64 keep G^-1 full.  From 96 up the symmetric matrix is kept once, by wrapped
 // diagonals: row d (0 .. KCAP / 2) holds the elements (i, (i + d) mod KCAP) at column i, so that
 // consecutive lanes read consecutive words whichever triangle an element is in (a packed
 // triangle would scatter them over the banks); the last row holds every element twice.  That
@@ -1734,15 +1734,20 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
 constexpr int kLdsWaves = 8;  // wavefronts of a workgroup at most
 template <int KCAP, int LPC, bool CORR>
 struct LdsLayout {
-  static constexpr bool kSym = KCAP >= 64;
+  static constexpr bool kSym = KCAP >= 96;
   static constexpr int kW = LPC > kWave ? LPC / kWave : 1;  // wavefronts of a chain
   static constexpr int kMat = kSym ? (KCAP / 2 + 1) * KCAP : KCAP * KCAP;
   static constexpr int kVec = kSym ? 2 * KCAP : KCAP;  // the two scratch vectors (twice in a row when wrapped)
   static constexpr int kStash = LPC >= kWave ? 0 : 6;  // random values per lane (registers from a wavefront up)
-  static constexpr int kRed = LPC > kWave ? 2 * (3 * kW + 1) : 0;  // partial sums of the wavefronts, two sets
+  // Lanes over which a vector's sums are taken: element i belongs to lane i mod kRO, which adds its
+  // elements in order before the butterfly over the kRO lanes.  Every wavefront of a chain forms
+  // the whole sum so, from LDS (no exchange of partial sums); 16 at capacity 48 and 32 at 64 are
+  // the orders of the narrow device-memory groups, whose chains this design repeats bit for bit
+  // there (as their products and edits are taken in the same order and rounding).
+  static constexpr int kRO = KCAP <= 32 ? LPC : KCAP == 48 ? 16 : 32;
   // matrix, two scratch vectors, x (b and the residual too in the corrected form), the PE list,
-  // the random values of the next LPC sweeps, the wavefronts' partial sums
-  static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 + kStash * LPC + kRed;
+  // the random values of the next LPC sweeps
+  static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 + kStash * LPC;
 };
 
 // the overlap of two columns, as overlap(), with the window-edge sums from the table of partial
@@ -1856,9 +1861,23 @@ __device__ inline double lds_dot(const double *D, const double *v, int i, int N)
   return e;
 }
 
-// H += cui u u^T row i [+ cvi v v^T], element i's share (i < N; u, v zero from N on)
-template <int KCAP, bool SYM, bool TWO>
-__device__ inline void lds_edit(double *D, const double *u, const double *v, double cui, double cvi, int i, int N) {
+// One element of an edit: h + (ui uk) cu [+ (vi vk) cv] in a sweep, rounded as the device-memory
+// groups round it (h is added to the sum of the two terms, of which `first`, the first row of a
+// chunk of eight, rounds the other one); fused into h where a list is built.
+template <bool TWO, bool BUILD>
+__device__ inline double lds_edited(double h, double ui, double uk, double cu, double vi, double vk, double cv,
+                                    bool first) {
+#pragma clang fp contract(off)
+  if constexpr (BUILD) return fma(ui * uk, cu, h);
+  else if (TWO && first) return h + fma(vi * vk, cv, ui * uk * cu);
+  else if constexpr (TWO) return h + fma(ui * uk, cu, vi * vk * cv);
+  else return h + ui * uk * cu;
+}
+
+// H += cu u u^T [+ cv v v^T], element i's share (i < N; u, v zero from N on)
+template <int KCAP, bool SYM, bool TWO, bool BUILD>
+__device__ inline void lds_edit(double *D, const double *u, const double *v, double ui, double cu, double vi,
+                                double cv, int i, int N) {
   if constexpr (SYM) {
     const int dm = N - 1 < KCAP / 2 - 1 ? N - 1 : KCAP / 2 - 1;
     for (int d0 = 0; d0 <= dm; d0 += 8) {
@@ -1867,19 +1886,15 @@ __device__ inline void lds_edit(double *D, const double *u, const double *v, dou
       for (int q = 0; q < 8; ++q) {
         h[q] = D[(d0 + q) * KCAP + i];
         a[q] = u[i + d0 + q];
-        if (TWO) b[q] = v[i + d0 + q];
+        b[q] = TWO ? v[i + d0 + q] : 0.0;
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        double x = fma(cui, a[q], h[q]);
-        if (TWO) x = fma(cvi, b[q], x);
-        D[(d0 + q) * KCAP + i] = x;
-      }
+      for (int q = 0; q < 8; ++q)
+        D[(d0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv, q == 0);
     }
     if (N > KCAP / 2) {
-      double x = fma(cui, u[i + KCAP / 2], D[KCAP / 2 * KCAP + i]);
-      if (TWO) x = fma(cvi, v[i + KCAP / 2], x);
-      D[KCAP / 2 * KCAP + i] = x;
+      double *e = D + KCAP / 2 * KCAP + i;
+      *e = lds_edited<TWO, BUILD>(*e, ui, u[i + KCAP / 2], cu, vi, TWO ? v[i + KCAP / 2] : 0.0, cv, false);
     }
   } else {
     for (int k0 = 0; k0 < N; k0 += 8) {
@@ -1888,14 +1903,11 @@ __device__ inline void lds_edit(double *D, const double *u, const double *v, dou
       for (int q = 0; q < 8; ++q) {
         h[q] = D[(k0 + q) * KCAP + i];
         a[q] = u[k0 + q];
-        if (TWO) b[q] = v[k0 + q];
+        b[q] = TWO ? v[k0 + q] : 0.0;
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        double x = fma(cui, a[q], h[q]);
-        if (TWO) x = fma(cvi, b[q], x);
-        D[(k0 + q) * KCAP + i] = x;
-      }
+      for (int q = 0; q < 8; ++q)
+        D[(k0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv, q == 0);
     }
   }
 }
@@ -1933,65 +1945,39 @@ __device__ inline void chain_sync_mem() {
   else WAVE_SYNC();
 }
 
-// Sums of NV values over a chain's lanes, and the value x of lane j (j < 0: none).  Over several
-// wavefronts: each wavefront's sums and x go to one of two sets in `red` (used in turn, so one
-// barrier per use is enough), which every lane adds up in the same order.  All LDS written
-// before the call is visible after it.
-template <int LPC, int NV>
-__device__ inline void chain_sums(double (&v)[NV], double &x, int j, int lane, int base, double *red, int &turn) {
-  if constexpr (LPC > kWave) {
-    constexpr int W = LPC / kWave;
-    double *r = red + turn * (3 * W + 1);
-    turn ^= 1;
+// Sum over a chain's elements of f(i, sum so far): lane i mod RO adds its elements in order, then
+// the butterfly over RO lanes; every wavefront of the chain forms it from LDS
+template <int KCAP, int RO, typename F>
+__device__ inline double chain_sum(int gl, F f) {
+  double t = 0.0;
 #pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = group_sum<kWave>(v[q]);
-    if ((lane & (kWave - 1)) == 0)
-#pragma unroll
-      for (int q = 0; q < NV; ++q) r[3 * (lane / kWave) + q] = v[q];
-    if (lane == j) r[3 * W] = x;
-    chain_sync<LPC>();
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      double t = r[q];
-#pragma unroll
-      for (int w = 1; w < W; ++w) t += r[3 * w + q];
-      v[q] = t;
-    }
-    x = r[3 * W];
-  } else {
-    WAVE_SYNC();
-#pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = group_sum<LPC>(v[q]);
-    if constexpr (LPC == kWave) x = lane_value(x, j < 0 ? 0 : j);
-    else x = __shfl(x, base + (j < 0 ? 0 : j), kWave);
-  }
+  for (int q = 0; q < KCAP / RO; ++q) t = f((gl & (RO - 1)) + q * RO, t);
+  return group_sum<RO>(t);
 }
 
 // G^-1 of the PE list zl[0..N) by bordering into the (finite) matrix D, each step the birth
 // update of the inverse of the leading block; va, vb: the scratch vectors.  False if a Schur
 // complement is not positive.
-template <int KCAP, int LPC, bool SYM>
+template <int KCAP, int LPC, bool SYM, int RO>
 __device__ bool lds_build(const ModelDev &md, const double *vtab, const double *ov, int Lw, double *D, double *va,
-                          double *vb, const int *zl, int N, int lane, int base, double *red, int &turn) {
+                          double *vb, const int *zl, int N, int lane, int gl) {
+  const bool own = KCAP % LPC == 0 || lane < KCAP;  // a lane with an element
   for (int k = 0; k < N; ++k) {
     const int gk = zl[k];
-    for (int i = lane; i < KCAP; i += LPC)
-      lds_vec<KCAP, SYM>(va, i, i < k ? overlap_edge(md, vtab, ov, gk, zl[i], Lw) : 0.0);
+    chain_sync<LPC>();
+    if (own) lds_vec<KCAP, SYM>(va, lane, lane < k ? overlap_edge(md, vtab, ov, gk, zl[lane], Lw) : 0.0);
     const double d = overlap_edge(md, vtab, ov, gk, gk, Lw) + md.rho;
     chain_sync<LPC>();
-    double q[1] = {0.0}, none = 0.0;
-    for (int i = lane; i < KCAP; i += LPC) {
-      const double e = i < k ? lds_dot<KCAP, SYM>(D, va, i, k) : 0.0;
-      q[0] += va[i] * e;
-      lds_vec<KCAP, SYM>(vb, i, e);
-    }
-    chain_sums<LPC, 1>(q, none, -1, lane, base, red, turn);
-    const double delta2 = d - q[0];
+    const double e = lane < k ? lds_dot<KCAP, SYM>(D, va, lane, k) : 0.0;
+    if (own) lds_vec<KCAP, SYM>(vb, lane, e);
+    chain_sync<LPC>();
+    const double q = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], vb[i], t); });
+    const double delta2 = d - q;
     if (!(delta2 > 0.0)) return false;
     const double inv = 1.0 / delta2;
-    for (int i = lane; i < k; i += LPC) lds_edit<KCAP, SYM, false>(D, vb, vb, vb[i] * inv, 0.0, i, k);
+    if (lane < k) lds_edit<KCAP, SYM, false, true>(D, vb, vb, e, inv, 0.0, 0.0, lane, k);
     chain_sync<LPC>();
-    for (int i = lane; i < k; i += LPC) lds_set<KCAP, SYM>(D, k, i, -vb[i] * inv);
+    if (lane < k) lds_set<KCAP, SYM>(D, k, lane, -e * inv);
     if (lane == 0) lds_set<KCAP, SYM>(D, k, k, inv);
     chain_sync<LPC>();
   }
@@ -2005,6 +1991,7 @@ __global__ void __launch_bounds__(kLdsWaves *kWave) __attribute__((amdgpu_waves_
 chain_lds_kernel(ChainArgs a) {
   using CL = LdsLayout<KCAP, LPC, CORR>;
   constexpr bool SYM = CL::kSym;
+  constexpr int RO = CL::kRO;
   constexpr int W = CL::kW, CPW = LPC < kWave ? kWave / LPC : 1;
   static_assert(LPC >= 16 && LPC >= KCAP, "one element of the vectors per lane");
   extern __shared__ double smem[];
@@ -2035,8 +2022,6 @@ chain_lds_kernel(ChainArgs a) {
   double *bl = CORR ? xl + KCAP : nullptr, *sl = CORR ? bl + KCAP : nullptr;
   int *zl = (int *)(xl + (CORR ? 3 : 1) * KCAP);
   double *stash = (double *)(zl + 2 * ((KCAP + 1) / 2));
-  double *red = stash;  // (the groups wider than a wavefront have no stash)
-  int turn = 0;
   double *Gm = CORR ? a.dws + slot * (int64_t)(KCAP * KCAP) : nullptr;
 
   const int64_t c = a.chains[slot];
@@ -2076,24 +2061,40 @@ chain_lds_kernel(ChainArgs a) {
   int gmin = INT32_MAX;  // smallest PE grid index
   double Q = 0.0;        // sum of the charge means, changes with accepted moves only
 
-  // s = b - G x against the exact G (corrected form), and Q: rows in chunks of 16, the loads of a
-  // chunk in flight together (rows and elements past N are zero or meet a zero x)
+  // After the list has changed: the residual s = b - G x against the exact G (corrected form) and
+  // Q.  Rows of G in chunks of 16, the loads of a chunk in flight together (rows and elements
+  // past N are zero or meet a zero x).  From capacity 96 up every kRefine changes x first takes
+  // up H s: an edit leaves about kappa eps in x, and without the refinement those add up over the
+  // chain (at N ~ 30 the total charge after 600 sweeps is 3.5e-15 off instead of 3.2e-14).
+  constexpr int kRefine = 16;
+  int to_refine = kRefine;
   auto residual = [&]() {
-    double r = 0.0;
     if constexpr (CORR) {
       const double *gp = Gm + (KCAP % LPC && lane >= KCAP ? KCAP - 1 : lane);
-      for (int k0 = 0; k0 < N; k0 += 16) {
-        double g[16];
+      const bool refine = SYM && --to_refine == 0;
+      for (int pass = refine ? 0 : 1; pass < 2; ++pass) {
+        double r = 0.0;
+        for (int k0 = 0; k0 < N; k0 += 16) {
+          double g[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) g[u] = gp[(k0 + u) * KCAP];
+          for (int u = 0; u < 16; ++u) g[u] = gp[(k0 + u) * KCAP];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) r = fma(g[u], xl[k0 + u], r);
+          for (int u = 0; u < 16; ++u) r = fma(g[u], xl[k0 + u], r);
+        }
+        const double rs = lane < N ? bl[lane] - r : 0.0;
+        if (pass == 0) {
+          to_refine = kRefine;
+          if (KCAP % LPC == 0 || lane < KCAP) lds_vec<KCAP, SYM>(va, lane, rs);
+          chain_sync<LPC>();
+          if (lane < N) xl[lane] += lds_dot<KCAP, SYM>(D, va, lane, N);
+          chain_sync<LPC>();
+        } else if (KCAP % LPC == 0 || lane < KCAP) {
+          sl[lane] = rs;
+        }
       }
-      if (KCAP % LPC == 0 || lane < KCAP) sl[lane] = lane < N ? bl[lane] - r : 0.0;
     }
-    double qs[1] = {lane < N ? xl[lane] : 0.0}, none = 0.0;
-    chain_sums<LPC, 1>(qs, none, -1, lane, gbase, red, turn);
-    Q = qs[0];
+    chain_sync<LPC>();
+    Q = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return t + xl[i]; });
   };
 
   // a caller-supplied initial PE list: G^-1 and x = G^-1 b of the list before the first sweep
@@ -2103,7 +2104,7 @@ chain_lds_kernel(ChainArgs a) {
       const int32_t *z0 = a.zinit + a.zinit_off[c];
       if (lane < n0) zl[lane] = z0[lane];
       chain_sync<LPC>();
-      if (lds_build<KCAP, LPC, SYM>(md, a.vtab, ov, Lw, D, va, vb, zl, n0, lane, gbase, red, turn)) {
+      if (lds_build<KCAP, LPC, SYM, RO>(md, a.vtab, ov, Lw, D, va, vb, zl, n0, lane, gl)) {
         const double b = lane < n0 ? mf[zl[lane] - glo] + md.rhom : 0.0;
         if (KCAP % LPC == 0 || lane < KCAP) lds_vec<KCAP, SYM>(va, lane, b);
         chain_sync<LPC>();
@@ -2147,7 +2148,7 @@ chain_lds_kernel(ChainArgs a) {
         if (ref_left == 0) {
           ref_left = a.refresh_M;
           if (N > 0) {
-            if (lds_build<KCAP, LPC, SYM>(md, a.vtab, ov, Lw, D, va, vb, zl, N, lane, gbase, red, turn)) {
+            if (lds_build<KCAP, LPC, SYM, RO>(md, a.vtab, ov, Lw, D, va, vb, zl, N, lane, gl)) {
               if (KCAP % LPC == 0 || lane < KCAP)
                 lds_vec<KCAP, SYM>(va, lane, lane < N ? mf[zl[lane] - glo] + md.rhom : 0.0);
               chain_sync<LPC>();
@@ -2222,14 +2223,17 @@ chain_lds_kernel(ChainArgs a) {
         if (glo <= ghi) tp = t0_terms<GW>(md, t0p, glo, ghi, gl, gbase);
         double S = 0.0;  // sum over the PEs of log r(t0p) / r(t0), r the rise factor
         if (biexp && N > 0) {
-          double ratio = 1.0;
-          if (lane < N) {
-            const int g = zl[lane];
-            ratio = rise_at(md, rt, tp, t0p, g) / rise_at(md, rt, tc, t0, g);
+          double pn = 1.0, pc = 1.0;
+#pragma unroll
+          for (int q = 0; q < (KCAP + GW - 1) / GW; ++q) {
+            const int i = gl + q * GW;
+            if (i < N) {
+              const int g = zl[i];
+              pn *= rise_at(md, rt, tp, t0p, g);
+              pc *= rise_at(md, rt, tc, t0, g);
+            }
           }
-          double v[1] = {log(ratio)}, none = 0.0;
-          chain_sums<LPC, 1>(v, none, -1, lane, gbase, red, turn);
-          S = v[0];
+          S = group_sum<GW>(log(pn / pc));
         }
         if (glo <= ghi) t0_phi(md, tp);
         const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
@@ -2285,40 +2289,42 @@ chain_lds_kernel(ChainArgs a) {
     if (need_mv) {
       mfv = mf[gnew - glo];
       if (lane < N && lane != j) gam = overlap_edge(md, a.vtab, ov, gnew, zl[lane], Lw);
+      chain_sync<LPC>();  // (the last proposal's sums are done with va and vb)
       if (KCAP % LPC == 0 || lane < KCAP) lds_vec<KCAP, SYM>(va, lane, gam);
+      chain_sync<LPC>();
     }
     if (removes) {
-      if (lane < N) hj = D[lds_at<KCAP, SYM>(j, lane)];
+      om = D[lds_at<KCAP, SYM>(j, j)];
       xj = xjp = xl[j];
-      double xc[1] = {0.0};
-      om = hj;
-      if constexpr (CORR) {
-        if (lane < N) xc[0] = hj * sl[lane];
-      }
-      chain_sums<LPC, 1>(xc, om, j, lane, gbase, red, turn);
-      if constexpr (CORR) xj += xc[0];
+      if (lane < N) hj = D[lds_at<KCAP, SYM>(j, lane)];
+      // (elements of H past N may be left over from removed PEs: they meet a zero of s)
+      if constexpr (CORR)
+        xj += chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(D[lds_at<KCAP, SYM>(j, i)], sl[i], t); });
       inv_om = 1.0 / om;
-    } else if (need_mv) {
-      chain_sync<LPC>();
     }
     if (need_mv) {
       const double d = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + md.rho;
-      double v[2] = {0.0, 0.0};
-      if (lane < N) {
-        eta = lds_dot<KCAP, SYM>(D, va, lane, N);
-        v[0] = gam * eta;
-        v[1] = gam * xl[lane];
-        if constexpr (CORR) v[1] += eta * sl[lane];
+      if (lane < N) eta = lds_dot<KCAP, SYM>(D, va, lane, N);
+      double q, p;
+      if constexpr (RO == LPC) {
+        q = group_sum<RO>(gam * eta);
+        p = group_sum<RO>(lane < N ? gam * xl[lane] : 0.0);
+        if (move == 3) ej = __shfl(eta, gbase + j, kWave);
+      } else {
+        if (KCAP % LPC == 0 || lane < KCAP) vb[lane] = eta;
+        chain_sync<LPC>();
+        q = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], vb[i], t); });
+        p = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], xl[i], t); });
+        if constexpr (CORR) p += chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(vb[i], sl[i], t); });
+        if (move == 3) ej = vb[j];
       }
-      ej = eta;
-      chain_sums<LPC, 2>(v, ej, j, lane, gbase, red, turn);
       if (move == 3) {
-        v[0] -= ej * ej * inv_om;
-        v[1] -= ej * xj * inv_om;
+        q -= ej * ej / om;
+        p -= ej * xj / om;
       }
       beta = mfv + md.rhom;
-      delta2 = d - v[0];
-      up = beta - v[1];
+      delta2 = d - q;
+      up = beta - p;
       inv_d2 = 1.0 / delta2;
     }
     if (need_mv || move == 2) {
@@ -2373,8 +2379,8 @@ chain_lds_kernel(ChainArgs a) {
       const double cu = move == 1 ? inv_d2 : -inv_om, cv = two ? inv_d2 : 0.0;
       const int last = N - 1;
       const double uu = move == 1 ? eta : hj;
-      const double vv = two && lane != j ? eta - hj * (ej * inv_om) : 0.0;
-      WAVE_SYNC();
+      const double vv = two && lane != j ? eta - hj * ej * inv_om : 0.0;
+      chain_sync<LPC>();
       if (KCAP % LPC == 0 || lane < KCAP) {
         lds_vec<KCAP, SYM>(va, lane, uu);
         if (two || LPC < kWave) lds_vec<KCAP, SYM>(vb, lane, vv);
@@ -2382,8 +2388,8 @@ chain_lds_kernel(ChainArgs a) {
       chain_sync<LPC>();
       if (lane < N) {
         // one edit code for the groups that share a wavefront, a shorter one for a single vector
-        if (LPC < kWave || two) lds_edit<KCAP, SYM, true>(D, va, vb, cu * uu, cv * vv, lane, N);
-        else lds_edit<KCAP, SYM, false>(D, va, vb, cu * uu, 0.0, lane, N);
+        if (LPC < kWave || two) lds_edit<KCAP, SYM, true, false>(D, va, vb, uu, cu, vv, cv, lane, N);
+        else lds_edit<KCAP, SYM, false, false>(D, va, vb, uu, cu, 0.0, 0.0, lane, N);
         const double xe = CORR ? xjp : xj;
         if (move == 1) xl[lane] -= uu * xn;
         else if (move == 2) xl[lane] -= uu * xe * inv_om;
