@@ -3233,16 +3233,20 @@ __global__ void __launch_bounds__(256) occupancy_kernel(PosteriorArgs a) {
   }
 }
 
+// One wavefront per waveform: lanes 0 .. 2 the moments of N, Q and t0, lanes 0 .. 3 the
+// acceptance rates, all lanes the histogram (coalesced; one thread per waveform walked its rows
+// word by word).
 __global__ void __launch_bounds__(256) posterior_kernel(PosteriorArgs a) {
-  const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t w = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave;
   if (w >= a.n_wave) return;
   // the chains of one waveform ran the same number of sweeps
   const int S = a.rec_steps ? a.rec_steps[w * a.n_chains] : a.n_steps - a.burn_in;
   const int nb = S > 0 ? (int)floor(sqrt((double)S)) : 0;
   const int lb = nb > 0 ? S / nb : 0;
   const int C = a.n_chains;
-  uint32_t st = 0;
-  for (int v = 0; v < 3; ++v) {
+  if (lane < 3) {
+    const int v = lane;
     double s1 = 0.0, s2 = 0.0, b1 = 0.0, b2 = 0.0;
     for (int ch = 0; ch < C; ++ch) {
       const double *ac = a.acc + (w * C + ch) * 12;
@@ -3265,51 +3269,55 @@ __global__ void __launch_bounds__(256) posterior_kernel(PosteriorArgs a) {
     a.var[w * 3 + v] = var;
     a.mcse[w * 3 + v] = mcse;
   }
-  double prop[4] = {0, 0, 0, 0}, accp[4] = {0, 0, 0, 0};
-  for (int ch = 0; ch < C; ++ch) {
-    const int32_t *cn = a.counts + (w * C + ch) * 8;
-    for (int m = 0; m < 4; ++m) {
-      prop[m] += cn[2 * m];
-      accp[m] += cn[2 * m + 1];
+  if (lane < 4) {
+    double prop = 0.0, acc = 0.0;
+    uint32_t st = 0;
+    for (int ch = 0; ch < C; ++ch) {
+      prop += a.counts[(w * C + ch) * 8 + 2 * lane];
+      acc += a.counts[(w * C + ch) * 8 + 2 * lane + 1];
+      st |= a.cstatus[w * C + ch];
     }
-    st |= a.cstatus[w * C + ch];
+    a.accept[w * 4 + lane] = prop > 0 ? acc / prop : 0.0;
+    if (lane == 0) a.status[w] = st;
   }
-  for (int m = 0; m < 4; ++m) a.accept[w * 4 + m] = prop[m] > 0 ? accp[m] / prop[m] : 0.0;
   if (a.p_n) {
     const int kz = a.kz;
-    double tot = 0.0;
-    for (int ch = 0; ch < C; ++ch)
-      for (int k = 0; k <= kz; ++k) tot += a.nhist[(w * C + ch) * (kz + 1) + k];
-    for (int k = 0; k <= kz; ++k) {
+    const int32_t *nh = a.nhist + w * C * (kz + 1);
+    double tot = 0.0;  // whole numbers: exact in any order
+    for (int k = lane; k <= kz; k += kWave) {
       double s = 0.0;
-      for (int ch = 0; ch < C; ++ch) s += a.nhist[(w * C + ch) * (kz + 1) + k];
+      for (int ch = 0; ch < C; ++ch) s += nh[ch * (kz + 1) + k];
+      tot += s;
+    }
+    tot = group_sum<kWave>(tot);
+    for (int k = lane; k <= kz; k += kWave) {
+      double s = 0.0;
+      for (int ch = 0; ch < C; ++ch) s += nh[ch * (kz + 1) + k];
       a.p_n[w * (kz + 1) + k] = tot > 0 ? s / tot : 0.0;
     }
   }
-  a.status[w] = st;
 }
 
-// ---- posterior extras: chain diagnostics and the lambda estimates, one thread per waveform
+// ---- posterior extras: chain diagnostics and the lambda estimates, one wavefront per waveform
 
 // d(lambda) = m(lambda) - lambda, m the mean of k under the weights h_k (lambda / lambda0)^k
 // (computed from the largest log-weight down); with `f` also the log-likelihood estimate
 // f(lambda) = -(lambda - lambda0) + log sum_k h_k (lambda / lambda0)^k.  lambda = 0 keeps k = 0.
-__device__ inline double lam_tilt(const int32_t *nh, int C, int kz1, int k_lo, int k_hi, double lam, double lam0,
-                                  double *f) {
+// lh(k): log h_k, -inf for h_k = 0.
+template <typename LH>
+__device__ inline double lam_tilt(LH lh, int k_lo, int k_hi, double lam, double lam0, double *f) {
   const double lr = lam > 0.0 ? log(lam / lam0) : 0.0;
   const int top = lam > 0.0 ? k_hi : 0;
   double mx = -INFINITY;
   for (int k = k_lo; k <= top; ++k) {
-    double h = 0.0;
-    for (int ch = 0; ch < C; ++ch) h += nh[ch * kz1 + k];
-    if (h > 0.0) mx = fmax(mx, log(h) + k * lr);
+    const double l = lh(k);
+    if (l > -INFINITY) mx = fmax(mx, l + k * lr);
   }
   double se = 0.0, sk = 0.0;
   for (int k = k_lo; k <= top; ++k) {
-    double h = 0.0;
-    for (int ch = 0; ch < C; ++ch) h += nh[ch * kz1 + k];
-    if (h > 0.0) {
-      const double e = exp(log(h) + k * lr - mx);
+    const double l = lh(k);
+    if (l > -INFINITY) {
+      const double e = exp(l + k * lr - mx);
       se += e;
       sk += k * e;
     }
@@ -3318,13 +3326,73 @@ __device__ inline double lam_tilt(const int32_t *nh, int C, int kz1, int k_lo, i
   return sk / se - lam;
 }
 
-__global__ void __launch_bounds__(256) posterior_extra_kernel(PosteriorArgs a) {
-  const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// lambda-hat: the + to - crossings of d on 64 grid points of [k_lo, k_hi], each refined to the
+// root, and lambda = 0 when k_lo = 0 and d <= 0 at the second point; the largest f wins.  Each
+// lane evaluates one point: the grid is one evaluation, and a refinement cuts its interval into
+// 65 per evaluation (9 of them where bisecting by one thread took 52).
+template <typename LH>
+__device__ inline double lambda_mle(LH lh, int k_lo, int k_hi, double lam0, int lane) {
+  if (k_lo < 0) return NAN;
+  if (k_lo == k_hi) return k_lo;
+  constexpr int kGrid = kWave;
+  const double span = (double)(k_hi - k_lo);
+  const double x = k_lo + span * lane / (kGrid - 1);
+  const double dx = lam_tilt(lh, k_lo, k_hi, x, lam0, nullptr);
+  const double xp = __shfl(x, lane > 0 ? lane - 1 : 0, kWave), dp = __shfl(dx, lane > 0 ? lane - 1 : 0, kWave);
+  const bool zero = k_lo == 0 && (__ballot(lane == 1 && dx <= 0.0) != 0);
+  uint64_t cross = __ballot(lane > 0 && dp > 0.0 && dx <= 0.0);
+  double est = NAN, best_f = -INFINITY;
+  if (zero) {
+    double f0;
+    (void)lam_tilt(lh, k_lo, k_hi, 0.0, lam0, &f0);
+    if (f0 > best_f) {
+      best_f = f0;
+      est = 0.0;
+    }
+  }
+  while (cross) {
+    const int i = __ffsll((unsigned long long)cross) - 1;
+    cross &= cross - 1;
+    double lo = __shfl(xp, i, kWave), hi = __shfl(x, i, kWave);
+    double cand = hi;
+    if (__shfl(dx, i, kWave) != 0.0) {
+      for (int it = 0; it < 40; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (!(mid > lo && mid < hi)) break;
+        const double p = lo + (hi - lo) * (lane + 1) / (kWave + 1);
+        const bool neg = !(lam_tilt(lh, k_lo, k_hi, p, lam0, nullptr) > 0.0) || p >= hi;
+        const uint64_t bal = __ballot(neg);
+        const int l = bal ? __ffsll((unsigned long long)bal) - 1 : kWave;
+        const double nlo = __shfl(p, l > 0 ? l - 1 : 0, kWave), nhi = __shfl(p, l < kWave ? l : 0, kWave);
+        if (l > 0 && nlo > lo) lo = nlo;
+        if (l < kWave && nhi < hi) hi = nhi;
+      }
+      cand = 0.5 * (lo + hi);
+    }
+    double fc;
+    (void)lam_tilt(lh, k_lo, k_hi, cand, lam0, &fc);
+    if (fc > best_f) {
+      best_f = fc;
+      est = cand;
+    }
+  }
+  return est;
+}
+
+// The logs of the waveform's histogram in LDS (lds_k entries per wavefront; 0: rows too long for
+// it, taken from device memory at each use).  What bounds it is the chain of exponentials: about
+// 11 evaluations of K terms per waveform, each point by a lane of its own (8,000 waveforms of
+// four chains, with posterior_kernel: 18 ms with a thread per waveform, under 1 ms now).
+__global__ void __launch_bounds__(256) posterior_extra_kernel(PosteriorArgs a, int lds_k) {
+  extern __shared__ double smem[];
+  const int64_t w = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave;
   if (w >= a.n_wave) return;
   const int C = a.n_chains;
   const int S = a.rec_steps ? a.rec_steps[w * C] : a.n_steps - a.burn_in;
   // Gelman-Rubin R and the Monte Carlo error from the spread of the chain means
-  for (int v = 0; v < 3; ++v) {
+  if (lane < 3) {
+    const int v = lane;
     double msum = 0.0;
     for (int ch = 0; ch < C; ++ch) msum += a.acc[(w * C + ch) * 12 + 2 * v] / S;
     const double mbar = msum / C;
@@ -3347,65 +3415,36 @@ __global__ void __launch_bounds__(256) posterior_extra_kernel(PosteriorArgs a) {
     if (a.mcse_chains) a.mcse_chains[w * 3 + v] = mc;
   }
   if (!a.lambda_hat) return;
-  // lambda-hat: the + to - crossings of d on 64 grid points of [k_lo, k_hi], each refined by
-  // bisection, and lambda = 0 when k_lo = 0 and d <= 0 at the second point; the largest f wins
   const int kz1 = a.kz + 1;
   const int32_t *nh = a.nhist + w * C * kz1;
-  int k_lo = -1, k_hi = -1;
-  for (int k = 0; k < kz1; ++k) {
-    int32_t h = 0;
+  double *lg = smem + (int64_t)(threadIdx.x / kWave) * lds_k;
+  int k_lo = INT32_MAX, k_hi = -1;
+  for (int k = lane; k < kz1; k += kWave) {
+    double h = 0.0;
     for (int ch = 0; ch < C; ++ch) h += nh[ch * kz1 + k];
-    if (h > 0) {
-      if (k_lo < 0) k_lo = k;
+    if (lds_k > 0) lg[k] = log(h);
+    if (h > 0.0) {
+      k_lo = k < k_lo ? k : k_lo;
       k_hi = k;
     }
   }
-  double est = NAN;
-  const double lam0 = a.lam0[w];
-  if (k_lo >= 0 && k_lo == k_hi) {
-    est = k_lo;
-  } else if (k_lo >= 0) {
-    constexpr int kGrid = 64;
-    const double span = (double)(k_hi - k_lo);
-    double best_f = -INFINITY;
-    double dprev = 0.0;
-    for (int i = 0; i < kGrid; ++i) {
-      const double x = k_lo + span * i / (kGrid - 1);
-      const double dx = lam_tilt(nh, C, kz1, k_lo, k_hi, x, lam0, nullptr);
-      double cand = NAN;
-      if (i == 1 && k_lo == 0 && dx <= 0.0) {
-        double f0;
-        (void)lam_tilt(nh, C, kz1, k_lo, k_hi, 0.0, lam0, &f0);
-        if (f0 > best_f) {
-          best_f = f0;
-          est = 0.0;
-        }
-      }
-      if (i > 0 && dprev > 0.0 && dx <= 0.0) {
-        if (dx == 0.0) {
-          cand = x;
-        } else {
-          double lo = k_lo + span * (i - 1) / (kGrid - 1), hi = x;
-          for (int it = 0; it < 200; ++it) {
-            const double mid = 0.5 * (lo + hi);
-            if (!(mid > lo && mid < hi)) break;
-            if (lam_tilt(nh, C, kz1, k_lo, k_hi, mid, lam0, nullptr) > 0.0) lo = mid;
-            else hi = mid;
-          }
-          cand = 0.5 * (lo + hi);
-        }
-        double fc;
-        (void)lam_tilt(nh, C, kz1, k_lo, k_hi, cand, lam0, &fc);
-        if (fc > best_f) {
-          best_f = fc;
-          est = cand;
-        }
-      }
-      dprev = dx;
-    }
+  k_lo = group_min<kWave>(k_lo);
+  k_hi = -group_min<kWave>(-k_hi);
+  WAVE_SYNC();
+  if (k_hi < 0) k_lo = -1;
+  const double est =
+      lds_k > 0 ? lambda_mle([&](int k) { return lg[k]; }, k_lo, k_hi, a.lam0[w], lane)
+                : lambda_mle(
+                      [&](int k) {
+                        double h = 0.0;
+                        for (int ch = 0; ch < C; ++ch) h += nh[ch * kz1 + k];
+                        return log(h);
+                      },
+                      k_lo, k_hi, a.lam0[w], lane);
+  if (lane == 0) {
+    a.lambda_hat[w * 2] = est;
+    a.lambda_hat[w * 2 + 1] = a.mean[w * 3 + 1] / a.mu_q;  // lambda-hat_Q = E[Q] / mu_q
   }
-  a.lambda_hat[w * 2] = est;
-  a.lambda_hat[w * 2 + 1] = a.mean[w * 3 + 1] / a.mu_q;  // lambda-hat_Q = E[Q] / mu_q
 }
 
 template <int KCAP, int LPC, int WPB, bool HG, bool FORCE = false, bool F32 = false, bool MCP = false>
@@ -3681,11 +3720,12 @@ hipError_t launch_lucy(const LucyArgs &a, int64_t max_len, hipStream_t st) {
 
 hipError_t launch_posterior(const PosteriorArgs &a, hipStream_t st) {
   if (a.n_wave == 0) return hipSuccess;
-  const int64_t nb = (a.n_wave + 255) / 256;
+  const int64_t nb = (a.n_wave + 3) / 4;  // four wavefronts, one waveform each
   hipLaunchKernelGGL(posterior_kernel, dim3((unsigned)nb), dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && (a.rhat || a.mcse_chains || a.lambda_hat)) {
-    hipLaunchKernelGGL(posterior_extra_kernel, dim3((unsigned)nb), dim3(256), 0, st, a);
+    const int lds_k = a.lambda_hat && a.kz + 1 <= 2048 ? a.kz + 1 : 0;
+    hipLaunchKernelGGL(posterior_extra_kernel, dim3((unsigned)nb), dim3(256), sizeof(double) * 4 * lds_k, st, a, lds_k);
     e = hipGetLastError();
   }
   if (e == hipSuccess && a.occupancy) {
