@@ -259,15 +259,14 @@ bool finite(double v) { return std::isfinite(v); }
 // The LDS kernels in the form of the device-memory ones (corrected from capacity 48 up, to
 // capacity 160): not a design a caller sets, but where routed_design sends a bucket.
 constexpr int kDesignLds = 4;
-static const int64_t kLdsChains[kNumCaps] = {1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30};
 
 bool design_available(const fsmp_ctx *c, int kcap, int design) {
   const bool fp32 = c->cfg.precision == FSMP_FP32_REFRESH;
   const bool mcp = c->cfg.n_mix > 0;
   switch (design) {
-    case FSMP_DESIGN_GROUP: return !fp32 && !mcp && chain_lds_supported(kcap, false, c->tab.M, c->cfg.grid_sub);
+    case FSMP_DESIGN_GROUP: return !fp32 && !mcp && chain_lds_supported(kcap, false, false);
     case kDesignLds:
-      return !fp32 && !mcp && chain_lds_supported(kcap, kcap >= 48, c->tab.M, c->cfg.grid_sub);
+      return !fp32 && chain_lds_supported(kcap, kcap >= 48, mcp);
     case FSMP_DESIGN_LANE: return !fp32 && !mcp && (kcap == 16 || kcap == 32);
     case FSMP_DESIGN_GROUP_DEVMEM: return chain_dm_supported(kcap, c->tab.M, c->cfg.grid_sub, fp32, mcp);
     case FSMP_DESIGN_GROUP_DEVMEM_WIDE:
@@ -283,15 +282,44 @@ int effective_design(const fsmp_ctx *c, int kcap, int design) {
   return FSMP_DESIGN_GROUP_DEVMEM;
 }
 
-// The kernels a bucket of `cnt` chains runs: the effective design; but where the caller has not
-// set one, or has set the wide device-memory groups, the LDS kernels for as many chains as
-// kLdsChains.
+// Up to this many chains per capacity the LDS kernels end before the device-memory groups.  Few
+// chains: the latency of a sweep decides (LDS 4-12 us, device memory 8-98 us); many: the LDS
+// holds fewer chains per CU than the device-memory groups run.  Both sides on windows of 512
+// samples with the lists at their length, microseconds per sweep of the whole launch, LDS /
+// narrow groups:
+//   capacity 16: 8,000 chains 4.9 / 8.1, 24,000 14.1 / 9.9;  32: 24,000 29.5 / 35, 64,000 75 / 66;
+//   48: 1,000 4.0 / 12.0, 8,000 22.3 / 16.0;  64: 1,000 4.3 / 10.9, 8,000 32.1 / 25.5;
+//   96: 1,000 11.6 / 34, 4,000 31.9 / 45.9;  128: 1,000 16 / 41, 4,000 56 / 67;
+//   160: 1,000 34 / 61, 4,000 128 / 124;  192: 4,000 155 / 278.
+// Against the wide groups (chosen for sweep counts that differ 8x, where their longest chains
+// take 47-79 ms of 4,000 sweeps and LDS 17-35): always up to capacity 64, where they take
+// 7-11 ns per chain and sweep against 1-4, and while the LDS share of a mean chain stays below
+// that latency above.
+constexpr int64_t kAnyChains = INT64_MAX;
+static const int64_t kLdsChains[kNumCaps] = {14000, 32000, 5500, 3500, 6000, 5000, 3800, kAnyChains};
+static const int64_t kLdsChainsWide[kNumCaps] = {kAnyChains, kAnyChains, kAnyChains, kAnyChains,
+                                                 5500, 4000, 2000, kAnyChains};
+// FP32-refresh form, up to this many chains the wide groups (16 lanes per chain) at capacities 16
+// and 32: 4,000 chains x 100 sweeps 1.08 against 1.43 ms and 1.40 against 2.69; 16,000 at
+// capacity 16 2.45 against 1.69, at 32 wide also at 64,000 (10.9 against 18.6).
+static const int64_t kF32WideChains[kNumCaps] = {8000, kAnyChains};
+
+// The kernels a bucket of `cnt` chains runs: the design the caller (or the autotuner) has set;
+// where none is set, and for the wide device-memory groups, by the number of chains.  Past the
+// LDS kernels' range an unset capacity 16 runs the narrow groups (64,000 chains x 200 sweeps:
+// 4.2 ms against 6.9 ms with a lane per chain).
 int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
   const int dz = effective_design(c, kCaps[q], c->design[q]);
-  if ((!c->design_set[q] || dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE) && cnt <= kLdsChains[q] &&
-      design_available(c, kCaps[q], kDesignLds))
-    return kDesignLds;
-  return dz;
+  const bool wide = dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE;
+  if (c->design_set[q] && !wide) return dz;
+  if (c->cfg.precision == FSMP_FP32_REFRESH)
+    return !wide && cnt <= kF32WideChains[q] && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM_WIDE)
+               ? (int)FSMP_DESIGN_GROUP_DEVMEM_WIDE
+               : dz;
+  if (cnt <= (wide ? kLdsChainsWide : kLdsChains)[q] && design_available(c, kCaps[q], kDesignLds)) return kDesignLds;
+  return dz == FSMP_DESIGN_LANE && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM)
+             ? (int)FSMP_DESIGN_GROUP_DEVMEM
+             : dz;
 }
 
 // device-memory doubles of a bucket's chain state in a design
@@ -1103,7 +1131,10 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     if (!c->fork) e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(c->fork, st);
   }
-  for (int bi = 0; bi < kNumCaps && e == hipSuccess; ++bi) {
+  // the largest capacity first: its chains take most of a CU's LDS each, and the wavefronts of the
+  // smaller ones then fill what is left (the other way round the large ones wait until a CU is
+  // nearly empty)
+  for (int bi = kNumCaps - 1; bi >= 0 && e == hipSuccess; --bi) {
     const int64_t cnt = bucket_start[bi + 1] - bucket_start[bi];
     if (cnt == 0) continue;
     hipStream_t ks = st;

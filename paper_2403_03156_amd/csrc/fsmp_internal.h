@@ -174,7 +174,7 @@ hipError_t launch_lucy(const LucyArgs &a, int64_t max_len, hipStream_t st);
 // Launchers (fsmp_kernels.hip).  Each returns hipSuccess or the launch error.
 hipError_t launch_prologue(const PrologueArgs &a, hipStream_t st);
 hipError_t launch_posterior(const PosteriorArgs &a, hipStream_t st);
-// lane groups with H in LDS (FP64, single charge law, no replay); `corr`: the corrected form,
+// lane groups with H in LDS (FP64, no replay; the mixture law in the corrected form only); `corr`: the corrected form,
 // capacities 48 and up, whose exact G is in dws (lds_ws_doubles); without it capacities up to 64
 hipError_t launch_chain_lds(int kcap, bool corr, const ChainArgs &a, hipStream_t st, int32_t *lanes,
                             int64_t *blocks);
@@ -190,7 +190,7 @@ constexpr int kNumCaps = 8;
 constexpr size_t kMaxOvp = 8u << 20;  // bytes of the table of partial overlap sums
 constexpr int kMaxRise = 1024;  // longest rise table (8 KB of LDS beside the overlap tables)
 constexpr int kCaps[kNumCaps] = {16, 32, 48, 64, 96, 128, 160, 192};
-bool chain_lds_supported(int kcap, bool corr, int M, int sub);  // the LDS instance exists and fits
+bool chain_lds_supported(int kcap, bool corr, bool mcp);  // the LDS instance exists and fits
 // lane groups with H in device memory (FP64, or FP32 in the precision form; `wide`: the
 // wider groups, FP64 sampling with the single charge law only): dws must hold
 // group_dm_ws_doubles(kcap, n_list, fp32, wide)

@@ -1731,23 +1731,25 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
 // device memory and reads it once per accepted move, for the residual.  (Taking its elements
 // from the overlap table in LDS instead was slower: 27.7 -> 36.5 ms for 873 chains of 500 sweeps
 // at capacity 128; the lanes' gathers conflict.)
-constexpr int kLdsWaves = 8;  // wavefronts of a workgroup at most
-template <int KCAP, int LPC, bool CORR>
+//
+// MCP: the Gaussian-mixture charge law, every PE with its component (el).
+template <int KCAP, int LPC, bool CORR, bool MCP>
 struct LdsLayout {
   static constexpr bool kSym = KCAP >= 96;
   static constexpr int kW = LPC > kWave ? LPC / kWave : 1;  // wavefronts of a chain
   static constexpr int kMat = kSym ? (KCAP / 2 + 1) * KCAP : KCAP * KCAP;
   static constexpr int kVec = kSym ? 2 * KCAP : KCAP;  // the two scratch vectors (twice in a row when wrapped)
-  static constexpr int kStash = LPC >= kWave ? 0 : 6;  // random values per lane (registers from a wavefront up)
   // Lanes over which a vector's sums are taken: element i belongs to lane i mod kRO, which adds its
   // elements in order before the butterfly over the kRO lanes.  Every wavefront of a chain forms
   // the whole sum so, from LDS (no exchange of partial sums); 16 at capacity 48 and 32 at 64 are
   // the orders of the narrow device-memory groups, whose chains this design repeats bit for bit
   // there (as their products and edits are taken in the same order and rounding).
-  static constexpr int kRO = KCAP <= 32 ? LPC : KCAP == 48 ? 16 : 32;
-  // matrix, two scratch vectors, x (b and the residual too in the corrected form), the PE list,
-  // the random values of the next LPC sweeps
-  static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 + kStash * LPC;
+  // The mixture form does so at 16 and 32 too (4 lanes): with one component it is the single
+  // law's chains in those groups.
+  static constexpr int kRO = KCAP <= 32 ? (MCP ? 4 : LPC) : KCAP == 48 ? 16 : 32;
+  // matrix, two scratch vectors, x (b and the residual too in the corrected form), the PE list (and
+  // the components)
+  static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 * (MCP ? 2 : 1);
 };
 
 // the overlap of two columns, as overlap(), with the window-edge sums from the table of partial
@@ -1957,16 +1959,16 @@ __device__ inline double chain_sum(int gl, F f) {
 
 // G^-1 of the PE list zl[0..N) by bordering into the (finite) matrix D, each step the birth
 // update of the inverse of the leading block; va, vb: the scratch vectors.  False if a Schur
-// complement is not positive.
+// complement is not positive.  el: the PEs' mixture components, or null.
 template <int KCAP, int LPC, bool SYM, int RO>
 __device__ bool lds_build(const ModelDev &md, const double *vtab, const double *ov, int Lw, double *D, double *va,
-                          double *vb, const int *zl, int N, int lane, int gl) {
+                          double *vb, const int *zl, int N, int lane, int gl, const int *el) {
   const bool own = KCAP % LPC == 0 || lane < KCAP;  // a lane with an element
   for (int k = 0; k < N; ++k) {
     const int gk = zl[k];
     chain_sync<LPC>();
     if (own) lds_vec<KCAP, SYM>(va, lane, lane < k ? overlap_edge(md, vtab, ov, gk, zl[lane], Lw) : 0.0);
-    const double d = overlap_edge(md, vtab, ov, gk, gk, Lw) + md.rho;
+    const double d = overlap_edge(md, vtab, ov, gk, gk, Lw) + (el ? md.mix_rho[el[k]] : md.rho);
     chain_sync<LPC>();
     const double e = lane < k ? lds_dot<KCAP, SYM>(D, va, lane, k) : 0.0;
     if (own) lds_vec<KCAP, SYM>(vb, lane, e);
@@ -1985,43 +1987,41 @@ __device__ bool lds_build(const ModelDev &md, const double *vtab, const double *
 }
 
 // The Gibbs / RJMCMC chains of chain_kernel (the same moves, acceptances and random numbers;
-// FP64, single charge law) with G^-1 in LDS.
-template <int KCAP, int LPC, bool CORR>
-__global__ void __launch_bounds__(kLdsWaves *kWave) __attribute__((amdgpu_waves_per_eu(2)))
+// FP64) with G^-1 in LDS.
+template <int KCAP, int LPC, bool CORR, bool MCP>
+__global__ void __launch_bounds__(LPC > kWave ? LPC : kWave) __attribute__((amdgpu_waves_per_eu(2)))
 chain_lds_kernel(ChainArgs a) {
-  using CL = LdsLayout<KCAP, LPC, CORR>;
+  using CL = LdsLayout<KCAP, LPC, CORR, MCP>;
   constexpr bool SYM = CL::kSym;
   constexpr int RO = CL::kRO;
   constexpr int W = CL::kW, CPW = LPC < kWave ? kWave / LPC : 1;
   static_assert(LPC >= 16 && LPC >= KCAP, "one element of the vectors per lane");
   extern __shared__ double smem[];
   const ModelDev &md = a.md;
-  // the overlap table in LDS where the wavefronts of a workgroup share it, in device memory (a
-  // few reads per sweep, from the caches) where a workgroup is one chain: the LDS then holds
-  // two chains of capacity 128 per CU
-  constexpr bool OVL = W == 1;
-  double *ovl = smem;
-  double *rt = smem + (OVL ? md.sub * md.M : 0);
+  // A workgroup is one wavefront (or one chain of several), so that chains of every capacity pack
+  // into the LDS of a CU side by side; the overlap table stays in device memory (a few reads per
+  // sweep, from the caches), only the rise factors and the logs are copied.  (Workgroups of four
+  // wavefronts around one copy of the tables filled a CU each: the launches of a call ran one
+  // after the other, 10.9 instead of PACK_FIG ms for 8,000 windows of the mixture law.)
+  double *rt = smem;
   double *lgn = rt + md.rise_n;
-  if constexpr (OVL)
-    for (int i = threadIdx.x; i < md.sub * md.M; i += blockDim.x) ovl[i] = a.ovl[i];
-  const double *ov = OVL ? ovl : a.ovl;
+  const double *ov = a.ovl;
   for (int i = threadIdx.x; i < md.rise_n; i += blockDim.x) rt[i] = md.rtab[i];
   for (int i = threadIdx.x; i < KCAP + 2; i += blockDim.x) lgn[i] = log((double)i);
   __syncthreads();
   // lane: the index in the chain's group (its element of the vectors); l64 in the wavefront
   // (gl in the part of a wavefront that the group is)
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), l64 = threadIdx.x % kWave;
+  const int l64 = threadIdx.x % kWave;
   const int grp = LPC < kWave ? l64 / LPC : 0, gbase = grp * LPC;
   const int lane = W > 1 ? (int)threadIdx.x : l64 % LPC, gl = W > 1 ? l64 : lane;
   constexpr int GW = LPC < kWave ? LPC : kWave;  // lanes that share the per-chain scalars' work
-  const int64_t slot = W > 1 ? (int64_t)blockIdx.x : ((int64_t)blockIdx.x * (blockDim.x / kWave) + wv) * CPW + grp;
+  const int64_t slot = (int64_t)blockIdx.x * CPW + grp;
   if (slot >= a.n_list) return;
-  double *D = lgn + (KCAP + 2) + (W > 1 ? 0 : (int64_t)(wv * CPW + grp) * CL::kDoubles);
+  double *D = lgn + (KCAP + 2) + grp * CL::kDoubles;
   double *va = D + CL::kMat, *vb = va + CL::kVec, *xl = vb + CL::kVec;
   double *bl = CORR ? xl + KCAP : nullptr, *sl = CORR ? bl + KCAP : nullptr;
   int *zl = (int *)(xl + (CORR ? 3 : 1) * KCAP);
-  double *stash = (double *)(zl + 2 * ((KCAP + 1) / 2));
+  int *el = zl + 2 * ((KCAP + 1) / 2);  // (the mixture form's components)
   double *Gm = CORR ? a.dws + slot * (int64_t)(KCAP * KCAP) : nullptr;
 
   const int64_t c = a.chains[slot];
@@ -2044,18 +2044,16 @@ chain_lds_kernel(ChainArgs a) {
 
   for (int k = lane; k <= a.kz; k += LPC) a.nhist[c * (a.kz + 1) + k] = 0;
   for (int k = lane; k < CL::kMat + 2 * CL::kVec + (CORR ? 3 : 1) * KCAP; k += LPC) D[k] = 0.0;
-  for (int k = lane; k < KCAP; k += LPC) zl[k] = 0;
+  for (int k = lane; k < KCAP * (MCP ? 2 : 1); k += LPC) zl[k] = 0;
   if constexpr (CORR)
     for (int k = lane; k < KCAP * KCAP; k += LPC) Gm[k] = 0.0;
   chain_sync_mem<LPC>();
 
   double t0 = a.t0init[w];
   int N = 0;
-  T0Terms tc{};
-  if (glo <= ghi) {
-    tc = t0_terms<GW>(md, t0, glo, ghi, gl, gbase);
-    t0_phi(md, tc);
-  }
+  // (an empty T has no points at or after t0: Phi is 0)
+  T0Terms tc = t0_terms<GW>(md, t0, glo, ghi, gl, gbase);
+  t0_phi(md, tc);
   double Lam = lam * md.dt * tc.Phi;
   const bool biexp = md.kind == FSMP_PHI_BIEXP;
   int gmin = INT32_MAX;  // smallest PE grid index
@@ -2104,7 +2102,7 @@ chain_lds_kernel(ChainArgs a) {
       const int32_t *z0 = a.zinit + a.zinit_off[c];
       if (lane < n0) zl[lane] = z0[lane];
       chain_sync<LPC>();
-      if (lds_build<KCAP, LPC, SYM, RO>(md, a.vtab, ov, Lw, D, va, vb, zl, n0, lane, gl)) {
+      if (lds_build<KCAP, LPC, SYM, RO>(md, a.vtab, ov, Lw, D, va, vb, zl, n0, lane, gl, nullptr)) {
         const double b = lane < n0 ? mf[zl[lane] - glo] + md.rhom : 0.0;
         if (KCAP % LPC == 0 || lane < KCAP) lds_vec<KCAP, SYM>(va, lane, b);
         chain_sync<LPC>();
@@ -2137,7 +2135,7 @@ chain_lds_kernel(ChainArgs a) {
   int run_n = -1, run_s = 0;  // N of the current run among the recorded steps, its first step
   int b_left = lb, in_batch = nb * lb;
   int ref_left = a.refresh_M;
-  uint32_t st_r3 = 0, st_r4 = 0, st_r5 = 0;
+  uint32_t st_r3 = 0, st_r4 = 0, st_r5 = 0, st_r7 = 0;
   double st_l2 = 0.0, st_l6 = 0.0, st_xt = 0.0, st_xs = 0.0;
 
   for (int step = 0; step < n_steps; ++step) {
@@ -2148,9 +2146,9 @@ chain_lds_kernel(ChainArgs a) {
         if (ref_left == 0) {
           ref_left = a.refresh_M;
           if (N > 0) {
-            if (lds_build<KCAP, LPC, SYM, RO>(md, a.vtab, ov, Lw, D, va, vb, zl, N, lane, gl)) {
+            if (lds_build<KCAP, LPC, SYM, RO>(md, a.vtab, ov, Lw, D, va, vb, zl, N, lane, gl, MCP ? el : nullptr)) {
               if (KCAP % LPC == 0 || lane < KCAP)
-                lds_vec<KCAP, SYM>(va, lane, lane < N ? mf[zl[lane] - glo] + md.rhom : 0.0);
+                lds_vec<KCAP, SYM>(va, lane, lane < N ? mf[zl[lane] - glo] + (MCP ? md.mix_rhom[el[lane]] : md.rhom) : 0.0);
               chain_sync<LPC>();
               if (lane < N) xl[lane] = lds_dot<KCAP, SYM>(D, va, lane, N);
               residual();
@@ -2163,8 +2161,8 @@ chain_lds_kernel(ChainArgs a) {
       }
     }
     // ---- random values: every GW sweeps each lane makes those of one of the next GW (both
-    // Philox blocks, the three logs, the Box-Muller pair); a sweep reads its own, from lane
-    // registers from a wavefront per chain up, else from LDS
+    // Philox blocks, the three logs, the Box-Muller pair); a sweep reads its own, by lane reads
+    // from a wavefront per chain up, else by lane permutes
     const int sl_ = step & (GW - 1);
     if (sl_ == 0) {
       uint32_t q0[4], q1[4];
@@ -2179,38 +2177,29 @@ chain_lds_kernel(ChainArgs a) {
       st_r3 = q0[3];
       st_r4 = q1[0];
       st_r5 = q1[1];
-      if constexpr (LPC < kWave) {
-        WAVE_SYNC();
-        double *q = stash + lane * 6;
-        q[0] = st_xt;
-        q[1] = st_xs;
-        q[2] = st_l2;
-        q[3] = st_l6;
-        ((uint32_t *)q)[8] = st_r3;
-        ((uint32_t *)q)[9] = st_r4;
-        ((uint32_t *)q)[10] = st_r5;
-        WAVE_SYNC();
-      }
+      st_r7 = q1[3];
     }
-    uint32_t r3, r4, r5;
+    uint32_t r3, r4, r5, r7 = 0;
     double lg2, lg6, xi_t0, xi_sh;
     if constexpr (LPC >= kWave) {
       r3 = (uint32_t)__builtin_amdgcn_readlane((int)st_r3, sl_);
       r4 = (uint32_t)__builtin_amdgcn_readlane((int)st_r4, sl_);
       r5 = (uint32_t)__builtin_amdgcn_readlane((int)st_r5, sl_);
+      if constexpr (MCP) r7 = (uint32_t)__builtin_amdgcn_readlane((int)st_r7, sl_);
       lg2 = lane_value(st_l2, sl_);
       lg6 = lane_value(st_l6, sl_);
       xi_t0 = lane_value(st_xt, sl_);
       xi_sh = lane_value(st_xs, sl_);
     } else {
-      const double *q = stash + sl_ * 6;
-      xi_t0 = q[0];
-      xi_sh = q[1];
-      lg2 = q[2];
-      lg6 = q[3];
-      r3 = ((const uint32_t *)q)[8];
-      r4 = ((const uint32_t *)q)[9];
-      r5 = ((const uint32_t *)q)[10];
+      const int from = gbase + sl_;
+      r3 = (uint32_t)__shfl((int)st_r3, from, kWave);
+      r4 = (uint32_t)__shfl((int)st_r4, from, kWave);
+      r5 = (uint32_t)__shfl((int)st_r5, from, kWave);
+      if constexpr (MCP) r7 = (uint32_t)__shfl((int)st_r7, from, kWave);
+      lg2 = __shfl(st_l2, from, kWave);
+      lg6 = __shfl(st_l6, from, kWave);
+      xi_t0 = __shfl(st_xt, from, kWave);
+      xi_sh = __shfl(st_xs, from, kWave);
     }
 
     // ---- Gibbs half-step 1: t0 by Metropolis-Hastings
@@ -2219,8 +2208,7 @@ chain_lds_kernel(ChainArgs a) {
     if (t0p >= md.t0_min && t0p <= md.t0_max) {
       const double xmin = (N > 0) ? (double)gmin * md.dt - t0p : 1.0;
       if (biexp ? (xmin > 0.0) : (xmin >= 0.0)) {
-        T0Terms tp = tc;
-        if (glo <= ghi) tp = t0_terms<GW>(md, t0p, glo, ghi, gl, gbase);
+        T0Terms tp = t0_terms<GW>(md, t0p, glo, ghi, gl, gbase);
         double S = 0.0;  // sum over the PEs of log r(t0p) / r(t0), r the rise factor
         if (biexp && N > 0) {
           double pn = 1.0, pc = 1.0;
@@ -2235,7 +2223,7 @@ chain_lds_kernel(ChainArgs a) {
           }
           S = group_sum<GW>(log(pn / pc));
         }
-        if (glo <= ghi) t0_phi(md, tp);
+        t0_phi(md, tp);
         const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
         const double la0 = part - (lam * md.dt * tp.Phi - lam * md.dt * tc.Phi);
         if (lg2 < la0) {
@@ -2253,6 +2241,22 @@ chain_lds_kernel(ChainArgs a) {
     int j = -1, gnew = -1, sh = 0;
     bool valid = false, need_mv = false;
     double dnu = 0.0, la = -INFINITY, lpd = 0.0, pr_sh = 1.0;
+    // mixture form: the component of a born or updated PE from word r7 (inverse CDF of the
+    // weights); rho, its log, rho mu, rho mu^2 of the new and of the removed / moved PE
+    int enew = 0;
+    bool same = true;  // an update keeps the PE's component
+    double rn = md.rho, lrn = md.log_rho, rmn = md.rhom, rm2n = md.rhom2;
+    double lro = md.log_rho, rm2o = md.rhom2;
+    if constexpr (MCP) {
+      const double ue = u01(r7);
+      enew = md.n_mix - 1;
+      for (int q = md.n_mix - 2; q >= 0; --q)
+        if (ue < md.mix_cdf[q]) enew = q;
+      rn = md.mix_rho[enew];
+      lrn = md.mix_lrho[enew];
+      rmn = md.mix_rhom[enew];
+      rm2n = md.mix_rhom2[enew];
+    }
     if (move == 1) {
       if (N >= kmax) {
         st |= FSMP_ST_KMAX;
@@ -2262,18 +2266,23 @@ chain_lds_kernel(ChainArgs a) {
       }
     } else {
       j = group_uniform<LPC>((int)(((uint64_t)r4 * (uint64_t)N) >> 32));
+      if constexpr (MCP) {
+        lro = md.mix_lrho[el[j]];
+        rm2o = md.mix_rhom2[el[j]];
+        same = move != 3 || enew == el[j];
+      }
       if (move == 3) {
         const int gj = zl[j];
         sh = (int)rint(xi_sh * md.shift_sd / md.dt);
         gnew = gj + sh;
         const double xnew = (double)gnew * md.dt - t0;
         if (gnew >= glo && gnew <= ghi && (biexp ? xnew > 0.0 : xnew >= 0.0)) {
-          if (sh == 0) {
+          if (sh == 0 && same) {
             valid = true;
             la = 0.0;
           } else {
             lpd = (double)(gj - gnew) * md.dt * md.inv_tau2;
-            if (biexp) pr_sh = rise_at(md, rt, tc, t0, gnew) / rise_at(md, rt, tc, t0, gj);
+            if (biexp && sh != 0) pr_sh = rise_at(md, rt, tc, t0, gnew) / rise_at(md, rt, tc, t0, gj);
             need_mv = true;
           }
         }
@@ -2303,7 +2312,7 @@ chain_lds_kernel(ChainArgs a) {
       inv_om = 1.0 / om;
     }
     if (need_mv) {
-      const double d = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + md.rho;
+      const double d = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + rn;
       if (lane < N) eta = lds_dot<KCAP, SYM>(D, va, lane, N);
       double q, p;
       if constexpr (RO == LPC) {
@@ -2322,7 +2331,7 @@ chain_lds_kernel(ChainArgs a) {
         q -= ej * ej / om;
         p -= ej * xj / om;
       }
-      beta = mfv + md.rhom;
+      beta = mfv + rmn;
       delta2 = d - q;
       up = beta - p;
       inv_d2 = 1.0 / delta2;
@@ -2334,13 +2343,15 @@ chain_lds_kernel(ChainArgs a) {
         double l0, l1, l2;
         group_log3<GW>(move == 1 ? delta2 : om, move == 3 ? delta2 : Lam, pr_sh, gl, gbase, l0, l1, l2);
         if (move == 1) {
-          dnu = -0.5 * (-md.log_rho + l0 + (md.rhom2 - up * up * inv_d2) * md.inv_s);
+          dnu = -0.5 * (-lrn + l0 + (rm2n - up * up * inv_d2) * md.inv_s);
           la = dnu + l1 - lgn[N + 1] + (N == 0 ? md.logJ : 0.0);
         } else if (move == 2) {
-          dnu = 0.5 * (-md.log_rho - l0 + (md.rhom2 - xj * xj * inv_om) * md.inv_s);
+          dnu = 0.5 * (-lro - l0 + (rm2o - xj * xj * inv_om) * md.inv_s);
           la = dnu - l1 + lgn[N] - (N == 1 ? md.logJ : 0.0);
         } else {
           dnu = 0.5 * (-l0 - l1 + (up * up * inv_d2 - xj * xj * inv_om) * md.inv_s);
+          // mixture form: the removed and the added PE carry their own rho and rho mu^2
+          if constexpr (MCP) dnu += 0.5 * (lrn - lro + (rm2o - rm2n) * md.inv_s);
           la = dnu + (lpd + l2);
         }
         valid = true;
@@ -2349,7 +2360,7 @@ chain_lds_kernel(ChainArgs a) {
       }
     }
     const bool accepted = group_uniform<LPC>(valid && lg6 < la) != 0;
-    const bool edits = accepted && (move != 3 || sh != 0);
+    const bool edits = accepted && (move != 3 || sh != 0 || !same);
     c_p += (lane == 0) | (lane == move);
     c_a += (lane == 0 && t0acc) | (lane == move && accepted);
     if (a.work) {
@@ -2410,9 +2421,10 @@ chain_lds_kernel(ChainArgs a) {
           lds_set<KCAP, SYM>(D, r, r, inv_d2);
           if (move == 1) xl[r] = xn;
           zl[r] = gnew;
+          if constexpr (MCP) el[r] = enew;
           if constexpr (CORR) {
             bl[r] = beta;
-            Gm[r * KCAP + r] = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + md.rho;
+            Gm[r * KCAP + r] = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + rn;
           }
         }
         if (move == 1) N++;
@@ -2425,6 +2437,7 @@ chain_lds_kernel(ChainArgs a) {
           if constexpr (CORR) gv = Gm[last * KCAP + lane];
         }
         zlast = zl[last];
+        const int elast = MCP ? el[last] : 0;
         xlast = xl[last];
         if constexpr (CORR) blast = bl[last];
         chain_sync<LPC>();
@@ -2440,6 +2453,7 @@ chain_lds_kernel(ChainArgs a) {
           }
           if (lane == j) {
             zl[j] = zlast;
+            if constexpr (MCP) el[j] = elast;
             xl[j] = xlast;
             if constexpr (CORR) bl[j] = blast;
           }
@@ -2548,6 +2562,7 @@ chain_lds_kernel(ChainArgs a) {
   for (int k = lane; k < kz; k += LPC) {
     a.z[c * kz + k] = k < N ? zl[k] : -1;
     a.charge[c * kz + k] = k < N ? xl[k] : 0.0;
+    if (MCP && a.comp) a.comp[c * kz + k] = k < N ? el[k] : -1;
   }
   if (lane < 3) {
     double *ac = a.acc + c * 12;
@@ -3784,69 +3799,82 @@ static size_t chain_lds_bytes(const GroupCfg &g, int M, int sub, bool hg, bool f
   return sizeof(double) * ((size_t)M * (1 + sub) + (size_t)g.kcap + 2 + (size_t)cpb * per);
 }
 
-// lanes per chain and LDS doubles of one chain of the LDS instances (0: no such instance)
-static int lds_chain_doubles(int kcap, bool corr, int *lpc) {
-  *lpc = kcap <= 32 ? kcap : kcap <= 64 ? 64 : kcap <= 128 ? 128 : 192;
+// lanes per chain and LDS doubles of one chain of the LDS instances (0: no such instance); `corr`
+// means what it does in launch_chain_lds
+template <bool MCP>
+static int lds_chain_doubles_t(int kcap, bool corr) {
   switch (kcap) {
-    case 16: return corr ? 0 : LdsLayout<16, 16, false>::kDoubles;
-    case 32: return corr ? 0 : LdsLayout<32, 32, false>::kDoubles;
-    case 48: return corr ? LdsLayout<48, 64, true>::kDoubles : LdsLayout<48, 64, false>::kDoubles;
-    case 64: return corr ? LdsLayout<64, 64, true>::kDoubles : LdsLayout<64, 64, false>::kDoubles;
-    case 96: return corr ? LdsLayout<96, 128, true>::kDoubles : 0;
-    case 128: return corr ? LdsLayout<128, 128, true>::kDoubles : 0;
-    case 160: return corr ? LdsLayout<160, 192, true>::kDoubles : 0;
-    case 192: return corr ? LdsLayout<192, 192, true>::kDoubles : 0;
+    case 16: return corr ? 0 : LdsLayout<16, 16, false, MCP>::kDoubles;
+    case 32: return corr ? 0 : LdsLayout<32, 32, false, MCP>::kDoubles;
+    case 48: return LdsLayout<48, 64, true, MCP>::kDoubles;  // (the uncorrected form takes less)
+    case 64: return LdsLayout<64, 64, true, MCP>::kDoubles;
+    case 96: return corr ? LdsLayout<96, 128, true, MCP>::kDoubles : 0;
+    case 128: return corr ? LdsLayout<128, 128, true, MCP>::kDoubles : 0;
+    case 160: return corr ? LdsLayout<160, 192, true, MCP>::kDoubles : 0;
+    case 192: return corr ? LdsLayout<192, 192, true, MCP>::kDoubles : 0;
     default: return 0;
   }
 }
+static int lds_chain_doubles(int kcap, bool corr, bool mcp, int *lpc) {
+  *lpc = kcap <= 32 ? kcap : kcap <= 64 ? 64 : kcap <= 128 ? 128 : 192;
+  if (!mcp && !corr && kcap == 48) return LdsLayout<48, 64, false, false>::kDoubles;
+  if (!mcp && !corr && kcap == 64) return LdsLayout<64, 64, false, false>::kDoubles;
+  if (mcp && !corr && kcap >= 48) return 0;
+  return mcp ? lds_chain_doubles_t<true>(kcap, corr) : lds_chain_doubles_t<false>(kcap, corr);
+}
 
-// LDS bytes of a workgroup of `waves` wavefronts (one chain in the groups wider than a
-// wavefront) without the rise table
-static size_t lds_block_bytes(int kcap, bool corr, int M, int sub, int waves) {
+// LDS bytes of a workgroup (one wavefront, or one chain of several) without the rise table
+static size_t lds_block_bytes(int kcap, bool corr, bool mcp) {
   int lpc;
-  const int per = lds_chain_doubles(kcap, corr, &lpc);
-  if (lpc > kWave) return sizeof(double) * ((size_t)kcap + 2 + per);
-  return sizeof(double) * ((size_t)M * sub + (size_t)kcap + 2 + (size_t)waves * (kWave / lpc) * per);
+  const int per = lds_chain_doubles(kcap, corr, mcp, &lpc);
+  return sizeof(double) * ((size_t)kcap + 2 + (size_t)(lpc < kWave ? kWave / lpc : 1) * per);
 }
 
 size_t lds_ws_doubles(int kcap, bool corr, int64_t n_list) { return corr ? (size_t)n_list * kcap * kcap : 0; }
 
-bool chain_lds_supported(int kcap, bool corr, int M, int sub) {
+bool chain_lds_supported(int kcap, bool corr, bool mcp) {
   int lpc;
-  return lds_chain_doubles(kcap, corr, &lpc) > 0 && lds_block_bytes(kcap, corr, M, sub, 1) <= 160 * 1024;
+  return lds_chain_doubles(kcap, corr, mcp, &lpc) > 0 && lds_block_bytes(kcap, corr, mcp) <= 160 * 1024;
 }
 
-template <int KCAP, int LPC, bool CORR>
+template <int KCAP, int LPC, bool CORR, bool MCP = false>
 static hipError_t launch_chain_lds_t(const ChainArgs &args, hipStream_t st, int32_t *lanes, int64_t *blocks) {
   ChainArgs a = args;
-  constexpr int W = LdsLayout<KCAP, LPC, CORR>::kW, CPW = LPC < kWave ? kWave / LPC : 1;
-  const int64_t units = (a.n_list + CPW - 1) / CPW;  // wavefronts, or chains of several
+  constexpr int W = LdsLayout<KCAP, LPC, CORR, MCP>::kW, CPW = LPC < kWave ? kWave / LPC : 1;
   *lanes = LPC;
-  *blocks = 0;
-  if (units == 0) return hipSuccess;
+  *blocks = (a.n_list + CPW - 1) / CPW;
+  if (*blocks == 0) return hipSuccess;
   if (CORR && a.dws == nullptr) return hipErrorInvalidValue;
-  // As many wavefronts per workgroup as share one copy of the tables: what the LDS holds when the
-  // chains fill the chip, fewer (down to one) so that a small launch spreads over the 256 CUs.
-  // The rise table only where it fits beside one wavefront.
-  const size_t kLds = 160 * 1024, rise = sizeof(double) * a.md.rise_n;
-  if (lds_block_bytes(KCAP, CORR, a.md.M, a.md.sub, 1) + rise > kLds) a.md.rise_n = 0;
-  const size_t extra = sizeof(double) * a.md.rise_n;
-  int w = W > 1 ? 1 : (int)std::min<int64_t>(kLdsWaves, (units + 255) / 256);
-  while (w > 1 && lds_block_bytes(KCAP, CORR, a.md.M, a.md.sub, w) + extra > kLds) --w;
-  const size_t lds = lds_block_bytes(KCAP, CORR, a.md.M, a.md.sub, w) + extra;
+  // the rise table where it fits
+  const size_t kLds = 160 * 1024;
+  size_t lds = lds_block_bytes(KCAP, CORR, MCP);
+  if (lds + sizeof(double) * a.md.rise_n > kLds) a.md.rise_n = 0;
+  lds += sizeof(double) * a.md.rise_n;
   if (lds > kLds) return hipErrorInvalidValue;  // the host checks the configurations against this
   if (lds > 64 * 1024) {
-    (void)hipFuncSetAttribute((const void *)chain_lds_kernel<KCAP, LPC, CORR>,
+    (void)hipFuncSetAttribute((const void *)chain_lds_kernel<KCAP, LPC, CORR, MCP>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     (void)hipGetLastError();
   }
-  *blocks = (units + w - 1) / w;
-  hipLaunchKernelGGL((chain_lds_kernel<KCAP, LPC, CORR>), dim3((unsigned)*blocks), dim3(kWave * W * w), lds, st, a);
+  hipLaunchKernelGGL((chain_lds_kernel<KCAP, LPC, CORR, MCP>), dim3((unsigned)*blocks), dim3(kWave * W), lds, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_chain_lds(int kcap, bool corr, const ChainArgs &a, hipStream_t st, int32_t *lanes,
                             int64_t *blocks) {
+  if (a.md.n_mix > 0) {
+    switch (kcap) {
+      case 16: return launch_chain_lds_t<16, 16, false, true>(a, st, lanes, blocks);
+      case 32: return launch_chain_lds_t<32, 32, false, true>(a, st, lanes, blocks);
+      case 48: return launch_chain_lds_t<48, 64, true, true>(a, st, lanes, blocks);
+      case 64: return launch_chain_lds_t<64, 64, true, true>(a, st, lanes, blocks);
+      case 96: return launch_chain_lds_t<96, 128, true, true>(a, st, lanes, blocks);
+      case 128: return launch_chain_lds_t<128, 128, true, true>(a, st, lanes, blocks);
+      case 160: return launch_chain_lds_t<160, 192, true, true>(a, st, lanes, blocks);
+      case 192: return launch_chain_lds_t<192, 192, true, true>(a, st, lanes, blocks);
+      default: return hipErrorInvalidValue;
+    }
+  }
   if (corr) {
     switch (kcap) {
       case 48: return launch_chain_lds_t<48, 64, true>(a, st, lanes, blocks);
