@@ -151,10 +151,11 @@ struct LucyArgs {
   const float *wave;
   const int64_t *woff;     // [n+1]
   const int32_t *kmax;     // [n]
+  const int32_t *order;    // the launch's waveforms
   const double *kern;      // [LVp] V(s) / sum V, zero-padded to LVp (a multiple of 24)
   const double *kern_rev;  // [LVp] kern[LV - 1 - s], zero beyond LV
   int32_t LV, LVp, sub, n_iter, kz;
-  int64_t n_wave;
+  int64_t n_wave;          // waveforms of the launch
   double inv_area;         // 1 / sum_s V(s): deconvolved flux -> PE charge
   double threshold;
   int32_t margin;          // ns

@@ -3550,31 +3550,34 @@ __device__ inline void lucy_corr(const double *X, ConstD k, int LVp, int i0, dou
   }
 }
 
-__global__ void __launch_bounds__(256) lucy_kernel(LucyArgs a) {
+// The data are float32: they are kept so in LDS (half the bytes of a double, one more window of
+// 2,048 samples per CU).
+__global__ void __launch_bounds__(512) lucy_kernel(LucyArgs a) {
   extern __shared__ double lds[];
   const int LV = a.LV, LVp = a.LVp;
   const ConstD K = (ConstD)a.kern;       // [LVp] K[s], zero beyond LV
   const ConstD Kr = (ConstD)a.kern_rev;  // [LVp] K[LV - 1 - s], zero beyond LV
-  __shared__ double redl[8];
+  __shared__ double redl[8];  // (at most eight wavefronts)
   __shared__ int redc[8];
   constexpr int R1 = kLucyR1, R2 = kLucyR2;
-  for (int64_t w = blockIdx.x; w < a.n_wave; w += gridDim.x) {
+  for (int64_t wi = blockIdx.x; wi < a.n_wave; wi += gridDim.x) {
+    const int64_t w = a.order[wi];
     const int Lw = (int)(a.woff[w + 1] - a.woff[w]);
     const int ntau = Lw + LV - 1;
     const int nd = (Lw + R1 - 1) / R1 * R1;       // d zero-padded to whole first-sum chunks
     const int n2 = (ntau + R2 - 1) / R2 * R2;     // outputs of the second sum, whole chunks
     const int nu = n2 + LVp + R1;                 // elements of u (zero beyond ntau)
     const int nrp = n2 + LVp + R2;                // elements of rp: LV - 1 zeros | ratio | zeros
-    double *d = lds;                              // [nd], plain layout
-    double *u = d + nd;                           // skewed by R1
+    double *u = lds;                              // skewed by R1
     double *rp = u + lsk<R1>(nu) + 1;             // skewed by R2
+    float *d = (float *)(rp + lsk<R2>(nrp) + 1);  // [nd], plain layout
     const float *x = a.wave + a.woff[w];
     __syncthreads();
     double sd = 0.0;
     for (int t = threadIdx.x; t < nd; t += blockDim.x) {
-      const double v = t < Lw ? fmax((double)x[t], 0.0) : 0.0;
+      const float v = t < Lw ? fmaxf(x[t], 0.0f) : 0.0f;
       d[t] = v;
-      sd += v;
+      sd += (double)v;
     }
     for (int o = 32; o > 0; o >>= 1) sd += __shfl_xor(sd, o);
     if ((threadIdx.x & 63) == 0) redl[threadIdx.x >> 6] = sd;
@@ -3595,7 +3598,7 @@ __global__ void __launch_bounds__(256) lucy_kernel(LucyArgs a) {
         for (int j = 0; j < R1; ++j) {
           // exact division: w^r decays to denormals where d is 0 (0 / w^r must stay 0)
           const double v = acc[j];
-          const double q = d[c0 + j] / v;
+          const double q = (double)d[c0 + j] / v;
           rp[lsk<R2>(LV - 1 + c0 + j)] = v > 0.0 ? q : 0.0;
         }
       }
@@ -3627,7 +3630,7 @@ __global__ void __launch_bounds__(256) lucy_kernel(LucyArgs a) {
     double *flag = u;  // plain layout from here on
     for (int i = threadIdx.x; i < Lw; i += blockDim.x) {
       const bool c = qh[i + LV - 1] > a.threshold;   // tau = i >= 0
-      d[i] = c ? 1.0 : 0.0;
+      d[i] = c ? 1.0f : 0.0f;
       cnt += c;
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -3650,7 +3653,7 @@ __global__ void __launch_bounds__(256) lucy_kernel(LucyArgs a) {
     if (cnt > kmax) {
       // keep the kmax largest qhat (ties: earlier tau): rank every candidate
       for (int i = threadIdx.x; i < Lw; i += blockDim.x) {
-        if (d[i] == 0.0) {
+        if (d[i] == 0.0f) {
           flag[i] = 0.0;
           continue;
         }
@@ -3663,13 +3666,13 @@ __global__ void __launch_bounds__(256) lucy_kernel(LucyArgs a) {
         flag[i] = rank < kmax ? 1.0 : 0.0;
       }
       __syncthreads();
-      for (int i = threadIdx.x; i < Lw; i += blockDim.x) d[i] = flag[i];
+      for (int i = threadIdx.x; i < Lw; i += blockDim.x) d[i] = (float)flag[i];
       __syncthreads();
     }
     if (threadIdx.x == 0) {
       int t_min = -1, t_max = -1;
       for (int i = 0; i < Lw; ++i)
-        if (d[i] != 0.0) {
+        if (d[i] != 0.0f) {
           if (t_min < 0) t_min = i;
           t_max = i;
         }
@@ -3684,7 +3687,7 @@ __global__ void __launch_bounds__(256) lucy_kernel(LucyArgs a) {
       } else {
         t0 = fmin(fmax(t_min - 0.5 / sub, a.t0_min), a.t0_max);
         for (int i = t_min; i <= t_max; ++i)
-          if (d[i] != 0.0 && i - t0 > 0.0 && n < a.kz) a.z[w * (int64_t)a.kz + n++] = sub * i;
+          if (d[i] != 0.0f && i - t0 > 0.0 && n < a.kz) a.z[w * (int64_t)a.kz + n++] = sub * i;
         a.g_range[2 * w] = max(0, sub * (t_min - a.margin));
         a.g_range[2 * w + 1] = min(sub * Lw - 1, sub * (t_max + a.margin));
         a.cut[2 * w] = max(0, t_min - a.margin);
@@ -3713,8 +3716,8 @@ size_t lucy_lds_bytes(int64_t Lw, int LVp) {
   const int64_t ntau = Lw + LVp - 1;
   const int64_t nd = (Lw + R1 - 1) / R1 * R1, n2 = (ntau + R2 - 1) / R2 * R2;
   const int64_t nu = n2 + LVp + R1, nrp = n2 + LVp + R2;
-  // d, then u and rp, each skewed by one pad element per window width
-  return sizeof(double) * (size_t)(nd + (nu + nu / R1 + 1) + (nrp + nrp / R2 + 1));
+  // u and rp, each skewed by one pad element per window width, then d
+  return sizeof(double) * (size_t)((nu + nu / R1 + 1) + (nrp + nrp / R2 + 1)) + sizeof(float) * (size_t)((nd + 1) / 2 * 2);
 }
 
 hipError_t launch_lucy(const LucyArgs &a, int64_t max_len, hipStream_t st) {
@@ -3723,7 +3726,7 @@ hipError_t launch_lucy(const LucyArgs &a, int64_t max_len, hipStream_t st) {
   // enough threads for the longer pass of the longest window, in whole wavefronts
   const int64_t chunks = std::max((max_len + kLucyR1 - 1) / kLucyR1, (max_len + a.LV - 1 + kLucyR2 - 1) / kLucyR2);
   int threads = (int)((chunks + 63) / 64 * 64);
-  threads = threads < 64 ? 64 : (threads > 256 ? 256 : threads);
+  threads = threads < 64 ? 64 : (threads > 512 ? 512 : threads);
   if (lds > 64 * 1024) {
     (void)hipFuncSetAttribute((const void *)lucy_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     (void)hipGetLastError();
