@@ -1741,12 +1741,11 @@ struct LdsLayout {
   static constexpr int kVec = kSym ? 2 * KCAP : KCAP;  // the two scratch vectors (twice in a row when wrapped)
   // Lanes over which a vector's sums are taken: element i belongs to lane i mod kRO, which adds its
   // elements in order before the butterfly over the kRO lanes.  Every wavefront of a chain forms
-  // the whole sum so, from LDS (no exchange of partial sums); 16 at capacity 48 and 32 at 64 are
-  // the orders of the narrow device-memory groups, whose chains this design repeats bit for bit
-  // there (as their products and edits are taken in the same order and rounding).
-  // The mixture form does so at 16 and 32 too (4 lanes): with one component it is the single
-  // law's chains in those groups.
-  static constexpr int kRO = KCAP <= 32 ? (MCP ? 4 : LPC) : KCAP == 48 ? 16 : 32;
+  // the whole sum so, from LDS (no exchange of partial sums).  Up to capacity 64 these are the
+  // orders of the narrow device-memory groups, whose chains this design repeats bit for bit
+  // there (products and edits too are taken in the same order and rounding): a chain's result
+  // does not depend on which of the two its launch is given.
+  static constexpr int kRO = KCAP <= 32 ? 4 : KCAP == 48 ? 16 : 32;
   // matrix, two scratch vectors, x (b and the residual too in the corrected form), the PE list (and
   // the components)
   static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 * (MCP ? 2 : 1);
@@ -2315,18 +2314,12 @@ chain_lds_kernel(ChainArgs a) {
       const double d = overlap_edge(md, a.vtab, ov, gnew, gnew, Lw) + rn;
       if (lane < N) eta = lds_dot<KCAP, SYM>(D, va, lane, N);
       double q, p;
-      if constexpr (RO == LPC) {
-        q = group_sum<RO>(gam * eta);
-        p = group_sum<RO>(lane < N ? gam * xl[lane] : 0.0);
-        if (move == 3) ej = __shfl(eta, gbase + j, kWave);
-      } else {
-        if (KCAP % LPC == 0 || lane < KCAP) vb[lane] = eta;
-        chain_sync<LPC>();
-        q = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], vb[i], t); });
-        p = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], xl[i], t); });
-        if constexpr (CORR) p += chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(vb[i], sl[i], t); });
-        if (move == 3) ej = vb[j];
-      }
+      if (KCAP % LPC == 0 || lane < KCAP) vb[lane] = eta;
+      chain_sync<LPC>();
+      q = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], vb[i], t); });
+      p = chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(va[i], xl[i], t); });
+      if constexpr (CORR) p += chain_sum<KCAP, RO>(gl, [&](int i, double t) { return fma(vb[i], sl[i], t); });
+      if (move == 3) ej = vb[j];
       if (move == 3) {
         q -= ej * ej / om;
         p -= ej * xj / om;
