@@ -22,6 +22,9 @@ FLAGS = [
     # hoisted out of the loop they fill the 256 registers and spill; left in place they are
     # scalar moves beside the vector work.
     "-mllvm", "-disable-machine-licm",
+    # The launch arguments of the kernel that holds the chains of four capacities have more uses
+    # than the optimiser follows by default: it then copies them to scratch memory.
+    "-mllvm", "-instcombine-max-copied-from-constant-users=5000",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

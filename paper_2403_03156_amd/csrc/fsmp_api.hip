@@ -1083,8 +1083,38 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   ca.zinit_off = (b->z_init_offsets && n > 0) ? d_zinit_off : nullptr;
   ca.refresh_M = cf.refresh_M;
   ca.drift_bound = 1e-3;
+  // the LDS buckets of capacities up to 64 in one launch (its leader is the largest of them)
+  // where all their workgroups run at once; not while launches are timed, nor for the mixture law
+  auto bucket_n = [&](int bi) { return bucket_start[bi + 1] - bucket_start[bi]; };
+  LdsMix mix{};
+  int mix_leader = -1;
+  bool mix_corr = false;
+  bool in_mix[kNumCaps] = {};
+  if (!c->timing && !c->serial && cf.n_mix == 0 && !force) {
+    int members = 0;
+    bool corr48 = false, plain48 = false;
+    for (int bi = 0; bi < kNumCaps; ++bi) {
+      const int mi = lds_mix_index(caps[bi]), dz = bucket_n(bi) > 0 ? design_of(bi) : -1;
+      if (mi < 0 || (dz != FSMP_DESIGN_GROUP && dz != kDesignLds)) continue;
+      in_mix[bi] = true;
+      ++members;
+      mix_leader = bi;
+      if (caps[bi] >= 48) (dz == kDesignLds ? corr48 : plain48) = true;
+      mix.chains[mi] = d_chains + bucket_start[bi];
+      mix.n_list[mi] = bucket_n(bi);
+      mix.dws[mi] = lane_doff[bi + 1] > lane_doff[bi] ? d_lane + lane_doff[bi] : nullptr;
+      mix.dscr[mi] = ca.qdraw ? d_draw + draw_off[bi] : nullptr;
+    }
+    mix_corr = corr48;
+    int64_t at_once = 0;
+    if (members < 2 || (corr48 && plain48) || lds_mix_blocks(mix, mix_corr, ca.md.rise_n, &at_once) > at_once) {
+      mix_leader = -1;
+      for (bool &v : in_mix) v = false;
+    }
+  }
+  auto launched = [&](int bi) { return bucket_n(bi) > 0 && (!in_mix[bi] || bi == mix_leader); };
   int n_buckets = 0;
-  for (int bi = 0; bi < kNumCaps; ++bi) n_buckets += bucket_start[bi + 1] > bucket_start[bi];
+  for (int bi = 0; bi < kNumCaps; ++bi) n_buckets += launched(bi);
   // the allocation-free variant runs the buckets one after the other on the caller's stream
   const bool fan = n_buckets > 1 && !noalloc && !c->serial;
   // Lanes of concurrent work: the caller's stream and up to GPU_MAX_HW_QUEUES - 1 side
@@ -1121,7 +1151,7 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     for (int r = 0; r < n_buckets; ++r) {
       int best = -1;
       for (int bi = 0; bi < kNumCaps; ++bi)
-        if (!done[bi] && bucket_start[bi + 1] > bucket_start[bi] && (best < 0 || cost[bi] > cost[best])) best = bi;
+        if (!done[bi] && launched(bi) && (best < 0 || cost[bi] > cost[best])) best = bi;
       int ln = 0;
       for (int k = 1; k < n_lanes; ++k)
         if (load[k] < load[ln]) ln = k;
@@ -1140,7 +1170,7 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   // nearly empty)
   for (int bi = kNumCaps - 1; bi >= 0 && e == hipSuccess; --bi) {
     const int64_t cnt = bucket_start[bi + 1] - bucket_start[bi];
-    if (cnt == 0) continue;
+    if (!launched(bi)) continue;
     hipStream_t ks = st;
     // lane 0 is the caller's stream, lane k > 0 side stream k - 1
     const bool side = fork_join && lane_of[bi] > 0;
@@ -1166,6 +1196,11 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     ca.dscr = ca.qdraw ? d_draw + draw_off[bi] : nullptr;
     e = timed(name, caps[bi], ks, [&](fsmp_timing &t) {
       t.chains = cnt;
+      if (bi == mix_leader) {
+        t.chains = mix.n_list[0] + mix.n_list[1] + mix.n_list[2] + mix.n_list[3];
+        t.lanes = caps[bi] >= 48 ? 64 : caps[bi];
+        return launch_chain_lds_mix(mix_corr, ca, mix, ks, &t.blocks);
+      }
       return dz == FSMP_DESIGN_LANE    ? launch_chain_lane(caps[bi], ca, ks, &t.lanes, &t.blocks)
              : dz == FSMP_DESIGN_GROUP ? launch_chain_lds(caps[bi], false, ca, ks, &t.lanes, &t.blocks)
              : dz == kDesignLds        ? launch_chain_lds(caps[bi], caps[bi] >= 48, ca, ks, &t.lanes, &t.blocks)
@@ -1180,7 +1215,7 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   // the caller's stream waits for the side lanes after its own buckets are enqueued
   if (fork_join)
     for (int bi = 0; bi < kNumCaps && e == hipSuccess; ++bi)
-      if (bucket_start[bi + 1] > bucket_start[bi] && lane_of[bi] > 0) e = hipStreamWaitEvent(st, c->join[bi], 0);
+      if (launched(bi) && lane_of[bi] > 0) e = hipStreamWaitEvent(st, c->join[bi], 0);
   if (c->capture) {
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(c->capture, &g);

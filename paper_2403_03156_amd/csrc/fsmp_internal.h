@@ -180,6 +180,17 @@ hipError_t launch_posterior(const PosteriorArgs &a, hipStream_t st);
 hipError_t launch_chain_lds(int kcap, bool corr, const ChainArgs &a, hipStream_t st, int32_t *lanes,
                             int64_t *blocks);
 size_t lds_ws_doubles(int kcap, bool corr, int64_t n_list);
+// the buckets of capacities 64, 48, 32 and 16 (index 0 to 3) in one launch
+struct LdsMix {
+  const int32_t *chains[4];
+  int64_t n_list[4];
+  double *dws[4], *dscr[4];
+  int64_t end[4];  // first workgroup after the bucket's
+};
+int lds_mix_index(int kcap);  // 0 to 3, or -1
+// workgroups of the launch, and how many of them the chip's LDS holds at once
+int64_t lds_mix_blocks(const LdsMix &m, bool corr, int rise_n, int64_t *at_once);
+hipError_t launch_chain_lds_mix(bool corr, const ChainArgs &a, LdsMix m, hipStream_t st, int64_t *blocks);
 hipError_t launch_overlap_partial(const double *vtab, double *out, int sub, int M, int LV, hipStream_t st);
 // lane-per-chain variant (FP64, capacities 16 and 32); dws / iws must hold lane_ws_doubles /
 // lane_ws_ints(kcap, n_list)

@@ -1987,15 +1987,19 @@ __device__ bool lds_build(const ModelDev &md, const double *vtab, const double *
 
 // The Gibbs / RJMCMC chains of chain_kernel (the same moves, acceptances and random numbers;
 // FP64) with G^-1 in LDS.
+// bk: the launch's chains; block: the workgroup's index among theirs.
+struct LdsBucket {
+  const int32_t *chains;
+  int64_t n_list;
+  double *dws, *dscr;
+};
 template <int KCAP, int LPC, bool CORR, bool MCP>
-__global__ void __launch_bounds__(LPC > kWave ? LPC : kWave) __attribute__((amdgpu_waves_per_eu(2)))
-chain_lds_kernel(ChainArgs a) {
+__device__ __attribute__((always_inline)) inline void chain_lds_body(const ChainArgs &a, const LdsBucket &bk, int64_t block, double *smem) {
   using CL = LdsLayout<KCAP, LPC, CORR, MCP>;
   constexpr bool SYM = CL::kSym;
   constexpr int RO = CL::kRO;
   constexpr int W = CL::kW, CPW = LPC < kWave ? kWave / LPC : 1;
   static_assert(LPC >= 16 && LPC >= KCAP, "one element of the vectors per lane");
-  extern __shared__ double smem[];
   const ModelDev &md = a.md;
   // A workgroup is one wavefront (or one chain of several), so that chains of every capacity pack
   // into the LDS of a CU side by side; the overlap table stays in device memory (a few reads per
@@ -2014,16 +2018,16 @@ chain_lds_kernel(ChainArgs a) {
   const int grp = LPC < kWave ? l64 / LPC : 0, gbase = grp * LPC;
   const int lane = W > 1 ? (int)threadIdx.x : l64 % LPC, gl = W > 1 ? l64 : lane;
   constexpr int GW = LPC < kWave ? LPC : kWave;  // lanes that share the per-chain scalars' work
-  const int64_t slot = (int64_t)blockIdx.x * CPW + grp;
-  if (slot >= a.n_list) return;
+  const int64_t slot = block * CPW + grp;
+  if (slot >= bk.n_list) return;
   double *D = lgn + (KCAP + 2) + grp * CL::kDoubles;
   double *va = D + CL::kMat, *vb = va + CL::kVec, *xl = vb + CL::kVec;
   double *bl = CORR ? xl + KCAP : nullptr, *sl = CORR ? bl + KCAP : nullptr;
   int *zl = (int *)(xl + (CORR ? 3 : 1) * KCAP);
   int *el = zl + 2 * ((KCAP + 1) / 2);  // (the mixture form's components)
-  double *Gm = CORR ? a.dws + slot * (int64_t)(KCAP * KCAP) : nullptr;
+  double *Gm = CORR ? bk.dws + slot * (int64_t)(KCAP * KCAP) : nullptr;
 
-  const int64_t c = a.chains[slot];
+  const int64_t c = bk.chains[slot];
   const int64_t w = c / a.n_chains;
   const int Lw = (int)(a.woff[w + 1] - a.woff[w]);
   const double lam = a.lam[w];
@@ -2510,7 +2514,7 @@ chain_lds_kernel(ChainArgs a) {
         // factorisation runs from the last PE backwards on a copy of H's lower triangle in the
         // chain's device-memory scratch; y = R xi accumulates column by column
         const int64_t rec = c * a.n_rec + i / a.thin;
-        double *Ad = a.dscr + slot * (int64_t)(KCAP * KCAP + KCAP);
+        double *Ad = bk.dscr + slot * (int64_t)(KCAP * KCAP + KCAP);
         double *Av = Ad + KCAP * KCAP;  // the column being eliminated
         chain_sync_mem<LPC>();
         bool ok = true;
@@ -2583,6 +2587,32 @@ chain_lds_kernel(ChainArgs a) {
       wk[4] = 0.0;
     }
   }
+}
+
+template <int KCAP, int LPC, bool CORR, bool MCP>
+__global__ void __launch_bounds__(LPC > kWave ? LPC : kWave) __attribute__((amdgpu_waves_per_eu(2)))
+chain_lds_kernel(ChainArgs a) {
+  extern __shared__ double smem[];
+  chain_lds_body<KCAP, LPC, CORR, MCP>(a, LdsBucket{a.chains, a.n_list, a.dws, a.dscr}, blockIdx.x, smem);
+}
+
+// The buckets of capacities up to 64 in one launch, for calls whose workgroups all fit the chip at
+// once: as launches of their own they need a hardware queue each to run side by side, and streams
+// share queues as HIP deals them (one server event of 1,200 channels: two of its three launches
+// ran one after the other: 8.4 ms the call, 4.7 in one launch; 1,000 short windows 7.4, 6.5).
+template <bool CORR>
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
+chain_lds_mix_kernel(ChainArgs a, LdsMix m) {
+  extern __shared__ double smem[];
+  const int64_t b = blockIdx.x;
+  if (b < m.end[0])
+    chain_lds_body<64, 64, CORR, false>(a, LdsBucket{m.chains[0], m.n_list[0], m.dws[0], m.dscr[0]}, b, smem);
+  else if (b < m.end[1])
+    chain_lds_body<48, 64, CORR, false>(a, LdsBucket{m.chains[1], m.n_list[1], m.dws[1], m.dscr[1]}, b - m.end[0], smem);
+  else if (b < m.end[2])
+    chain_lds_body<32, 32, false, false>(a, LdsBucket{m.chains[2], m.n_list[2], m.dws[2], m.dscr[2]}, b - m.end[1], smem);
+  else
+    chain_lds_body<16, 16, false, false>(a, LdsBucket{m.chains[3], m.n_list[3], m.dws[3], m.dscr[3]}, b - m.end[2], smem);
 }
 
 // ------------------------------------------------------------------ chains, one lane each
@@ -3889,6 +3919,49 @@ hipError_t launch_chain_lds(int kcap, bool corr, const ChainArgs &a, hipStream_t
     case 64: return launch_chain_lds_t<64, 64, false>(a, st, lanes, blocks);
     default: return hipErrorInvalidValue;
   }
+}
+
+static constexpr int kMixCap[4] = {64, 48, 32, 16};
+
+int lds_mix_index(int kcap) {
+  for (int q = 0; q < 4; ++q)
+    if (kMixCap[q] == kcap) return q;
+  return -1;
+}
+
+// LDS of a workgroup of the mixed launch: its largest bucket's
+static size_t lds_mix_bytes(const LdsMix &m, bool corr, int rise_n) {
+  size_t lds = 0;
+  for (int q = 0; q < 4; ++q)
+    if (m.n_list[q] > 0) lds = std::max(lds, lds_block_bytes(kMixCap[q], corr && kMixCap[q] >= 48, false));
+  return lds + sizeof(double) * rise_n;
+}
+
+int64_t lds_mix_blocks(const LdsMix &m, bool corr, int rise_n, int64_t *at_once) {
+  int64_t nb = 0;
+  for (int q = 0; q < 4; ++q) {
+    const int64_t cpw = q < 2 ? 1 : kWave / kMixCap[q];
+    nb += (m.n_list[q] + cpw - 1) / cpw;
+  }
+  *at_once = 256 * std::min<int64_t>(8, (int64_t)(160 * 1024 / (lds_mix_bytes(m, corr, rise_n) + 256)));
+  return nb;
+}
+
+hipError_t launch_chain_lds_mix(bool corr, const ChainArgs &a, LdsMix m, hipStream_t st, int64_t *blocks) {
+  int64_t nb = 0;
+  for (int q = 0; q < 4; ++q) {
+    const int64_t cpw = q < 2 ? 1 : kWave / kMixCap[q];
+    nb += (m.n_list[q] + cpw - 1) / cpw;
+    m.end[q] = nb;
+    if (corr && q < 2 && m.n_list[q] > 0 && m.dws[q] == nullptr) return hipErrorInvalidValue;
+  }
+  *blocks = nb;
+  if (nb == 0) return hipSuccess;
+  const size_t lds = lds_mix_bytes(m, corr, a.md.rise_n);  // (the tables fit beside every one of these)
+  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  if (corr) hipLaunchKernelGGL((chain_lds_mix_kernel<true>), dim3((unsigned)nb), dim3(kWave), lds, st, a, m);
+  else hipLaunchKernelGGL((chain_lds_mix_kernel<false>), dim3((unsigned)nb), dim3(kWave), lds, st, a, m);
+  return hipGetLastError();
 }
 
 hipError_t launch_overlap_partial(const double *vtab, double *out, int sub, int M, int LV, hipStream_t st) {
