@@ -24,7 +24,9 @@
  *   - every chain draws its random numbers from Philox4x32-10 (Salmon et al., SC'11)
  *     with key (seed lo, seed hi) and counter (step, block, uid lo, uid hi),
  *     uid = wave_id * n_chains + chain: a chain's result does not depend on the batch
- *     it runs in, on the launch shape or on the other chains.
+ *     it runs in, on the launch shape or on the other chains (from PE capacity 96 up the
+ *     kernel, and with it the rounding of the charges' last bits, follows the number of
+ *     chains; up to 64 both kernels round alike.  fsmp_set_design fixes it).
  *   - pointers marked "device" are HIP device memory of the context's device; pointers
  *     marked "host" are ordinary host memory read during the call.  The caller owns every
  *     buffer it passes; the context owns its tables and workspace.
@@ -440,6 +442,14 @@ fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
  * and 32 in the FP32-refresh form, 16 lanes per chain), for batches whose longest chains
  * set the launch's duration.  Capacities are 16, 32, 48, 64, 96, 128, 160, 192; a waveform
  * runs in the smallest one >= its kmax.  capacity 0 = every capacity that has the design.
+ * A capacity whose design is not set (by this call, the autotuner or FSMP_CHAIN_DESIGN) runs
+ * the LDS kernels, which exist in the library for every capacity and the mixture law, in the
+ * corrected form from 48 up, for as many chains as they are the faster ones for (14,000 at
+ * capacity 16 to 3,800 at 160), and the narrow device-memory groups beyond; the FP32 form its
+ * wide groups for few chains.  FSMP_DESIGN_GROUP_DEVMEM_WIDE stands for the kernels that shorten
+ * a sweep: it too runs the LDS kernels while the chains are few enough (always up to capacity
+ * 64, 5,500 chains at 96 to 2,000 at 160).  Small calls run the LDS chains of all capacities up
+ * to 64 in one launch, unless timings are on.
  * FSMP_ENOTSUP if the requested pair does not exist.  The FP32-refresh form runs
  * FSMP_DESIGN_GROUP_DEVMEM and its wide groups (capacity 48 at 64); the mixture charge law
  * FSMP_DESIGN_GROUP_DEVMEM only; replays run FSMP_DESIGN_GROUP_DEVMEM, or

@@ -203,13 +203,11 @@ struct fsmp_ctx {
   DevBuf<double> lane_d;
   DevBuf<int32_t> lane_i;
   DevBuf<double> draw_scr;  // charge draws: KCAP (KCAP + 1) FP64 words per chain
-  DevBuf<double> ovp;       // partial overlap sums (ModelDev::ovp)
   DevBuf<double> ptab;      // light-curve partial-sum factors (ModelDev::ptab)
   // per PE capacity (kCaps), FSMP_DESIGN_*: 0 = lane group per chain, H in LDS
   // (capacities up to 64); 1 = one lane per chain, state in device memory; 2 = lane group
-  // per chain, H in device memory.  Defaults from the batched 100k-waveform measurement:
-  // one lane per chain wins at capacity 16 (few PEs, the serial work shared by 64 chains),
-  // the device-memory groups everywhere above.
+  // per chain, H in device memory.  While a capacity's design is not set (design_set),
+  // routed_design picks its kernels by the number of chains.
   int design[kNumCaps] = {1, 2, 2, 2, 2, 2, 2, 2};
   bool design_set[kNumCaps] = {};  // set by fsmp_set_design, the autotuner or the environment
   PinBuf stage;
@@ -320,6 +318,16 @@ int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
   return dz == FSMP_DESIGN_LANE && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM)
              ? (int)FSMP_DESIGN_GROUP_DEVMEM
              : dz;
+}
+
+// Whether the mixed-precision form's capacity-16 chains run in the launch of capacity 32 (no design
+// set; both in the wide groups of 16 lanes, so their sums and their outputs are the same): a
+// launch less to find a hardware queue for.  4,000 windows of 5 capacities on 4 queues: 12.4 ms
+// with a launch of its own, 10.2 together.
+bool f32_joined(const fsmp_ctx *c, int64_t cnt16, int64_t cnt32) {
+  return c->cfg.precision == FSMP_FP32_REFRESH && !c->design_set[0] && !c->design_set[1] && cnt16 > 0 && cnt32 > 0 &&
+         cnt16 + cnt32 <= kF32WideChains[0] && design_available(c, 32, FSMP_DESIGN_GROUP_DEVMEM_WIDE) &&
+         design_available(c, 16, FSMP_DESIGN_GROUP_DEVMEM_WIDE);
 }
 
 // device-memory doubles of a bucket's chain state in a design
@@ -549,16 +557,18 @@ fsmp_status fsmp_create(fsmp_ctx **out, const fsmp_ser *ser, const fsmp_intensit
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(device);
   hipError_t e = hipMalloc((void **)&c->d_vtab, sizeof(double) * c->tab.M);
-  if (e == hipSuccess) e = hipMalloc((void **)&c->d_ovl, sizeof(double) * c->tab.ovl.size());
+  // the overlap table, and behind it the table of its partial sums
+  size_t n_ovp = c->tab.ovl.size() * (size_t)(c->tab.LV + 1);
+  if (n_ovp * sizeof(double) > kMaxOvp) n_ovp = 0;
+  if (e == hipSuccess) e = hipMalloc((void **)&c->d_ovl, sizeof(double) * (c->tab.ovl.size() + n_ovp));
   if (e == hipSuccess) e = hipMemcpy(c->d_vtab, c->tab.vtab.data(), sizeof(double) * c->tab.M, hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipMemcpy(c->d_ovl, c->tab.ovl.data(), sizeof(double) * c->tab.ovl.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage_done, hipEventDisableTiming);
-  const size_t n_ovp = c->tab.ovl.size() * (size_t)(c->tab.LV + 1);
-  if (e == hipSuccess && n_ovp * sizeof(double) <= kMaxOvp) {
-    e = c->ovp.ensure(n_ovp);
-    if (e == hipSuccess) e = launch_overlap_partial(c->d_vtab, c->ovp.p, c->tab.sub, c->tab.M, c->tab.LV, nullptr);
-    c->md.ovp = c->ovp.p;
+  if (e == hipSuccess && n_ovp > 0) {
+    double *p = c->d_ovl + c->tab.ovl.size();
+    e = launch_overlap_partial(c->d_vtab, p, c->tab.sub, c->tab.M, c->tab.LV, nullptr);
+    c->md.ovp = p;
   }
   if (e == hipSuccess) e = ensure_ptab(c, 0);  // (synchronises the device)
   if (e == hipSuccess) {
@@ -616,7 +626,6 @@ void fsmp_destroy(fsmp_ctx *c) {
   c->lane_d.release();
   c->draw_scr.release();
   c->ptab.release();
-  c->ovp.release();
   c->lane_i.release();
   c->stage.release();
   (void)hipSetDevice(prev);
@@ -642,6 +651,10 @@ size_t fsmp_workspace_bytes(const fsmp_ctx *c, const fsmp_batch *b) {
     if (fp32 && kc == 48) kc = 64;
     for (int q = 0; q < kNumCaps; ++q)
       if (kCaps[q] == kc) cnt[q] += cf.n_chains;
+  }
+  if (f32_joined(c, cnt[0], cnt[1])) {
+    cnt[1] += cnt[0];
+    cnt[0] = 0;
   }
   // batch metadata, chain lists, matched filter over T
   size_t bytes = (size_t)(n + 1) * 16 + (size_t)n * (8 + 8 + 4 + 8 + 8 + 4 + 4) + (size_t)n * cf.n_chains * 4 + grid * 8;
@@ -839,11 +852,20 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     if (sbin(x) != sbin(y)) return sbin(x) > sbin(y);
     return b->lambda[x] < b->lambda[y] || (b->lambda[x] == b->lambda[y] && x < y);
   });
+  int64_t cnt16 = 0, cnt32 = 0;
+  if (fp32)
+    for (int64_t i = 0; i < n; ++i) {
+      const int kc = chain_kcap_for(kmx[i]);
+      cnt16 += kc == 16 ? cf.n_chains : 0;
+      cnt32 += kc == 32 ? cf.n_chains : 0;
+    }
+  const bool joined = fp32 && f32_joined(c, cnt16, cnt32);
   for (int bi = 0; bi < kNumCaps; ++bi) {
     bucket_start[bi] = n_order;
     for (int64_t ii = 0; ii < n; ++ii) {
       const int64_t i = wsorted[ii];
       int kc = chain_kcap_for(kmx[i]);
+      if (joined && kc == 16) kc = 32;
       if (fp32 && kc == 48) kc = 64;  // the precision form has no capacity-48 instance
       if (kc != caps[bi]) continue;
       for (int ch = 0; ch < cf.n_chains; ++ch) order[n_order++] = (int32_t)(i * cf.n_chains + ch);
@@ -1351,7 +1373,11 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   for (int d = 0; d < kDesigns && st == FSMP_OK; ++d) {
     for (int q = 0; q < kNumCaps; ++q) {
       ms[d][q] = -1.0;
-      c->design[q] = design_available(c, kCaps[q], d) ? d : saved_design[q];
+      // (the LDS design at 48 and 64 has no residual correction: the wide design runs the same
+      // kernels with it and is tried in its place)
+      const bool tried = design_available(c, kCaps[q], d) &&
+                         !(d == FSMP_DESIGN_GROUP && kCaps[q] >= 48 && design_available(c, kCaps[q], kDesignLds));
+      c->design[q] = tried ? d : saved_design[q];
     }
     st = fsmp_sample(c, &bt, &o, hip_stream);
     if (st != FSMP_OK) break;

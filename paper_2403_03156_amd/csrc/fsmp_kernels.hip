@@ -1773,8 +1773,12 @@ __device__ inline double overlap_edge(const ModelDev &md, const double *vtab, co
 
 // partial sums of the stationary overlaps, [sub][M][LV + 1]: entry m sums the first m samples
 // that both columns see (in increasing order, as the direct sum)
-__global__ void __launch_bounds__(256) overlap_partial_kernel(const double *vtab, double *out, int sub, int M, int LV) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(64) overlap_partial_kernel(const double *vtab_g, double *out, int sub, int M, int LV) {
+  extern __shared__ double smem[];
+  double *vtab = smem;
+  for (int i = threadIdx.x; i < M; i += blockDim.x) vtab[i] = vtab_g[i];
+  __syncthreads();
+  const int t = blockIdx.x * 64 + threadIdx.x;
   if (t >= sub * M) return;
   const int p = t / M, d = t % M;
   const int n0 = (p + d + sub - 1) / sub, n1 = (p + M - 1) / sub;
@@ -2063,10 +2067,11 @@ __device__ __attribute__((always_inline)) inline void chain_lds_body(const Chain
   double Q = 0.0;        // sum of the charge means, changes with accepted moves only
 
   // After the list has changed: the residual s = b - G x against the exact G (corrected form) and
-  // Q.  Rows of G in chunks of 16, the loads of a chunk in flight together (rows and elements
-  // past N are zero or meet a zero x).  From capacity 96 up every kRefine changes x first takes
+  // Q.  Rows of G in chunks of RG, the loads of a chunk in flight together (rows and elements
+  // past N are zero or meet a zero x; chunks of 32 measured no faster).  From capacity 96 up every kRefine changes x first takes
   // up H s: an edit leaves about kappa eps in x, and without the refinement those add up over the
   // chain (at N ~ 30 the total charge after 600 sweeps is 3.5e-15 off instead of 3.2e-14).
+  constexpr int RG = 16;
   constexpr int kRefine = 16;
   int to_refine = kRefine;
   auto residual = [&]() {
@@ -2075,12 +2080,12 @@ __device__ __attribute__((always_inline)) inline void chain_lds_body(const Chain
       const bool refine = SYM && --to_refine == 0;
       for (int pass = refine ? 0 : 1; pass < 2; ++pass) {
         double r = 0.0;
-        for (int k0 = 0; k0 < N; k0 += 16) {
-          double g[16];
+        for (int k0 = 0; k0 < N; k0 += RG) {
+          double g[RG];
 #pragma unroll
-          for (int u = 0; u < 16; ++u) g[u] = gp[(k0 + u) * KCAP];
+          for (int u = 0; u < RG; ++u) g[u] = gp[(k0 + u) * KCAP];
 #pragma unroll
-          for (int u = 0; u < 16; ++u) r = fma(g[u], xl[k0 + u], r);
+          for (int u = 0; u < RG; ++u) r = fma(g[u], xl[k0 + u], r);
         }
         const double rs = lane < N ? bl[lane] - r : 0.0;
         if (pass == 0) {
@@ -3965,8 +3970,8 @@ hipError_t launch_chain_lds_mix(bool corr, const ChainArgs &a, LdsMix m, hipStre
 }
 
 hipError_t launch_overlap_partial(const double *vtab, double *out, int sub, int M, int LV, hipStream_t st) {
-  hipLaunchKernelGGL(overlap_partial_kernel, dim3((unsigned)((sub * M + 255) / 256)), dim3(256), 0, st, vtab, out, sub,
-                     M, LV);
+  hipLaunchKernelGGL(overlap_partial_kernel, dim3((unsigned)((sub * M + 63) / 64)), dim3(64), sizeof(double) * M, st,
+                     vtab, out, sub, M, LV);
   return hipGetLastError();
 }
 
