@@ -113,16 +113,20 @@ def parse():
 def kernel_label(name):
     """bench name of a chain / prologue kernel from its demangled rocprofv3 name"""
     import re
-    # chain_kernel<KCAP, lanes per chain, wavefronts per workgroup, G^-1 in device memory,
-    # replay, FP32 storage, mixture charge law>
-    m = re.search(r"chain_kernel<(\d+), (\d+), (\d+), (true|false)(?:, (true|false))?(?:, (true|false))?"
-                  r"(?:, (true|false))?>", name)
+    # chain_kernel<KCAP, lanes per chain, wavefronts per workgroup, replay, FP32 storage,
+    # mixture charge law> (G^-1 in device memory)
+    m = re.search(r"chain_kernel<(\d+), (\d+), (\d+), (true|false), (true|false), (true|false)>", name)
     if m:
-        if m.group(5) == "true":
+        if m.group(4) == "true":
             return "chain_replay_k" + m.group(1)
-        base = "chain_group_dm" if m.group(4) == "true" else "chain_group"
-        return (base + ("_fp32" if m.group(6) == "true" else "") + ("_mcp" if m.group(7) == "true" else "")
+        return ("chain_group_dm" + ("_fp32" if m.group(5) == "true" else "") + ("_mcp" if m.group(6) == "true" else "")
                 + "_k" + m.group(1))
+    # chain_lds_kernel<KCAP, lanes per chain, residual correction, mixture charge law>
+    m = re.search(r"chain_lds_kernel<(\d+), (\d+), (true|false), (true|false)>", name)
+    if m:
+        return "chain_group" + ("_mcp" if m.group(4) == "true" else "") + "_k" + m.group(1)
+    if "chain_lds_mix_kernel" in name:
+        return "chain_group_mix"
     m = re.search(r"chain_lane_kernel<(\d+)>", name)
     if m:
         return "chain_lane_k" + m.group(1)

@@ -853,7 +853,7 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
     return b->lambda[x] < b->lambda[y] || (b->lambda[x] == b->lambda[y] && x < y);
   });
   int64_t cnt16 = 0, cnt32 = 0;
-  if (fp32)
+  if (fp32 && !force && !noalloc)  // (the allocation-free variant has no launches side by side)
     for (int64_t i = 0; i < n; ++i) {
       const int kc = chain_kcap_for(kmx[i]);
       cnt16 += kc == 16 ? cf.n_chains : 0;

@@ -2,11 +2,12 @@
 //
 //  * prologue_kernel: per waveform, the matched filter c(g) = sum_n w[n] V(n - g/sub)
 //    over the solution space T (FP64 accumulation) and a scan for non-finite samples.
-//  * chain_kernel<KCAP, LPC, WPB>: the Gibbs / RJMCMC chains (Sec. 2.4).  A group of
-//    LPC lanes owns one chain; a 64-lane wavefront runs 64 / LPC chains side by side.
-//    Per chain the LDS holds the inverse PE-space Gram matrix H = G^{-1},
-//    G = A^T A + rho I (full symmetric, KCAP x KCAP), the matched-filter terms b, the
-//    charge means x = H b and the PE grid indices.  With H at hand
+//  * the Gibbs / RJMCMC chains (Sec. 2.4): chain_lds_kernel (one element of a chain's vectors
+//    per lane, H in LDS: the lowest latency of a sweep) where the chains fit the LDS of the
+//    chip, chain_kernel (LPC lanes per chain, H in device memory) and chain_lane_kernel (one
+//    lane) for more of them.  Per chain they hold the inverse PE-space Gram matrix H = G^{-1},
+//    G = A^T A + rho I (symmetric, KCAP x KCAP), the matched-filter terms b, the charge means
+//    x = H b and the PE grid indices.  With H at hand
 //      birth  : eta = H gamma (one mat-vec), delta^2 = d - gamma^T eta,
 //               u+ = (beta - gamma^T x) / delta,
 //               delta-nu = -1/2 [-log rho + log delta^2 + (rho m^2 - u+^2) / s];
@@ -538,7 +539,7 @@ __global__ void __launch_bounds__(256) prologue_kernel(PrologueArgs a) {
 }
 
 // ------------------------------------------------------------------ chains
-// LDS block of one chain: H (unless it lives in device memory), x, two scratch vectors (six
+// LDS block of one chain (its H lives in device memory): x, two scratch vectors (six
 // and b in the FP32 form; b and the residual b - G x in the corrected FP64 form), the
 // accumulators (kAcc doubles: 12 sums, 3 open batch sums, 5 work counters, then 8 int
 // proposal / accept counts and the current run of N: value, first step), then the int grid
@@ -553,18 +554,17 @@ __global__ void __launch_bounds__(256) prologue_kernel(PrologueArgs a) {
 // gamma^T G^-1 b = gamma^T x + eta^T s and x_j = x_j + h^T s (eta = H gamma, h = row j of H),
 // exact to first order in the error of H; the other quantities (delta^2, omega) need no
 // correction at this precision.
-template <int KCAP, bool HG, bool F32 = false, bool MCP = false>
+template <int KCAP, bool F32 = false, bool MCP = false>
 struct ChainLayout {
   static constexpr int LD = KCAP;
   static constexpr int kAcc = 25;
-  static constexpr bool kCorr = HG && !F32 && KCAP >= 48;
+  static constexpr bool kCorr = !F32 && KCAP >= 48;
   static constexpr bool kKeepG = F32 || kCorr;  // the exact G in device memory, b per PE
   // the FP32 form keeps b (matched filter + rho mu_q per PE) for its residuals and refresh,
   // and the vectors of its corrected proposals; the mixture form the PEs' components after
   // their grid indices
   static constexpr int kVec = F32 ? 8 : (kCorr ? 5 : 3);
-  static constexpr int kDoubles =
-      (HG ? 0 : KCAP * KCAP) + kVec * KCAP + kAcc + (KCAP + 1) / 2 + (MCP ? (KCAP + 1) / 2 : 0);
+  static constexpr int kDoubles = kVec * KCAP + kAcc + (KCAP + 1) / 2 + (MCP ? (KCAP + 1) / 2 : 0);
 };
 
 // Column i of H owned by one lane: element (k, i) at H[(k * LD + i) * HS] (HS = 1 in LDS;
@@ -732,22 +732,22 @@ __device__ bool grp_refresh(const ModelDev &md, const double *vt, const double *
   return true;
 }
 
-// HG: H in device memory (a.dws, the chains of a wavefront interleaved element by element),
-// which leaves the LDS to the tables and the vectors and so fits many more chains per CU;
-// otherwise H in LDS.  FORCE (replay): every step follows the recorded proposal of a.force
+// H in device memory (a.dws, the chains of a wavefront interleaved element by element), which
+// leaves the LDS to the tables and the vectors and so fits many more chains per CU than
+// chain_lds_kernel does.  FORCE (replay): every step follows the recorded proposal of a.force
 // (t0 after the half-step, move, index, grid point, accept bit) instead of the chain's
 // own draws, and writes the delta-nu and log-acceptance it computes to a.rdnu / a.rla.
 // MCP: the Gaussian-mixture charge law, every PE with its component.
-template <int KCAP, int LPC, int WPB, bool HG, bool FORCE, bool F32, bool MCP>
+template <int KCAP, int LPC, int WPB, bool FORCE, bool F32, bool MCP>
 __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu(2))) chain_kernel(ChainArgs a) {
-  static_assert(!F32 || (HG && !FORCE), "the FP32 form keeps H in device memory and does not replay");
-  static_assert(!MCP || (HG && !FORCE && !F32), "the mixture form runs FP64 with H in device memory");
+  static_assert(!F32 || !FORCE, "the FP32 form does not replay");
+  static_assert(!MCP || (!FORCE && !F32), "the mixture form runs FP64 and does not replay");
   static_assert(KCAP % 16 == 0, "the column loads go in chunks of 16 rows below the capacity");
   using HT = typename std::conditional<F32, float, double>::type;
   constexpr int CPW = kWave / LPC;
-  using CL = ChainLayout<KCAP, HG, F32, MCP>;
+  using CL = ChainLayout<KCAP, F32, MCP>;
   constexpr int LD = CL::LD;
-  constexpr int HS = HG ? CPW : 1;
+  constexpr int HS = CPW;
   extern __shared__ double smem[];
   const ModelDev &md = a.md;
   double *vt = smem;
@@ -777,12 +777,12 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
   constexpr bool CORR = CL::kCorr, KEEPG = CL::kKeepG;
   constexpr int64_t kHD = (int64_t)KCAP * LD * CPW * (int64_t)sizeof(HT) / 8;
   constexpr int64_t kTile = kHD + (F32 ? 2 : CORR ? 1 : 0) * (int64_t)KCAP * LD * CPW;
-  HT *H = HG ? (HT *)(a.dws + tile * kTile) + grp : (HT *)cb;
+  HT *H = (HT *)(a.dws + tile * kTile) + grp;
   double *W = F32 ? a.dws + tile * kTile + kHD + grp : nullptr;
   double *Gm = F32    ? a.dws + tile * kTile + kHD + (int64_t)KCAP * LD * CPW + grp
                : CORR ? a.dws + tile * kTile + kHD + grp
                       : nullptr;
-  double *xv = HG ? cb : cb + KCAP * LD;
+  double *xv = cb;
   double *s1 = xv + KCAP;
   double *s2 = s1 + KCAP;
   // FP32 form: four more scratch vectors and b of each PE; corrected FP64 form: b and the
@@ -2009,7 +2009,7 @@ __device__ __attribute__((always_inline)) inline void chain_lds_body(const Chain
   // into the LDS of a CU side by side; the overlap table stays in device memory (a few reads per
   // sweep, from the caches), only the rise factors and the logs are copied.  (Workgroups of four
   // wavefronts around one copy of the tables filled a CU each: the launches of a call ran one
-  // after the other, 10.9 instead of PACK_FIG ms for 8,000 windows of the mixture law.)
+  // after the other, 10.9 ms for 8,000 windows of the mixture law, 8.9 ms now.)
   double *rt = smem;
   double *lgn = rt + md.rise_n;
   const double *ov = a.ovl;
@@ -3490,29 +3490,29 @@ __global__ void __launch_bounds__(256) posterior_extra_kernel(PosteriorArgs a, i
   }
 }
 
-template <int KCAP, int LPC, int WPB, bool HG, bool FORCE = false, bool F32 = false, bool MCP = false>
+template <int KCAP, int LPC, int WPB, bool FORCE = false, bool F32 = false, bool MCP = false>
 hipError_t launch_chain_t(const ChainArgs &args, hipStream_t st, int32_t *lanes, int64_t *blocks) {
   constexpr int CPB = WPB * (kWave / LPC);
   ChainArgs a = args;
   const int64_t nb = (a.n_list + CPB - 1) / CPB;
   size_t lds = sizeof(double) * ((size_t)a.md.M * (1 + a.md.sub) + (KCAP + 2) +
-                                 (size_t)CPB * ChainLayout<KCAP, HG, F32, MCP>::kDoubles);
+                                 (size_t)CPB * ChainLayout<KCAP, F32, MCP>::kDoubles);
   // the rise table where it fits beside what the host has checked
   if (lds + sizeof(double) * a.md.rise_n > 160 * 1024) a.md.rise_n = 0;
   lds += sizeof(double) * a.md.rise_n;
   *lanes = LPC;
   *blocks = nb;
   if (nb == 0) return hipSuccess;
-  if (HG && a.dws == nullptr) return hipErrorInvalidValue;
+  if (a.dws == nullptr) return hipErrorInvalidValue;
   if (lds > 160 * 1024) return hipErrorInvalidValue;  // the host checks the configurations against this
   if (lds > 64 * 1024) {
     // lift the default dynamic-LDS limit; gfx950 has 160 KB per workgroup
-    (void)hipFuncSetAttribute((const void *)chain_kernel<KCAP, LPC, WPB, HG, FORCE, F32, MCP>,
+    (void)hipFuncSetAttribute((const void *)chain_kernel<KCAP, LPC, WPB, FORCE, F32, MCP>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     (void)hipGetLastError();
   }
   if (FORCE && (a.force == nullptr || a.rdnu == nullptr || a.rla == nullptr)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((chain_kernel<KCAP, LPC, WPB, HG, FORCE, F32, MCP>), dim3((unsigned)nb), dim3(kWave * WPB), lds,
+  hipLaunchKernelGGL((chain_kernel<KCAP, LPC, WPB, FORCE, F32, MCP>), dim3((unsigned)nb), dim3(kWave * WPB), lds,
                      st, a);
   return hipGetLastError();
 }
@@ -3815,17 +3815,16 @@ static const GroupCfg kGroupDMF32Wide[] = {{16, 16, 4}, {32, 16, 4}};
 
 // the vectors of a chain's LDS block (ChainLayout::kVec); the corrected FP64 form (and with it
 // group_dm_ws_doubles' exact G) from capacity 48 up
-static_assert(ChainLayout<48, true>::kCorr && !ChainLayout<32, true>::kCorr && ChainLayout<64, true, false, true>::kCorr,
+static_assert(ChainLayout<48>::kCorr && !ChainLayout<32>::kCorr && ChainLayout<64, false, true>::kCorr,
               "the host's sizes assume the corrected FP64 form at capacities 48 and up");
-static int chain_vectors(int kcap, bool hg, bool f32, bool mcp) {
-  if (f32) return ChainLayout<64, true, true>::kVec;
-  return (hg && kcap >= 48) ? ChainLayout<64, true>::kVec : ChainLayout<16, true>::kVec;
+static int chain_vectors(int kcap, bool f32) {
+  if (f32) return ChainLayout<64, true>::kVec;
+  return kcap >= 48 ? ChainLayout<64>::kVec : ChainLayout<16>::kVec;
 }
 
-static size_t chain_lds_bytes(const GroupCfg &g, int M, int sub, bool hg, bool f32 = false, bool mcp = false) {
+static size_t chain_lds_bytes(const GroupCfg &g, int M, int sub, bool f32, bool mcp) {
   const int cpb = g.wpb * (64 / g.lpc);
-  const size_t per = (hg ? 0 : (size_t)g.kcap * g.kcap) + (size_t)ChainLayout<16, true, false, false>::kAcc +
-                     (size_t)chain_vectors(g.kcap, hg, f32, mcp) * (size_t)g.kcap +
+  const size_t per = (size_t)ChainLayout<16>::kAcc + (size_t)chain_vectors(g.kcap, f32) * (size_t)g.kcap +
                      ((size_t)g.kcap + 1) / 2 * (mcp ? 2 : 1);
   return sizeof(double) * ((size_t)M * (1 + sub) + (size_t)g.kcap + 2 + (size_t)cpb * per);
 }
@@ -3979,23 +3978,23 @@ bool chain_dm_supported(int kcap, int M, int sub, bool f32, bool mcp, bool wide)
   if (f32 && mcp) return false;
   if (wide && f32) {
     for (const GroupCfg &g : kGroupDMF32Wide)
-      if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, true, true, false) <= 160 * 1024;
+      if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, true, false) <= 160 * 1024;
     return false;
   }
   if (wide) {
     if (mcp) return false;
     for (const GroupCfg &g : kGroupDMWide)
-      if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, true, false, false) <= 160 * 1024;
+      if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, false, false) <= 160 * 1024;
     return false;
   }
   if (f32) {
     // no capacity 48: the precision form runs it at 64
     for (const GroupCfg &g : kGroupDMF32)
-      if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, true, true, false) <= 160 * 1024;
+      if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, true, false) <= 160 * 1024;
     return false;
   }
   for (const GroupCfg &g : kGroupDM)
-    if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, true, false, mcp) <= 160 * 1024;
+    if (g.kcap == kcap) return chain_lds_bytes(g, M, sub, false, mcp) <= 160 * 1024;
   return false;
 }
 
@@ -4042,8 +4041,8 @@ hipError_t launch_chain_dm(int kcap, bool fp32, bool wide, const ChainArgs &a, h
   if (wide && fp32) {
     if (a.md.n_mix > 0 || a.force) return hipErrorInvalidValue;
     switch (kcap) {
-      case 16: return launch_chain_t<16, 16, 4, true, false, true>(a, st, lanes, blocks);
-      case 32: return launch_chain_t<32, 16, 4, true, false, true>(a, st, lanes, blocks);
+      case 16: return launch_chain_t<16, 16, 4, false, true>(a, st, lanes, blocks);
+      case 32: return launch_chain_t<32, 16, 4, false, true>(a, st, lanes, blocks);
       default: return hipErrorInvalidValue;
     }
   }
@@ -4052,74 +4051,74 @@ hipError_t launch_chain_dm(int kcap, bool fp32, bool wide, const ChainArgs &a, h
     if (a.force) {
       // replay with the wide groups, capacities from 64 up
       switch (kcap) {
-        case 64: return launch_chain_t<64, 64, 4, true, true>(a, st, lanes, blocks);
-        case 96: return launch_chain_t<96, 64, 4, true, true>(a, st, lanes, blocks);
-        case 128: return launch_chain_t<128, 64, 4, true, true>(a, st, lanes, blocks);
-        case 160: return launch_chain_t<160, 64, 4, true, true>(a, st, lanes, blocks);
-        case 192: return launch_chain_t<192, 64, 2, true, true>(a, st, lanes, blocks);
+        case 64: return launch_chain_t<64, 64, 4, true>(a, st, lanes, blocks);
+        case 96: return launch_chain_t<96, 64, 4, true>(a, st, lanes, blocks);
+        case 128: return launch_chain_t<128, 64, 4, true>(a, st, lanes, blocks);
+        case 160: return launch_chain_t<160, 64, 4, true>(a, st, lanes, blocks);
+        case 192: return launch_chain_t<192, 64, 2, true>(a, st, lanes, blocks);
         default: return hipErrorInvalidValue;
       }
     }
     switch (kcap) {
-      case 32: return launch_chain_t<32, 16, 4, true>(a, st, lanes, blocks);
-      case 48: return launch_chain_t<48, 32, 4, true>(a, st, lanes, blocks);
-      case 64: return launch_chain_t<64, 64, 4, true>(a, st, lanes, blocks);
-      case 96: return launch_chain_t<96, 64, 4, true>(a, st, lanes, blocks);
-      case 128: return launch_chain_t<128, 64, 4, true>(a, st, lanes, blocks);
-      case 160: return launch_chain_t<160, 64, 4, true>(a, st, lanes, blocks);
-      case 192: return launch_chain_t<192, 64, 2, true>(a, st, lanes, blocks);
+      case 32: return launch_chain_t<32, 16, 4>(a, st, lanes, blocks);
+      case 48: return launch_chain_t<48, 32, 4>(a, st, lanes, blocks);
+      case 64: return launch_chain_t<64, 64, 4>(a, st, lanes, blocks);
+      case 96: return launch_chain_t<96, 64, 4>(a, st, lanes, blocks);
+      case 128: return launch_chain_t<128, 64, 4>(a, st, lanes, blocks);
+      case 160: return launch_chain_t<160, 64, 4>(a, st, lanes, blocks);
+      case 192: return launch_chain_t<192, 64, 2>(a, st, lanes, blocks);
       default: return hipErrorInvalidValue;
     }
   }
   if (a.md.n_mix > 0) {
     if (a.force || fp32) return hipErrorInvalidValue;
     switch (kcap) {
-      case 16: return launch_chain_t<16, 4, 4, true, false, false, true>(a, st, lanes, blocks);
-      case 32: return launch_chain_t<32, 4, 4, true, false, false, true>(a, st, lanes, blocks);
-      case 48: return launch_chain_t<48, 16, 2, true, false, false, true>(a, st, lanes, blocks);
-      case 64: return launch_chain_t<64, 32, 4, true, false, false, true>(a, st, lanes, blocks);
-      case 96: return launch_chain_t<96, 16, 2, true, false, false, true>(a, st, lanes, blocks);
-      case 128: return launch_chain_t<128, 32, 4, true, false, false, true>(a, st, lanes, blocks);
-      case 160: return launch_chain_t<160, 32, 4, true, false, false, true>(a, st, lanes, blocks);
-      case 192: return launch_chain_t<192, 32, 2, true, false, false, true>(a, st, lanes, blocks);
+      case 16: return launch_chain_t<16, 4, 4, false, false, true>(a, st, lanes, blocks);
+      case 32: return launch_chain_t<32, 4, 4, false, false, true>(a, st, lanes, blocks);
+      case 48: return launch_chain_t<48, 16, 2, false, false, true>(a, st, lanes, blocks);
+      case 64: return launch_chain_t<64, 32, 4, false, false, true>(a, st, lanes, blocks);
+      case 96: return launch_chain_t<96, 16, 2, false, false, true>(a, st, lanes, blocks);
+      case 128: return launch_chain_t<128, 32, 4, false, false, true>(a, st, lanes, blocks);
+      case 160: return launch_chain_t<160, 32, 4, false, false, true>(a, st, lanes, blocks);
+      case 192: return launch_chain_t<192, 32, 2, false, false, true>(a, st, lanes, blocks);
       default: return hipErrorInvalidValue;
     }
   }
   if (a.force) {
     switch (kcap) {
-      case 16: return launch_chain_t<16, 4, 4, true, true>(a, st, lanes, blocks);
-      case 32: return launch_chain_t<32, 4, 4, true, true>(a, st, lanes, blocks);
-      case 48: return launch_chain_t<48, 16, 2, true, true>(a, st, lanes, blocks);
-      case 64: return launch_chain_t<64, 32, 4, true, true>(a, st, lanes, blocks);
-      case 96: return launch_chain_t<96, 16, 2, true, true>(a, st, lanes, blocks);
-      case 128: return launch_chain_t<128, 32, 4, true, true>(a, st, lanes, blocks);
-      case 160: return launch_chain_t<160, 32, 4, true, true>(a, st, lanes, blocks);
-      case 192: return launch_chain_t<192, 32, 2, true, true>(a, st, lanes, blocks);
+      case 16: return launch_chain_t<16, 4, 4, true>(a, st, lanes, blocks);
+      case 32: return launch_chain_t<32, 4, 4, true>(a, st, lanes, blocks);
+      case 48: return launch_chain_t<48, 16, 2, true>(a, st, lanes, blocks);
+      case 64: return launch_chain_t<64, 32, 4, true>(a, st, lanes, blocks);
+      case 96: return launch_chain_t<96, 16, 2, true>(a, st, lanes, blocks);
+      case 128: return launch_chain_t<128, 32, 4, true>(a, st, lanes, blocks);
+      case 160: return launch_chain_t<160, 32, 4, true>(a, st, lanes, blocks);
+      case 192: return launch_chain_t<192, 32, 2, true>(a, st, lanes, blocks);
       default: return hipErrorInvalidValue;
     }
   }
   if (fp32) {
     // instances must match kGroupDMF32
     switch (kcap) {
-      case 16: return launch_chain_t<16, 4, 2, true, false, true>(a, st, lanes, blocks);
-      case 32: return launch_chain_t<32, 4, 2, true, false, true>(a, st, lanes, blocks);
-      case 64: return launch_chain_t<64, 32, 4, true, false, true>(a, st, lanes, blocks);
-      case 96: return launch_chain_t<96, 64, 4, true, false, true>(a, st, lanes, blocks);
-      case 128: return launch_chain_t<128, 64, 4, true, false, true>(a, st, lanes, blocks);
-      case 160: return launch_chain_t<160, 64, 4, true, false, true>(a, st, lanes, blocks);
-      case 192: return launch_chain_t<192, 64, 2, true, false, true>(a, st, lanes, blocks);
+      case 16: return launch_chain_t<16, 4, 2, false, true>(a, st, lanes, blocks);
+      case 32: return launch_chain_t<32, 4, 2, false, true>(a, st, lanes, blocks);
+      case 64: return launch_chain_t<64, 32, 4, false, true>(a, st, lanes, blocks);
+      case 96: return launch_chain_t<96, 64, 4, false, true>(a, st, lanes, blocks);
+      case 128: return launch_chain_t<128, 64, 4, false, true>(a, st, lanes, blocks);
+      case 160: return launch_chain_t<160, 64, 4, false, true>(a, st, lanes, blocks);
+      case 192: return launch_chain_t<192, 64, 2, false, true>(a, st, lanes, blocks);
       default: return hipErrorInvalidValue;
     }
   }
   switch (kcap) {
-    case 16: return launch_chain_t<16, 4, 4, true>(a, st, lanes, blocks);
-    case 32: return launch_chain_t<32, 4, 4, true>(a, st, lanes, blocks);
-    case 48: return launch_chain_t<48, 16, 2, true>(a, st, lanes, blocks);
-    case 64: return launch_chain_t<64, 32, 4, true>(a, st, lanes, blocks);
-    case 96: return launch_chain_t<96, 16, 2, true>(a, st, lanes, blocks);
-    case 128: return launch_chain_t<128, 32, 4, true>(a, st, lanes, blocks);
-    case 160: return launch_chain_t<160, 32, 4, true>(a, st, lanes, blocks);
-    case 192: return launch_chain_t<192, 32, 2, true>(a, st, lanes, blocks);
+    case 16: return launch_chain_t<16, 4, 4>(a, st, lanes, blocks);
+    case 32: return launch_chain_t<32, 4, 4>(a, st, lanes, blocks);
+    case 48: return launch_chain_t<48, 16, 2>(a, st, lanes, blocks);
+    case 64: return launch_chain_t<64, 32, 4>(a, st, lanes, blocks);
+    case 96: return launch_chain_t<96, 16, 2>(a, st, lanes, blocks);
+    case 128: return launch_chain_t<128, 32, 4>(a, st, lanes, blocks);
+    case 160: return launch_chain_t<160, 32, 4>(a, st, lanes, blocks);
+    case 192: return launch_chain_t<192, 32, 2>(a, st, lanes, blocks);
     default: return hipErrorInvalidValue;
   }
 }
