@@ -249,15 +249,15 @@ fsmp_status fail(fsmp_ctx *c, fsmp_status s, const char *fmt, ...) {
 
 bool finite(double v) { return std::isfinite(v); }
 
-// whether a kernel design exists for a PE capacity under this model (LDS footprint),
-// precision and charge law: the FP32 form and the mixture law run only in the lane groups
-// with G^-1 in device memory (the FP32 form without capacity 48, which it runs at 64); one
-// lane per chain exists at capacities 16 and 32 (FP64); the wide device-memory groups from
-// capacity 32 up (FP64, single charge law)
-// The LDS kernels in the form of the device-memory ones (corrected from capacity 48 up, to
-// capacity 160): not a design a caller sets, but where routed_design sends a bucket.
+// The LDS kernels in the form of the device-memory ones (corrected from capacity 48 up): not a
+// design a caller sets, but where routed_design sends a bucket.
 constexpr int kDesignLds = 4;
 
+// whether a kernel design exists for a PE capacity under this model (LDS footprint),
+// precision and charge law: the FP32 form runs only in the lane groups with G^-1 in device
+// memory (without capacity 48, which it runs at 64), the mixture law in those and in
+// kDesignLds; one lane per chain exists at capacities 16 and 32 (FP64); the wide
+// device-memory groups from capacity 32 up (FP64, single charge law)
 bool design_available(const fsmp_ctx *c, int kcap, int design) {
   const bool fp32 = c->cfg.precision == FSMP_FP32_REFRESH;
   const bool mcp = c->cfg.n_mix > 0;
