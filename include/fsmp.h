@@ -442,7 +442,8 @@ fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
  * and 32 in the FP32-refresh form, 16 lanes per chain), for batches whose longest chains
  * set the launch's duration.  Capacities are 16, 32, 48, 64, 96, 128, 160, 192; a waveform
  * runs in the smallest one >= its kmax.  capacity 0 = every capacity that has the design.
- * A capacity whose design is not set (by this call, the autotuner or FSMP_CHAIN_DESIGN) runs
+ * FSMP_DESIGN_AUTO, which a context starts with, leaves the choice to the library.  A capacity
+ * so (not set by this call, the autotuner or FSMP_CHAIN_DESIGN) runs
  * the LDS kernels, which exist in the library for every capacity and the mixture law, in the
  * corrected form from 48 up, for as many chains as they are the faster ones for (14,000 at
  * capacity 16 to 3,800 at 160), and the narrow device-memory groups beyond; the FP32 form its
@@ -454,8 +455,17 @@ fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
  * FSMP_DESIGN_GROUP_DEVMEM and its wide groups (capacity 48 at 64); the mixture charge law
  * FSMP_DESIGN_GROUP_DEVMEM only; replays run FSMP_DESIGN_GROUP_DEVMEM, or
  * FSMP_DESIGN_GROUP_DEVMEM_WIDE where the context has it at capacity 64 and up. */
-enum { FSMP_DESIGN_GROUP = 0, FSMP_DESIGN_LANE = 1, FSMP_DESIGN_GROUP_DEVMEM = 2, FSMP_DESIGN_GROUP_DEVMEM_WIDE = 3 };
+enum {
+  FSMP_DESIGN_GROUP = 0,
+  FSMP_DESIGN_LANE = 1,
+  FSMP_DESIGN_GROUP_DEVMEM = 2,
+  FSMP_DESIGN_GROUP_DEVMEM_WIDE = 3,
+  FSMP_DESIGN_AUTO = 5
+};
 fsmp_status fsmp_set_design(fsmp_ctx *ctx, int32_t capacity, int32_t design);
+/* The design set for a capacity, FSMP_DESIGN_AUTO where none is (FSMP_DESIGN_GROUP_DEVMEM where
+ * the library has no other kernels to choose from: the FP32-refresh form from capacity 48 up);
+ * fsmp_set_design takes it back.  Negative for a capacity that does not exist. */
 int32_t fsmp_get_design(const fsmp_ctx *ctx, int32_t capacity);
 
 /* Autotuner: runs the whole batch for trial_steps sweeps once per design, each capacity

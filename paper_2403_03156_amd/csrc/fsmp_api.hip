@@ -178,6 +178,8 @@ struct PinBuf {
 
 }  // namespace
 
+constexpr int kAuto = FSMP_DESIGN_AUTO;
+
 struct fsmp_ctx {
   int device = 0;
   fsmp_ser ser{};
@@ -206,10 +208,9 @@ struct fsmp_ctx {
   DevBuf<double> ptab;      // light-curve partial-sum factors (ModelDev::ptab)
   // per PE capacity (kCaps), FSMP_DESIGN_*: 0 = lane group per chain, H in LDS
   // (capacities up to 64); 1 = one lane per chain, state in device memory; 2 = lane group
-  // per chain, H in device memory.  While a capacity's design is not set (design_set),
-  // routed_design picks its kernels by the number of chains.
-  int design[kNumCaps] = {1, 2, 2, 2, 2, 2, 2, 2};
-  bool design_set[kNumCaps] = {};  // set by fsmp_set_design, the autotuner or the environment
+  // per chain, H in device memory; FSMP_DESIGN_AUTO = none set (by fsmp_set_design, the
+  // autotuner or the environment): routed_design picks the kernels by the number of chains.
+  int design[kNumCaps] = {kAuto, kAuto, kAuto, kAuto, kAuto, kAuto, kAuto, kAuto};
   PinBuf stage;
   hipEvent_t stage_done = nullptr;
   bool stage_pending = false;
@@ -273,7 +274,7 @@ bool design_available(const fsmp_ctx *c, int kcap, int design) {
   }
 }
 
-// the design a bucket runs in: the context's choice where it exists, else the lane groups
+// the design a bucket runs in: the context's choice where it is set and exists, else the lane groups
 // with G^-1 in device memory
 int effective_design(const fsmp_ctx *c, int kcap, int design) {
   if (design_available(c, kcap, design)) return design;
@@ -304,20 +305,18 @@ static const int64_t kF32WideChains[kNumCaps] = {8000, kAnyChains};
 
 // The kernels a bucket of `cnt` chains runs: the design the caller (or the autotuner) has set;
 // where none is set, and for the wide device-memory groups, by the number of chains.  Past the
-// LDS kernels' range an unset capacity 16 runs the narrow groups (64,000 chains x 200 sweeps:
-// 4.2 ms against 6.9 ms with a lane per chain).
+// LDS kernels' range a capacity that is not set runs the narrow groups (at capacity 16, 64,000
+// chains x 200 sweeps: 4.2 ms against 6.9 ms with a lane per chain).
 int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
   const int dz = effective_design(c, kCaps[q], c->design[q]);
   const bool wide = dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE;
-  if (c->design_set[q] && !wide) return dz;
+  if (c->design[q] != kAuto && !wide) return dz;
   if (c->cfg.precision == FSMP_FP32_REFRESH)
     return !wide && cnt <= kF32WideChains[q] && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM_WIDE)
                ? (int)FSMP_DESIGN_GROUP_DEVMEM_WIDE
                : dz;
   if (cnt <= (wide ? kLdsChainsWide : kLdsChains)[q] && design_available(c, kCaps[q], kDesignLds)) return kDesignLds;
-  return dz == FSMP_DESIGN_LANE && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM)
-             ? (int)FSMP_DESIGN_GROUP_DEVMEM
-             : dz;
+  return dz;
 }
 
 // Whether the mixed-precision form's capacity-16 chains run in the launch of capacity 32 (no design
@@ -325,7 +324,7 @@ int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
 // launch less to find a hardware queue for.  4,000 windows of 5 capacities on 4 queues: 12.4 ms
 // with a launch of its own, 10.2 together.
 bool f32_joined(const fsmp_ctx *c, int64_t cnt16, int64_t cnt32) {
-  return c->cfg.precision == FSMP_FP32_REFRESH && !c->design_set[0] && !c->design_set[1] && cnt16 > 0 && cnt32 > 0 &&
+  return c->cfg.precision == FSMP_FP32_REFRESH && c->design[0] == kAuto && c->design[1] == kAuto && cnt16 > 0 && cnt32 > 0 &&
          cnt16 + cnt32 <= kF32WideChains[0] && design_available(c, 32, FSMP_DESIGN_GROUP_DEVMEM_WIDE) &&
          design_available(c, 16, FSMP_DESIGN_GROUP_DEVMEM_WIDE);
 }
@@ -537,20 +536,15 @@ fsmp_status fsmp_create(fsmp_ctx **out, const fsmp_ser *ser, const fsmp_intensit
     return fail(nullptr, FSMP_EINVAL, "%s", m.c_str());
   }
   fill_model(c);
-  for (int q = 0; q < kNumCaps; ++q)
-    if (!design_available(c, kCaps[q], c->design[q])) c->design[q] = FSMP_DESIGN_GROUP_DEVMEM;
   if (const char *d = std::getenv("FSMP_CHAIN_DESIGN")) {
     // tuning override: one letter per capacity in kCaps order, g (lane group, H in LDS),
     // l (lane), d (lane group, H in device memory), w (its wide groups); a design that does
-    // not exist for a capacity leaves its default
+    // not exist for a capacity leaves it not set
     const size_t L = std::strlen(d);
     for (int q = 0; q < kNumCaps && q < (int)L; ++q) {
       const int want = d[q] == 'g' ? FSMP_DESIGN_GROUP : d[q] == 'l' ? FSMP_DESIGN_LANE
                        : d[q] == 'd' ? FSMP_DESIGN_GROUP_DEVMEM : d[q] == 'w' ? FSMP_DESIGN_GROUP_DEVMEM_WIDE : -1;
-      if (want >= 0 && design_available(c, kCaps[q], want)) {
-        c->design[q] = want;
-        c->design_set[q] = true;
-      }
+      if (want >= 0 && design_available(c, kCaps[q], want)) c->design[q] = want;
     }
   }
   int prev = 0;
@@ -1273,18 +1267,17 @@ fsmp_status fsmp_replay(fsmp_ctx *c, const fsmp_batch *b, const fsmp_logrec *log
 fsmp_status fsmp_set_design(fsmp_ctx *c, int32_t capacity, int32_t design) {
   if (!c) return FSMP_EINVAL;
   if (design != FSMP_DESIGN_GROUP && design != FSMP_DESIGN_LANE && design != FSMP_DESIGN_GROUP_DEVMEM &&
-      design != FSMP_DESIGN_GROUP_DEVMEM_WIDE)
+      design != FSMP_DESIGN_GROUP_DEVMEM_WIDE && design != kAuto)
     return fail(c, FSMP_EINVAL, "unknown design %d", design);
   bool any = false;
   for (int q = 0; q < kNumCaps; ++q) {
     if (capacity != 0 && capacity != kCaps[q]) continue;
     any = true;
-    if (!design_available(c, kCaps[q], design)) {
+    if (design != kAuto && !design_available(c, kCaps[q], design)) {
       if (capacity != 0) return fail(c, FSMP_ENOTSUP, "design %d does not exist for capacity %d", design, kCaps[q]);
       continue;
     }
     c->design[q] = design;
-    c->design_set[q] = true;
   }
   if (!any) return fail(c, FSMP_EINVAL, "capacity %d is not one of the kernel capacities", capacity);
   return FSMP_OK;
@@ -1293,7 +1286,12 @@ fsmp_status fsmp_set_design(fsmp_ctx *c, int32_t capacity, int32_t design) {
 int32_t fsmp_get_design(const fsmp_ctx *c, int32_t capacity) {
   if (!c) return FSMP_EINVAL;
   for (int q = 0; q < kNumCaps; ++q)
-    if (kCaps[q] == capacity) return c->design[q];
+    if (kCaps[q] == capacity) {
+      // not set: the device-memory groups where they are all there is to choose from
+      const bool choice = design_available(c, capacity, kDesignLds) ||
+                          design_available(c, capacity, FSMP_DESIGN_GROUP_DEVMEM_WIDE);
+      return c->design[q] == kAuto && !choice ? (int32_t)FSMP_DESIGN_GROUP_DEVMEM : c->design[q];
+    }
   return FSMP_EINVAL;
 }
 
@@ -1359,10 +1357,7 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   // (side by side, each would also carry what the others take from it)
   c->serial = true;
   int saved_design[kNumCaps];
-  bool saved_set[kNumCaps];
   std::memcpy(saved_design, c->design, sizeof saved_design);
-  std::memcpy(saved_set, c->design_set, sizeof saved_set);
-  for (bool &v : c->design_set) v = true;  // the trials run the designs themselves
   c->cfg.n_steps = tmax;
   c->cfg.burn_in = 0;
   c->cfg.record_flags = 0;
@@ -1391,17 +1386,13 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   c->timing = saved_timing;
   c->serial = false;
   std::memcpy(c->design, saved_design, sizeof saved_design);
-  std::memcpy(c->design_set, saved_set, sizeof saved_set);
   // per capacity the fastest of the designs that ran it
   if (st == FSMP_OK)
     for (int q = 0; q < kNumCaps; ++q) {
       int best = -1;
       for (int d = 0; d < kDesigns; ++d)
         if (ms[d][q] >= 0.0 && (best < 0 || ms[d][q] < ms[best][q])) best = d;
-      if (best >= 0) {
-        c->design[q] = best;
-        c->design_set[q] = true;
-      }
+      if (best >= 0) c->design[q] = best;
       c->tuned_design[q] = best;
       c->tuned_ms[q] = best >= 0 ? ms[best][q] : -1.0;
     }
@@ -1542,7 +1533,6 @@ fsmp_status fsmp_graph_create(fsmp_ctx *c, const fsmp_batch *b, const fsmp_sampl
     return fail(c, st, "graph context: %s", fsmp_last_error(nullptr));
   }
   std::memcpy(g->own->design, c->design, sizeof c->design);
-  std::memcpy(g->own->design_set, c->design_set, sizeof c->design_set);
   hipError_t e = hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
     fsmp_graph_destroy(g);

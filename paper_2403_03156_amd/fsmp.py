@@ -26,6 +26,7 @@ EXPORTS = ("fsmp_create", "fsmp_workspace_bytes", "fsmp_sample", "fsmp_posterior
            "fsmp_graph_create", "fsmp_graph_launch", "fsmp_graph_destroy", "fsmp_replay",
            "fsmp_autotune_steps", "fsmp_sample_noalloc")
 FSMP_DESIGN_GROUP, FSMP_DESIGN_LANE, FSMP_DESIGN_GROUP_DEVMEM, FSMP_DESIGN_GROUP_DEVMEM_WIDE = 0, 1, 2, 3
+FSMP_DESIGN_AUTO = 5  # the library's choice by the number of chains
 
 
 class fsmp_ser(ctypes.Structure):
