@@ -469,14 +469,15 @@ fsmp_status fsmp_set_design(fsmp_ctx *ctx, int32_t capacity, int32_t design);
 int32_t fsmp_get_design(const fsmp_ctx *ctx, int32_t capacity);
 
 /* Autotuner: runs the whole batch for trial_steps sweeps once per design, each capacity
- * in that design where it exists (outputs discarded, HIP-event timings of each capacity's
+ * in that design where it exists (FSMP_DESIGN_GROUP up to 32 only), and once more in the
+ * library's own choice where that is none of them (outputs discarded, HIP-event timings of each capacity's
  * launch, the capacities one after the other so that each time is the launch's own), then
- * keeps the fastest design per capacity in the context.  With per-waveform
+ * keeps the fastest design per capacity in the context: FSMP_DESIGN_AUTO where the library's
+ * choice was the fastest, or is the same device-memory groups.  With per-waveform
  * sweep counts (batch->n_steps) every waveform's trial keeps its share of them, scaled to a
  * mean of trial_steps (at least 1), so that the trial weighs a launch's longest chains
  * against its total work as the full run does.
- * Allocates scratch outputs for the trial and synchronises `hip_stream`.  The FP32-refresh
- * form and the mixture law have one design, which it keeps. */
+ * Allocates scratch outputs for the trial and synchronises `hip_stream`. */
 fsmp_status fsmp_autotune(fsmp_ctx *ctx, const fsmp_batch *batch, int32_t trial_steps, void *hip_stream);
 
 /* Chain-length autotuner: runs the batch once for pilot_steps sweeps (the configured

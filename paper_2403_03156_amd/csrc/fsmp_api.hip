@@ -1362,38 +1362,74 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   c->cfg.burn_in = 0;
   c->cfg.record_flags = 0;
   c->timing = true;
-  constexpr int kDesigns = 4;
+  // chains per capacity, and the kernels that each design runs for that many
+  int64_t cnt[kNumCaps] = {0};
+  for (int64_t i = 0; i < n; ++i) {
+    int kc = chain_kcap_for(b->kmax ? b->kmax[i] : c->cfg.k_max);
+    if (c->cfg.precision == FSMP_FP32_REFRESH && kc == 48) kc = 64;
+    for (int q = 0; q < kNumCaps; ++q)
+      if (kCaps[q] == kc) cnt[q] += c->cfg.n_chains;
+  }
+  auto kernels_of = [&](int q, int d) {
+    c->design[q] = d;
+    const int r = routed_design(c, q, cnt[q]);
+    c->design[q] = saved_design[q];
+    return r == FSMP_DESIGN_GROUP && kCaps[q] < 48 ? kDesignLds : r;
+  };
+  constexpr int kTrials[] = {FSMP_DESIGN_GROUP, FSMP_DESIGN_LANE, FSMP_DESIGN_GROUP_DEVMEM,
+                             FSMP_DESIGN_GROUP_DEVMEM_WIDE, kAuto};
+  constexpr int kDesigns = sizeof kTrials / sizeof kTrials[0];
   double ms[kDesigns][kNumCaps];
-  fsmp_status st = FSMP_OK;
-  for (int d = 0; d < kDesigns && st == FSMP_OK; ++d) {
-    for (int q = 0; q < kNumCaps; ++q) {
+  bool tried[kDesigns][kNumCaps];
+  for (int q = 0; q < kNumCaps; ++q) {
+    // the library's own choice last, where it is not what a design before it has run (the
+    // mixture law's LDS chains, and those above capacity 64 past the wide design's range)
+    bool covered = false;
+    for (int d = 0; d < kDesigns; ++d) {
+      const int z = kTrials[d];
       ms[d][q] = -1.0;
       // (the LDS design at 48 and 64 has no residual correction: the wide design runs the same
       // kernels with it and is tried in its place)
-      const bool tried = design_available(c, kCaps[q], d) &&
-                         !(d == FSMP_DESIGN_GROUP && kCaps[q] >= 48 && design_available(c, kCaps[q], kDesignLds));
-      c->design[q] = tried ? d : saved_design[q];
+      tried[d][q] = cnt[q] > 0 && (z == kAuto ? !covered
+                                              : design_available(c, kCaps[q], z) &&
+                                                    !(z == FSMP_DESIGN_GROUP && kCaps[q] >= 48 &&
+                                                      design_available(c, kCaps[q], kDesignLds)));
+      covered = covered || (tried[d][q] && kernels_of(q, z) == kernels_of(q, kAuto));
     }
+  }
+  fsmp_status st = FSMP_OK;
+  for (int d = 0; d < kDesigns && st == FSMP_OK; ++d) {
+    bool any = false;
+    for (int q = 0; q < kNumCaps; ++q) {
+      any = any || tried[d][q];
+      c->design[q] = tried[d][q] ? kTrials[d] : saved_design[q];
+    }
+    if (!any) continue;
     st = fsmp_sample(c, &bt, &o, hip_stream);
     if (st != FSMP_OK) break;
     std::vector<fsmp_timing> tv(c->timings.size() + 1);
     const int32_t nt = fsmp_last_timings(c, tv.data(), (int32_t)tv.size());
     for (int32_t k = 0; k < nt; ++k)
       for (int q = 0; q < kNumCaps; ++q)
-        if (tv[k].kcap == kCaps[q] && c->design[q] == d) ms[d][q] = tv[k].ms;
+        if (tv[k].kcap == kCaps[q] && tried[d][q]) ms[d][q] = tv[k].ms;
   }
   c->cfg = saved;
   c->timing = saved_timing;
   c->serial = false;
   std::memcpy(c->design, saved_design, sizeof saved_design);
-  // per capacity the fastest of the designs that ran it
+  // per capacity the fastest of the designs that ran it; nothing is set where the library chooses
+  // the same device-memory groups by itself (a later call of fewer chains then still gets the
+  // kernels for few, and the FP32 form one launch for capacities 16 and 32)
   if (st == FSMP_OK)
     for (int q = 0; q < kNumCaps; ++q) {
       int best = -1;
       for (int d = 0; d < kDesigns; ++d)
         if (ms[d][q] >= 0.0 && (best < 0 || ms[d][q] < ms[best][q])) best = d;
-      if (best >= 0) c->design[q] = best;
-      c->tuned_design[q] = best;
+      if (best >= 0) {
+        const int r = kernels_of(q, kTrials[best]);
+        c->design[q] = r != kDesignLds && r == kernels_of(q, kAuto) ? kAuto : kTrials[best];
+      }
+      c->tuned_design[q] = best >= 0 ? c->design[q] : -1;
       c->tuned_ms[q] = best >= 0 ? ms[best][q] : -1.0;
     }
   (void)hipStreamSynchronize((hipStream_t)hip_stream);

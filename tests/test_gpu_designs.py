@@ -52,3 +52,36 @@ def test_automatic_where_there_is_no_choice():
                        t0_min=wl.t0_min, t0_max=wl.t0_max, n_steps=10, burn_in=5, seed=1,
                        precision=fsmp.FSMP_FP32_REFRESH)
     assert [smp.get_design(c) for c in synth.KCAPS] == [fsmp.FSMP_DESIGN_AUTO] * 2 + [fsmp.FSMP_DESIGN_GROUP_DEVMEM] * 6
+
+
+# the five-Gaussian charge law of MCP-PMTs
+MIX = ([0.041, 0.516, 0.187, 0.195, 0.061], [0.92, 1.98, 3.01, 4.70, 6.79], [0.22, 0.48, 0.80, 1.30, 2.04])
+
+
+@pytest.mark.parametrize("form", ["mix", "fp32"])
+def test_autotuner_tries_the_automatic_choice(form):
+    # mixture law: the LDS chains are the library's choice only, no design a caller can name.  Mixed
+    # precision: the launch that capacities 16 and 32 share exists where neither is set.  (Times
+    # differ between runs: what a capacity may end with is checked, and that the kernels agree.)
+    wl = synth.PRESETS["batched"]
+    b = synth.generate(wl, n_wave=600, seed=9, lam=np.linspace(0.2, 8.0, 600))
+    km = synth.kmax_for(b["lam"])
+    assert set(km.tolist()) == {16, 32}
+    wave = torch.from_numpy(b["wave"]).cuda()
+    kw = {"mix": MIX} if form == "mix" else {"precision": fsmp.FSMP_FP32_REFRESH, "refresh_M": 64}
+    smp = fsmp.Sampler(ser=wl.ser, phi_kind=wl.phi_kind, tau_rise=wl.tau_rise, tau_decay=wl.tau_decay,
+                       t0_min=wl.t0_min, t0_max=wl.t0_max, n_steps=400, burn_in=200, seed=2, **kw)
+    print(f"[case] autotune {form}", flush=True)
+    fresh = _launches(smp, wave, b, km)
+    designs = smp.autotune(wave, b["offsets"], b["lam"], kmax=km, trial_steps=200)
+    print(f"[autotune] {designs}", flush=True)
+    tuned = _launches(smp, wave, b, km)
+    # 600 chains are a twentieth of what the kernels for few chains are the faster ones for
+    # (3.2 against 8-13 us a sweep; 1.1 against 1.4 and 1.4 against 2.7 ms for 4,000 chains)
+    assert designs[16] == designs[32] == fsmp.FSMP_DESIGN_AUTO
+    assert tuned == fresh
+    if form == "mix":
+        assert all(not name.startswith("chain_group_dm") for name, _ in tuned.values())
+    else:
+        assert set(tuned) == {32}  # one launch for both
+    assert all(designs[c] == smp.get_design(c) for c in synth.KCAPS)
