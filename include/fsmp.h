@@ -431,7 +431,7 @@ int32_t fsmp_last_timings(const fsmp_ctx *ctx, fsmp_timing *out, int32_t cap);
 fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
 
 /* ------------------------------------------------------------------ kernel designs
- * Four implementations of the same chains (identical results up to rounding order):
+ * Implementations of the same chains (identical results up to rounding order):
  * FSMP_DESIGN_GROUP runs one chain per group of lanes with G^{-1} in LDS (PE capacities up
  * to 64); FSMP_DESIGN_LANE runs one chain per lane with G^{-1} interleaved in device
  * memory (capacities 16 and 32); FSMP_DESIGN_GROUP_DEVMEM runs one chain per (narrower)
@@ -448,19 +448,24 @@ fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
  * corrected form from 48 up, for as many chains as they are the faster ones for (14,000 at
  * capacity 16 to 3,800 at 160), and the narrow device-memory groups beyond; the FP32 form its
  * wide groups for few chains.  FSMP_DESIGN_GROUP_DEVMEM_WIDE stands for the kernels that shorten
- * a sweep: it too runs the LDS kernels while the chains are few enough (always up to capacity
- * 64, 5,500 chains at 96 to 2,000 at 160).  Small calls run the LDS chains of all capacities up
+ * a sweep: in FP64 it too runs the LDS kernels while the chains are few enough (always up to
+ * capacity 64 and at 192, 5,500 chains at 96 to 2,000 at 160).  The kernels that these two choose
+ * from at any number of chains: FSMP_DESIGN_GROUP_LDS (every capacity, FP64 and the mixture law),
+ * FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY (capacities 96 to 160 in FP64; where the FP32 form has wide
+ * groups), FSMP_DESIGN_GROUP_DEVMEM.  Small calls run the LDS chains of all capacities up
  * to 64 in one launch, unless timings are on.
  * FSMP_ENOTSUP if the requested pair does not exist.  The FP32-refresh form runs
  * FSMP_DESIGN_GROUP_DEVMEM and its wide groups (capacity 48 at 64); the mixture charge law
- * FSMP_DESIGN_GROUP_DEVMEM only; replays run FSMP_DESIGN_GROUP_DEVMEM, or
- * FSMP_DESIGN_GROUP_DEVMEM_WIDE where the context has it at capacity 64 and up. */
+ * FSMP_DESIGN_GROUP_LDS and FSMP_DESIGN_GROUP_DEVMEM; replays run FSMP_DESIGN_GROUP_DEVMEM, or the
+ * wide groups where the context has either design of them at capacity 64 and up. */
 enum {
   FSMP_DESIGN_GROUP = 0,
   FSMP_DESIGN_LANE = 1,
   FSMP_DESIGN_GROUP_DEVMEM = 2,
   FSMP_DESIGN_GROUP_DEVMEM_WIDE = 3,
-  FSMP_DESIGN_AUTO = 5
+  FSMP_DESIGN_AUTO = 5,
+  FSMP_DESIGN_GROUP_LDS = 6,
+  FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY = 7
 };
 fsmp_status fsmp_set_design(fsmp_ctx *ctx, int32_t capacity, int32_t design);
 /* The design set for a capacity, FSMP_DESIGN_AUTO where none is (FSMP_DESIGN_GROUP_DEVMEM where

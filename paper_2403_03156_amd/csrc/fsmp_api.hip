@@ -250,9 +250,9 @@ fsmp_status fail(fsmp_ctx *c, fsmp_status s, const char *fmt, ...) {
 
 bool finite(double v) { return std::isfinite(v); }
 
-// The LDS kernels in the form of the device-memory ones (corrected from capacity 48 up): not a
-// design a caller sets, but where routed_design sends a bucket.
-constexpr int kDesignLds = 4;
+// The LDS kernels in the form of the device-memory ones (corrected from capacity 48 up), and the wide
+// device-memory groups at any number of chains (FSMP_DESIGN_GROUP_DEVMEM_WIDE itself is routed)
+constexpr int kDesignLds = FSMP_DESIGN_GROUP_LDS, kWideOnly = FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY;
 
 // whether a kernel design exists for a PE capacity under this model (LDS footprint),
 // precision and charge law: the FP32 form runs only in the lane groups with G^-1 in device
@@ -260,6 +260,11 @@ constexpr int kDesignLds = 4;
 // kDesignLds; one lane per chain exists at capacities 16 and 32 (FP64); the wide
 // device-memory groups from capacity 32 up (FP64, single charge law)
 bool design_available(const fsmp_ctx *c, int kcap, int design) {
+  // (sampling in FP64 has wide groups where they are the faster kernels at some number of chains)
+  if (design == kWideOnly) {
+    if (c->cfg.precision != FSMP_FP32_REFRESH && kcap != 96 && kcap != 128 && kcap != 160) return false;
+    design = FSMP_DESIGN_GROUP_DEVMEM_WIDE;
+  }
   const bool fp32 = c->cfg.precision == FSMP_FP32_REFRESH;
   const bool mcp = c->cfg.n_mix > 0;
   switch (design) {
@@ -290,10 +295,14 @@ int effective_design(const fsmp_ctx *c, int kcap, int design) {
 //   48: 1,000 4.0 / 12.0, 8,000 22.3 / 16.0;  64: 1,000 4.3 / 10.9, 8,000 32.1 / 25.5;
 //   96: 1,000 11.6 / 34, 4,000 31.9 / 45.9;  128: 1,000 16 / 41, 4,000 56 / 67;
 //   160: 1,000 34 / 61, 4,000 128 / 124;  192: 4,000 155 / 278.
+// At 192 on lists of 122 the LDS kernels are ahead of both others at every number of chains: LDS /
+// narrow / wide 1,000 53 / 138 / 75, 4,000 198 / 422 / 318, 32,000 1,510 / 3,368 / 2,002.
 // Against the wide groups (chosen for sweep counts that differ 8x, where their longest chains
 // take 47-79 ms of 4,000 sweeps and LDS 17-35): always up to capacity 64, where they take
 // 7-11 ns per chain and sweep against 1-4, and while the LDS share of a mean chain stays below
-// that latency above.
+// that latency above.  At 32, 48, 64 and 192 sampling has no wide groups: one chain of 16 with 8x the
+// sweeps of the others, LDS / wide 32: 16,000 4.5 / 11.5, 32,000 8.4 / 11.9;  48: 16,000 9.5 / 12.2;
+// 64: 4,000 5.0 / 8.2, 16,000 15.1 / 14.8;  192: 1,000 10 / 41, 16,000 134 / 187.
 constexpr int64_t kAnyChains = INT64_MAX;
 static const int64_t kLdsChains[kNumCaps] = {14000, 32000, 5500, 3500, 6000, 5000, 3800, kAnyChains};
 static const int64_t kLdsChainsWide[kNumCaps] = {kAnyChains, kAnyChains, kAnyChains, kAnyChains,
@@ -310,6 +319,7 @@ static const int64_t kF32WideChains[kNumCaps] = {8000, kAnyChains};
 int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
   const int dz = effective_design(c, kCaps[q], c->design[q]);
   const bool wide = dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE;
+  if (dz == kWideOnly) return FSMP_DESIGN_GROUP_DEVMEM_WIDE;
   if (c->design[q] != kAuto && !wide) return dz;
   if (c->cfg.precision == FSMP_FP32_REFRESH)
     return !wide && cnt <= kF32WideChains[q] && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM_WIDE)
@@ -538,12 +548,15 @@ fsmp_status fsmp_create(fsmp_ctx **out, const fsmp_ser *ser, const fsmp_intensit
   fill_model(c);
   if (const char *d = std::getenv("FSMP_CHAIN_DESIGN")) {
     // tuning override: one letter per capacity in kCaps order, g (lane group, H in LDS),
-    // l (lane), d (lane group, H in device memory), w (its wide groups); a design that does
+    // l (lane), d (lane group, H in device memory), w (its wide groups, at any number of
+    // chains; at the capacities without them for sampling the wide design's choice), c (the LDS
+    // kernels of the automatic choice, at any number of chains); a design that does
     // not exist for a capacity leaves it not set
     const size_t L = std::strlen(d);
     for (int q = 0; q < kNumCaps && q < (int)L; ++q) {
-      const int want = d[q] == 'g' ? FSMP_DESIGN_GROUP : d[q] == 'l' ? FSMP_DESIGN_LANE
-                       : d[q] == 'd' ? FSMP_DESIGN_GROUP_DEVMEM : d[q] == 'w' ? FSMP_DESIGN_GROUP_DEVMEM_WIDE : -1;
+      int want = d[q] == 'g' ? FSMP_DESIGN_GROUP : d[q] == 'l' ? FSMP_DESIGN_LANE
+                       : d[q] == 'd' ? FSMP_DESIGN_GROUP_DEVMEM : d[q] == 'w' ? kWideOnly : d[q] == 'c' ? kDesignLds : -1;
+      if (want == kWideOnly && !design_available(c, kCaps[q], want)) want = FSMP_DESIGN_GROUP_DEVMEM_WIDE;
       if (want >= 0 && design_available(c, kCaps[q], want)) c->design[q] = want;
     }
   }
@@ -823,12 +836,13 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   int64_t n_order = 0;
   int64_t bucket_start[kNumCaps + 1] = {0};
   const bool fp32 = cf.precision == FSMP_FP32_REFRESH;
-  auto design_of = [&](int bi) {
+  auto design_of = [&](int bi) -> int {
     // a replay runs the device-memory groups: the wide ones where the context has chosen them
     // at capacity 64 and up, else the narrow ones
     if (force) {
       const int dz = effective_design(c, caps[bi], c->design[bi]);
-      return dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE && caps[bi] >= 64 ? dz : (int)FSMP_DESIGN_GROUP_DEVMEM;
+      const bool wide = (dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE || dz == kWideOnly) && caps[bi] >= 64;
+      return wide ? FSMP_DESIGN_GROUP_DEVMEM_WIDE : FSMP_DESIGN_GROUP_DEVMEM;
     }
     return routed_design(c, bi, bucket_start[bi + 1] - bucket_start[bi]);
   };
@@ -1267,7 +1281,7 @@ fsmp_status fsmp_replay(fsmp_ctx *c, const fsmp_batch *b, const fsmp_logrec *log
 fsmp_status fsmp_set_design(fsmp_ctx *c, int32_t capacity, int32_t design) {
   if (!c) return FSMP_EINVAL;
   if (design != FSMP_DESIGN_GROUP && design != FSMP_DESIGN_LANE && design != FSMP_DESIGN_GROUP_DEVMEM &&
-      design != FSMP_DESIGN_GROUP_DEVMEM_WIDE && design != kAuto)
+      design != FSMP_DESIGN_GROUP_DEVMEM_WIDE && design != kAuto && design != kDesignLds && design != kWideOnly)
     return fail(c, FSMP_EINVAL, "unknown design %d", design);
   bool any = false;
   for (int q = 0; q < kNumCaps; ++q) {

@@ -4059,14 +4059,11 @@ hipError_t launch_chain_dm(int kcap, bool fp32, bool wide, const ChainArgs &a, h
         default: return hipErrorInvalidValue;
       }
     }
+    // sampling: the LDS chains are the faster ones at the other capacities whatever their number
     switch (kcap) {
-      case 32: return launch_chain_t<32, 16, 4>(a, st, lanes, blocks);
-      case 48: return launch_chain_t<48, 32, 4>(a, st, lanes, blocks);
-      case 64: return launch_chain_t<64, 64, 4>(a, st, lanes, blocks);
       case 96: return launch_chain_t<96, 64, 4>(a, st, lanes, blocks);
       case 128: return launch_chain_t<128, 64, 4>(a, st, lanes, blocks);
       case 160: return launch_chain_t<160, 64, 4>(a, st, lanes, blocks);
-      case 192: return launch_chain_t<192, 64, 2>(a, st, lanes, blocks);
       default: return hipErrorInvalidValue;
     }
   }

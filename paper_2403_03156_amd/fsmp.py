@@ -27,6 +27,8 @@ EXPORTS = ("fsmp_create", "fsmp_workspace_bytes", "fsmp_sample", "fsmp_posterior
            "fsmp_autotune_steps", "fsmp_sample_noalloc")
 FSMP_DESIGN_GROUP, FSMP_DESIGN_LANE, FSMP_DESIGN_GROUP_DEVMEM, FSMP_DESIGN_GROUP_DEVMEM_WIDE = 0, 1, 2, 3
 FSMP_DESIGN_AUTO = 5  # the library's choice by the number of chains
+# the kernels that AUTO and GROUP_DEVMEM_WIDE choose from, at any number of chains
+FSMP_DESIGN_GROUP_LDS, FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY = 6, 7
 
 
 class fsmp_ser(ctypes.Structure):

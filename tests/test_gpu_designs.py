@@ -3,8 +3,9 @@ library, names the kernels that its launches report."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2403_03156_amd import fsmp, synth
-from tests.fsmp_cases import gpu_sampler, to_host
+from tests.fsmp_cases import check_partings, compare_chains, gpu_sampler, oracle_params, to_host
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -85,3 +86,127 @@ def test_autotuner_tries_the_automatic_choice(form):
     else:
         assert set(tuned) == {32}  # one launch for both
     assert all(designs[c] == smp.get_design(c) for c in synth.KCAPS)
+
+
+def _mixed(wl, lam, seed=7):
+    b = synth.generate(wl, n_wave=len(lam), seed=seed, lam=np.asarray(lam, float))
+    return b, synth.kmax_for(b["lam"]), torch.from_numpy(b["wave"]).cuda()
+
+
+PINNED = {fsmp.FSMP_DESIGN_GROUP_LDS: ("chain_group_k", {96: 128, 128: 128, 160: 192}),
+          fsmp.FSMP_DESIGN_GROUP_DEVMEM: ("chain_group_dm_k", {96: 16, 128: 32, 160: 32}),
+          fsmp.FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY: ("chain_group_dm_k", {96: 64, 128: 64, 160: 64})}
+
+
+@pytest.mark.parametrize("design", list(PINNED))
+@pytest.mark.parametrize("start", [False, True])
+def test_pinned_kernels_against_the_oracle(design, start):
+    # every kernel of capacities 96 to 160, whatever the number of chains: birth by birth from no
+    # PEs, and from start lists
+    wl = synth.PRESETS["pileup"]
+    lam = [45.0, 50.0, 58.0, 62.0, 75.0, 85.0, 92.0, 100.0]
+    b, km, wave = _mixed(wl, lam)
+    assert set(km.tolist()) == {96, 128, 160}
+    n_steps, burn, seed, kz = 200, 80, 11, 160
+    print(f"[case] pinned {design} start lists {start}", flush=True)
+    kw, okw = {}, {}
+    if start:
+        z = [np.unique(np.clip(np.rint(np.asarray(t) * 4), 4 * 101, 4 * 1024 - 1).astype(int))[:k - 2].tolist()
+             for t, k in zip(b["times"], km)]
+        kw = dict(z_init=z, t0_init=np.full(len(km), 100.0))
+        okw = dict(z_init=z, t0_init=np.full(len(km), 100.0))
+
+    def sampler(flags):
+        s = gpu_sampler(wl, n_steps, burn, 1, seed, k_max=kz, record_flags=flags)
+        s.set_design(0, fsmp.FSMP_DESIGN_GROUP_DEVMEM)
+        for cap in (96, 128, 160):
+            s.set_design(cap, design)
+        return s
+
+    smp = sampler(0)
+    name, lanes = PINNED[design]
+    t = _launches(smp, wave, b, km, kz=kz, **kw)
+    assert {c: v[1] for c, v in t.items()} == lanes and all(v[0].startswith(name) for v in t.values()), t
+    g = to_host(smp.sample(wave, b["offsets"], b["lam"], kmax=km, kz=kz, **kw))
+    p = oracle_params(wl)
+    o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, n_steps, burn, seed, kz, kmax=km, **okw)
+    parted = compare_chains(g, o)
+    assert (g["n_pe"] > 10).all()
+    if start:
+        assert len(parted) == 0, parted
+    else:
+        check_partings(parted, p, b, b["lam"], km, 1, n_steps, burn, seed, kz, sampler)
+
+
+def test_wide_groups_where_they_do_not_exist():
+    wl = synth.PRESETS["plain"]
+    smp = gpu_sampler(wl, 10, 5, 1, 1)
+    for cap in (16, 32, 48, 64, 192):
+        with pytest.raises(RuntimeError):
+            smp.set_design(cap, fsmp.FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY)
+    smp.set_design(0, fsmp.FSMP_DESIGN_GROUP_DEVMEM)
+    smp.set_design(0, fsmp.FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY)
+    assert [smp.get_design(c) for c in synth.KCAPS] == [2] * 4 + [7] * 3 + [2]
+
+
+def test_replays_with_the_pinned_wide_groups():
+    # the wide design and the pinned one replay the same kernels
+    wl = synth.PRESETS["pileup"]
+    b, km, wave = _mixed(wl, [50.0, 70.0, 95.0])
+    p = oracle_params(wl)
+    o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, 60, 30, 4, 160, kmax=km, log=True)
+    out = []
+    for d in (fsmp.FSMP_DESIGN_GROUP_DEVMEM_WIDE, fsmp.FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY):
+        s = gpu_sampler(wl, 60, 30, 1, 4, k_max=160)
+        s.set_design(0, d)
+        dnu, la, _ = s.replay(wave, b["offsets"], b["lam"], np.asarray(o.log), kmax=km, kz=160)
+        out.append((dnu.cpu().numpy(), la.cpu().numpy()))
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
+def test_mixture_in_the_device_memory_groups():
+    wl = synth.PRESETS["batched"]
+    b, km, wave = _mixed(wl, np.concatenate([np.linspace(0.3, 22.0, 24), [40.0, 60.0]]))
+    assert set(km.tolist()) >= {16, 32, 48, 64, 96}
+    n_steps, burn, seed, kz = 200, 100, 5, int(km.max())
+    print("[case] mixture, device-memory groups", flush=True)
+    smp = fsmp.Sampler(ser=wl.ser, phi_kind=wl.phi_kind, tau_rise=wl.tau_rise, tau_decay=wl.tau_decay,
+                       t0_min=wl.t0_min, t0_max=wl.t0_max, sigma_eps=wl.sigma_eps, n_steps=n_steps, burn_in=burn,
+                       seed=seed, k_max=kz, mix=MIX)
+    smp.set_design(0, fsmp.FSMP_DESIGN_GROUP_DEVMEM)
+    assert all(v[0].startswith("chain_group_dm") for v in _launches(smp, wave, b, km, kz=kz).values())
+    g = to_host(smp.sample(wave, b["offsets"], b["lam"], kmax=km, kz=kz))
+    p = oracle_params(wl)
+    p.n_mix = len(MIX[0])
+    for i in range(p.n_mix):
+        p.mix_w[i], p.mix_mu[i], p.mix_sigma[i] = MIX[0][i], MIX[1][i], MIX[2][i]
+    o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, n_steps, burn, seed, kz, kmax=km)
+    parted = compare_chains(g, o)
+    assert len(parted) == 0, parted
+    np.testing.assert_array_equal(g["comp"], o.e)
+
+
+def test_mixed_precision_in_the_narrow_groups():
+    wl = synth.PRESETS["batched"]
+    b, km, wave = _mixed(wl, np.linspace(0.3, 9.0, 60))
+    assert set(km.tolist()) == {16, 32}
+    n_steps, burn, seed, kz = 300, 150, 31, 32
+    print("[case] mixed precision, narrow groups", flush=True)
+
+    def sampler(flags):
+        s = fsmp.Sampler(ser=wl.ser, phi_kind=wl.phi_kind, tau_rise=wl.tau_rise, tau_decay=wl.tau_decay,
+                         t0_min=wl.t0_min, t0_max=wl.t0_max, sigma_eps=wl.sigma_eps, mu_q=wl.mu_q,
+                         sigma_q=wl.sigma_q, n_steps=n_steps, burn_in=burn, seed=seed, record_flags=flags, k_max=kz,
+                         precision=fsmp.FSMP_FP32_REFRESH, refresh_M=64)
+        for cap in (16, 32):
+            s.set_design(cap, fsmp.FSMP_DESIGN_GROUP_DEVMEM)
+        return s
+
+    smp = sampler(0)
+    assert {v[1] for v in _launches(smp, wave, b, km, kz=kz).values()} == {4}  # lanes per chain
+    g = to_host(smp.sample(wave, b["offsets"], b["lam"], kmax=km, kz=kz))
+    p = oracle_params(wl)
+    o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, n_steps, burn, seed, kz, kmax=km)
+    parted = compare_chains(g, o, tol=1e-7)
+    check_partings(parted, p, b, b["lam"], km, 1, n_steps, burn, seed, kz, sampler)
