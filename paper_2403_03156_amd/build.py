@@ -18,6 +18,11 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed-FP32 instructions anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # Products are fused into sums only inside one source expression (or by an explicit fma), not
+    # wherever the code generator sees a pair: the kernels that hold the same chains (G^-1 in LDS
+    # and in device memory, one launch for several capacities) then round alike, as their sources
+    # say, whatever is inlined around an expression.
+    "-ffp-contract=on",
     # The sweep loops are long and use hundreds of FP64 constants (polynomials of log, exp, sin):
     # hoisted out of the loop they fill the 256 registers and spill; left in place they are
     # scalar moves beside the vector work.

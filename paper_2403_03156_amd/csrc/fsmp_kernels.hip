@@ -586,13 +586,26 @@ __device__ inline double grp_col_dot(const MT *H, const double *g, int i, int N)
       v[u] = g[k0 + u];
     }
 #pragma unroll
-    for (int u = 0; u < RC; ++u) e = (k0 + u < N) ? e + h[u] * v[u] : e;
+    for (int u = 0; u < RC; ++u) e = (k0 + u < N) ? fma(h[u], v[u], e) : e;
   }
   return e;
 }
 
-// H(k, i) += ai A_k cA [+ bi B_k cB] for k < N (loads of a chunk unconditional, stores guarded;
-// an FP32 H is read into FP64 and written back rounded)
+// One element of an edit of G^-1, rounded as written here in every kernel (so a chain's state is the
+// same bits in each): h + (ui uk) cu + (vi vk) cv, of a single vector h + (ui uk) cu with the term
+// rounded (what two vectors give with cv = 0); fused into h where a list is built.
+__device__ inline double edit_two(double h, double ui, double uk, double cu, double vi, double vk, double cv) {
+  const double t = vi * vk * cv;
+  return h + fma(ui * uk, cu, t);
+}
+__device__ inline double edit_one(double h, double ui, double uk, double cu) {
+  const double t = ui * uk * cu;
+  return h + t;
+}
+__device__ inline double edit_build(double h, double ui, double uk, double cu) { return fma(ui * uk, cu, h); }
+
+// H(k, i) += ai A_k cA + bi B_k cB for k < N (TWO; edit_two), or the step of a list's build (loads of a
+// chunk unconditional, stores guarded; an FP32 H is read into FP64 and written back rounded)
 template <int LD, int HS, bool TWO, typename MT>
 __device__ inline void grp_col_update(MT *H, int i, int N, double ai, const double *A, double cA, double bi,
                                       const double *B, double cB) {
@@ -606,7 +619,7 @@ __device__ inline void grp_col_update(MT *H, int i, int N, double ai, const doub
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const double v = TWO ? h[u] + (ai * av[u] * cA + bi * bw[u] * cB) : h[u] + ai * av[u] * cA;
+      const double v = TWO ? edit_two(h[u], ai, av[u], cA, bi, bw[u], cB) : edit_build(h[u], ai, av[u], cA);
       if (k0 + u < N) H[((k0 + u) * LD + i) * HS] = (MT)v;
     }
   }
@@ -692,7 +705,7 @@ __device__ bool grp_build(const ModelDev &md, const double *vt, const double *ov
     for (int i = lane; i < k; i += LPC) {
       const double e = grp_col_dot<LD, HS>(M, s1, i, k);
       s2[i] = e;
-      q += s1[i] * e;
+      q = fma(s1[i], e, q);
     }
     q = group_sum<LPC>(q);
     const double delta2 = d - q;
@@ -1083,7 +1096,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
           xj = xjp = xv[j];
           if constexpr (CORR) {
             double xc = 0.0;
-            for (int i = lane; i < N; i += LPC) xc += H[(j * LD + i) * HS] * rs[i];
+            for (int i = lane; i < N; i += LPC) xc = fma(H[(j * LD + i) * HS], rs[i], xc);
             xj += group_sum<LPC>(xc);
           }
           if constexpr (MCP) {
@@ -1145,11 +1158,11 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       for (int i = lane; i < N; i += LPC) {
         const double e = grp_col_dot<LD, HS>(M, s1, i, N);
         s2[i] = e;
-        q += s1[i] * e;
-        p += s1[i] * xv[i];
+        q = fma(s1[i], e, q);
+        p = fma(s1[i], xv[i], p);
         if constexpr (CORR) {
-          pc += e * rs[i];
-          if (move == 3) xc += (double)M[(j * LD + i) * HS] * rs[i];
+          pc = fma(e, rs[i], pc);
+          if (move == 3) xc = fma((double)M[(j * LD + i) * HS], rs[i], xc);
         }
       }
       q = group_sum<LPC>(q);
@@ -1866,17 +1879,12 @@ __device__ inline double lds_dot(const double *D, const double *v, int i, int N)
   return e;
 }
 
-// One element of an edit: h + (ui uk) cu [+ (vi vk) cv] in a sweep, rounded as the device-memory
-// groups round it (h is added to the sum of the two terms, of which `first`, the first row of a
-// chunk of eight, rounds the other one); fused into h where a list is built.
+// one element of an edit by one vector, or by two, or of the step of a list's build
 template <bool TWO, bool BUILD>
-__device__ inline double lds_edited(double h, double ui, double uk, double cu, double vi, double vk, double cv,
-                                    bool first) {
-#pragma clang fp contract(off)
-  if constexpr (BUILD) return fma(ui * uk, cu, h);
-  else if (TWO && first) return h + fma(vi * vk, cv, ui * uk * cu);
-  else if constexpr (TWO) return h + fma(ui * uk, cu, vi * vk * cv);
-  else return h + ui * uk * cu;
+__device__ inline double lds_edited(double h, double ui, double uk, double cu, double vi, double vk, double cv) {
+  if constexpr (BUILD) return edit_build(h, ui, uk, cu);
+  else if constexpr (TWO) return edit_two(h, ui, uk, cu, vi, vk, cv);
+  else return edit_one(h, ui, uk, cu);
 }
 
 // H += cu u u^T [+ cv v v^T], element i's share (i < N; u, v zero from N on)
@@ -1895,11 +1903,11 @@ __device__ inline void lds_edit(double *D, const double *u, const double *v, dou
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        D[(d0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv, q == 0);
+        D[(d0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv);
     }
     if (N > KCAP / 2) {
       double *e = D + KCAP / 2 * KCAP + i;
-      *e = lds_edited<TWO, BUILD>(*e, ui, u[i + KCAP / 2], cu, vi, TWO ? v[i + KCAP / 2] : 0.0, cv, false);
+      *e = lds_edited<TWO, BUILD>(*e, ui, u[i + KCAP / 2], cu, vi, TWO ? v[i + KCAP / 2] : 0.0, cv);
     }
   } else {
     for (int k0 = 0; k0 < N; k0 += 8) {
@@ -1912,7 +1920,7 @@ __device__ inline void lds_edit(double *D, const double *u, const double *v, dou
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        D[(k0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv, q == 0);
+        D[(k0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv);
     }
   }
 }
