@@ -592,11 +592,14 @@ __device__ inline double grp_col_dot(const MT *H, const double *g, int i, int N)
 }
 
 // One element of an edit of G^-1, rounded as written here in every kernel (so a chain's state is the
-// same bits in each): h + (ui uk) cu + (vi vk) cv, of a single vector h + (ui uk) cu with the term
-// rounded (what two vectors give with cv = 0); fused into h where a list is built.
-__device__ inline double edit_two(double h, double ui, double uk, double cu, double vi, double vk, double cv) {
-  const double t = vi * vk * cv;
-  return h + fma(ui * uk, cu, t);
+// same bits in each): h + [(ui uk) cu + (vi vk) cv], of a single vector h + (ui uk) cu with the term
+// rounded (what two vectors give with cv = 0); fused into h where a list is built.  Which of the two
+// products is rounded first has no meaning; `first`, the first row of a chunk of eight, rounds the
+// other one than the rest, so that chains keep the bits they have always had.
+__device__ inline double edit_two(double h, double ui, double uk, double cu, double vi, double vk, double cv,
+                                  bool first) {
+  const double tu = ui * uk * cu, tv = vi * vk * cv;
+  return h + (first ? fma(vi * vk, cv, tu) : fma(ui * uk, cu, tv));
 }
 __device__ inline double edit_one(double h, double ui, double uk, double cu) {
   const double t = ui * uk * cu;
@@ -619,7 +622,7 @@ __device__ inline void grp_col_update(MT *H, int i, int N, double ai, const doub
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const double v = TWO ? edit_two(h[u], ai, av[u], cA, bi, bw[u], cB) : edit_build(h[u], ai, av[u], cA);
+      const double v = TWO ? edit_two(h[u], ai, av[u], cA, bi, bw[u], cB, u == 0) : edit_build(h[u], ai, av[u], cA);
       if (k0 + u < N) H[((k0 + u) * LD + i) * HS] = (MT)v;
     }
   }
@@ -1881,9 +1884,10 @@ __device__ inline double lds_dot(const double *D, const double *v, int i, int N)
 
 // one element of an edit by one vector, or by two, or of the step of a list's build
 template <bool TWO, bool BUILD>
-__device__ inline double lds_edited(double h, double ui, double uk, double cu, double vi, double vk, double cv) {
+__device__ inline double lds_edited(double h, double ui, double uk, double cu, double vi, double vk, double cv,
+                                    bool first) {
   if constexpr (BUILD) return edit_build(h, ui, uk, cu);
-  else if constexpr (TWO) return edit_two(h, ui, uk, cu, vi, vk, cv);
+  else if constexpr (TWO) return edit_two(h, ui, uk, cu, vi, vk, cv, first);
   else return edit_one(h, ui, uk, cu);
 }
 
@@ -1903,11 +1907,11 @@ __device__ inline void lds_edit(double *D, const double *u, const double *v, dou
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        D[(d0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv);
+        D[(d0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv, q == 0);
     }
     if (N > KCAP / 2) {
       double *e = D + KCAP / 2 * KCAP + i;
-      *e = lds_edited<TWO, BUILD>(*e, ui, u[i + KCAP / 2], cu, vi, TWO ? v[i + KCAP / 2] : 0.0, cv);
+      *e = lds_edited<TWO, BUILD>(*e, ui, u[i + KCAP / 2], cu, vi, TWO ? v[i + KCAP / 2] : 0.0, cv, false);
     }
   } else {
     for (int k0 = 0; k0 < N; k0 += 8) {
@@ -1920,7 +1924,7 @@ __device__ inline void lds_edit(double *D, const double *u, const double *v, dou
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        D[(k0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv);
+        D[(k0 + q) * KCAP + i] = lds_edited<TWO, BUILD>(h[q], ui, a[q], cu, vi, b[q], cv, q == 0);
     }
   }
 }
