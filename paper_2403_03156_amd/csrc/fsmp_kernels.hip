@@ -184,8 +184,7 @@ __device__ inline XsExp xs_exp(const ModelDev &md, double xs) {
 __device__ inline double phi_partial(const ModelDev &md, const XsExp &x, int64_t k) {
   const double a = x.e2 * md.ptab[2 * k];
   if (md.kind == FSMP_PHI_EXP) return a * md.inv_tau2;
-  const double b = x.e12 * md.ptab[2 * k + 1];
-  return md.C * (a - b);
+  return md.C * fma(-x.e12, md.ptab[2 * k + 1], a);
 }
 
 struct GridPos {
@@ -209,9 +208,9 @@ __device__ inline double phi_total(const ModelDev &md, double t0, int glo, int g
   return p.n > 0 ? phi_partial(md, xs_exp(md, p.xs), p.n) : 0.0;
 }
 
-// 1 - e^{-y} for 0 <= y <= 1/4 by its Taylor series (thirteen terms: the rest is below
+// (1 - e^{-y}) / y for 0 <= y <= 1/4 by its Taylor series (thirteen terms: the rest is below
 // 2^-56 of the value), all terms in one chain of multiply-adds
-__device__ inline double one_minus_exp_small(double y) {
+__device__ inline double one_minus_exp_series(double y) {
   const double x = -y;
   double p = 1.0 / 6227020800.0;
   p = fma(p, x, 1.0 / 479001600.0);
@@ -225,8 +224,7 @@ __device__ inline double one_minus_exp_small(double y) {
   p = fma(p, x, 1.0 / 24.0);
   p = fma(p, x, 1.0 / 6.0);
   p = fma(p, x, 0.5);
-  p = fma(p, x, 1.0);
-  return y * p;
+  return fma(p, x, 1.0);
 }
 
 // What a light-curve start t0 contributes to a sweep, the same in all lanes of a chain's group:
@@ -268,8 +266,9 @@ __device__ inline T0Terms t0_terms(const ModelDev &md, double t0, int glo, int g
   const double y = f * (lane == 0 ? md.inv_tau2 : lane == 1 ? md.inv_tau12 : md.inv_tau1);
   double v, e;
   if (md.small_dt && f <= md.dt) {
-    v = one_minus_exp_small(y);
-    e = 1.0 - v;
+    const double p = one_minus_exp_series(y);
+    v = y * p;
+    e = fma(-y, p, 1.0);
   } else {
     v = -expm1(-y);
     e = exp(-y);
@@ -312,6 +311,46 @@ __device__ inline double group_sum(double v) {
   if constexpr (W >= 4) v += dpp_move<0x4E>(v);  // quad_perm [2, 3, 0, 1]: xor 2
   if constexpr (W >= 2) v += dpp_move<0xB1>(v);  // quad_perm [1, 0, 3, 2]: xor 1
   return v;
+}
+
+// v times the v of the lane whose index differs by S (16 or 32): gfx950's swaps of rows and of the
+// halves of a wavefront, with the same register on both sides, leave both factors in every lane
+template <int S>
+__device__ inline double lane_xor_product(double v) {
+#if defined(__AMDGCN__)
+  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  if constexpr (S == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) * __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) * __hiloint2double((int)h[1], (int)l[1]);
+  }
+#else
+  return v * __shfl_xor(v, S, kWave);
+#endif
+}
+
+// The product of v over the lanes of a group of W whose index is the same mod RO, by halves: lane
+// offsets W/2, ..., RO (below 16 as in group_sum: a rotation by 4 after one by 8 pairs as xor 4)
+template <int W, int RO>
+__device__ inline double class_product(double v) {
+  static_assert(RO == 4 || RO >= 16, "offsets below 16 come in a pair");
+  if constexpr (W >= 64 && RO < 64) v = lane_xor_product<32>(v);
+  if constexpr (W >= 32 && RO < 32) v = lane_xor_product<16>(v);
+  if constexpr (RO == 4) {
+    v *= dpp_move<0x128>(v);  // row_ror:8
+    v *= dpp_move<0x124>(v);  // row_ror:4
+  }
+  return v;
+}
+
+// x / b from inv = 1 / b: the quotient's own rounding but for rare ties
+__device__ inline double ratio(double x, double b, double inv) {
+  const double q = x * inv;
+  return fma(fma(-q, b, x), inv, q);
 }
 
 template <int W>
@@ -409,7 +448,7 @@ __device__ inline int birth_draw(const ModelDev &md, const T0Terms &t, double ta
   int lo = 0, hi = last;
   {
     const double a2 = md.Cd2 * t.e2, a12 = md.Cd12 * t.e12;
-    const double R = (a2 - a12) - target;
+    const double R = fma(md.Cd2, t.e2, -a12) - target;
     const float L = 0.69314718f * (fast_log2((float)a2) - fast_log2((float)R));
     const float w0 = (float)a12 * fast_rcp((float)a2);
     float k = L * md.ga_inv;
@@ -1013,22 +1052,29 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         if (glo <= ghi) tp = t0_terms<LPC>(md, t0p, glo, ghi, lane, gbase);
         double S = 0.0;  // sum over the PEs of log r(t0p) / r(t0), r the rise factor
         if (biexp && N > 0) {
-          // the rise factors of a lane's PEs at both t0 multiplied in runs of up to eight (each
-          // at least an ulp of t0 over tau_rise: far from underflow), one log per run
-          double pn = 1.0, pc = 1.0;
-          int m = 0;
-          for (int i = lane; i < N; i += LPC) {
-            const int g = zg[i];
-            pn *= rise_at(md, rt, tp, t0p, g);
-            pc *= rise_at(md, rt, tc, t0, g);
-            if (++m == 8) {
-              S += log(pn / pc);
-              pn = pc = 1.0;
-              m = 0;
+          // the rise factors of a lane's PEs at both t0 multiplied (each at least an ulp of t0 over
+          // tau_rise: eight are far from underflow), one log per lane.  PEs m and m + H of a lane
+          // first, then every other of those, then the two halves: the order of class_product
+          constexpr int E = (KCAP + LPC - 1) / LPC, H = (E + 1) / 2;
+          static_assert(E <= 8, "one log per lane");
+          double pn[2] = {1.0, 1.0}, pc[2] = {1.0, 1.0};
+          int i = lane;
+          for (int m = 0; m < H && i < N; ++m, i += LPC) {
+            double n0 = rise_at(md, rt, tp, t0p, zg[i]), c0 = rise_at(md, rt, tc, t0, zg[i]);
+            if (i + H * LPC < N) {
+              const int g = zg[i + H * LPC];
+              n0 *= rise_at(md, rt, tp, t0p, g);
+              c0 *= rise_at(md, rt, tc, t0, g);
+            }
+            if (m & 1) {
+              pn[1] *= n0;
+              pc[1] *= c0;
+            } else {
+              pn[0] *= n0;
+              pc[0] *= c0;
             }
           }
-          S += log(pn / pc);
-          S = group_sum<LPC>(S);
+          S = group_sum<LPC>(log((pn[0] * pn[1]) / (pc[0] * pc[1])));
         }
         if (glo <= ghi) t0_phi(md, tp);
         const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
@@ -1109,8 +1155,9 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
           if (om > 0.0) {
             double lom, lLam;
             group_log2<LPC>(om, Lam, lane, gbase, lom, lLam);
-            dnu = 0.5 * (-lro - lom + (rm2o - xj * xj / om) * md.inv_s);
-            la = dnu - lLam + lgn[N] - (N == 1 ? md.logJ : 0.0);
+            const double v = -lro - lom + (rm2o - ratio(xj * xj, om, 1.0 / om)) * md.inv_s;
+            dnu = 0.5 * v;
+            la = fma(0.5, v, -lLam) + lgn[N] - (N == 1 ? md.logJ : 0.0);
             valid = true;
           } else {
             st |= FSMP_ST_FACTOR;
@@ -1180,8 +1227,9 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
           up = beta - p;
           double ld2, lLam;
           group_log2<LPC>(delta2, Lam, lane, gbase, ld2, lLam);
-          dnu = -0.5 * (-lrn + ld2 + (rm2n - up * up / delta2) * md.inv_s);
-          la = dnu + lLam - lgn[N + 1] + (N == 0 ? md.logJ : 0.0);
+          const double v = -lrn + ld2 + (rm2n - ratio(up * up, delta2, 1.0 / delta2)) * md.inv_s;
+          dnu = -0.5 * v;
+          la = fma(-0.5, v, lLam) - lgn[N + 1] + (N == 0 ? md.logJ : 0.0);
           valid = true;
         } else {
           st |= FSMP_ST_FACTOR;
@@ -1197,7 +1245,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         if (delta2 > 0.0 && om > 0.0) {
           double lom, ld2, lpr;
           group_log3<LPC>(om, delta2, pr_sh, lane, gbase, lom, ld2, lpr);
-          dnu = 0.5 * (-lom - ld2 + (up * up / delta2 - xj * xj / om) * md.inv_s);
+          dnu = 0.5 * (-lom - ld2 + (ratio(up * up, delta2, 1.0 / delta2) - ratio(xj * xj, om, 1.0 / om)) * md.inv_s);
           // mixture form: the removed and the added PE carry their own rho and rho mu^2
           if constexpr (MCP) dnu += 0.5 * (lrn - lro + (rm2o - rm2n) * md.inv_s);
           la = dnu + (lpd + lpr);
@@ -2241,7 +2289,12 @@ __device__ __attribute__((always_inline)) inline void chain_lds_body(const Chain
               pc *= rise_at(md, rt, tc, t0, g);
             }
           }
-          S = group_sum<GW>(log(pn / pc));
+          if constexpr (SYM) {
+            S = group_sum<GW>(log(pn / pc));
+          } else {
+            // one log for the PEs that share a lane of the narrow device-memory groups
+            S = group_sum<RO>(log(class_product<GW, RO>(pn) / class_product<GW, RO>(pc)));
+          }
         }
         t0_phi(md, tp);
         const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
@@ -2357,13 +2410,15 @@ __device__ __attribute__((always_inline)) inline void chain_lds_body(const Chain
         double l0, l1, l2;
         group_log3<GW>(move == 1 ? delta2 : om, move == 3 ? delta2 : Lam, pr_sh, gl, gbase, l0, l1, l2);
         if (move == 1) {
-          dnu = -0.5 * (-lrn + l0 + (rm2n - up * up * inv_d2) * md.inv_s);
-          la = dnu + l1 - lgn[N + 1] + (N == 0 ? md.logJ : 0.0);
+          const double v = -lrn + l0 + (rm2n - ratio(up * up, delta2, inv_d2)) * md.inv_s;
+          dnu = -0.5 * v;
+          la = fma(-0.5, v, l1) - lgn[N + 1] + (N == 0 ? md.logJ : 0.0);
         } else if (move == 2) {
-          dnu = 0.5 * (-lro - l0 + (rm2o - xj * xj * inv_om) * md.inv_s);
-          la = dnu - l1 + lgn[N] - (N == 1 ? md.logJ : 0.0);
+          const double v = -lro - l0 + (rm2o - ratio(xj * xj, om, inv_om)) * md.inv_s;
+          dnu = 0.5 * v;
+          la = fma(0.5, v, -l1) + lgn[N] - (N == 1 ? md.logJ : 0.0);
         } else {
-          dnu = 0.5 * (-l0 - l1 + (up * up * inv_d2 - xj * xj * inv_om) * md.inv_s);
+          dnu = 0.5 * (-l0 - l1 + (ratio(up * up, delta2, inv_d2) - ratio(xj * xj, om, inv_om)) * md.inv_s);
           // mixture form: the removed and the added PE carry their own rho and rho mu^2
           if constexpr (MCP) dnu += 0.5 * (lrn - lro + (rm2o - rm2n) * md.inv_s);
           la = dnu + (lpd + l2);

@@ -27,3 +27,18 @@ def test_lds_and_device_memory_groups_agree_bit_for_bit(tmp_path, mix):
     assert (out[0]["n_pe"][4:] > 5).all()
     for k in KEYS:
         np.testing.assert_array_equal(out[0][k], out[1][k], err_msg=k)
+
+
+def test_the_records_of_every_step_agree_bit_for_bit(tmp_path):
+    wl = synth.PRESETS["pileup"]
+    lam = np.array([0.8, 9.0, 14.0, 21.0])
+    b = synth.generate(wl, n_wave=len(lam), seed=15, lam=lam, lengths=np.array([300] * 4))
+    km = np.array([16, 32, 48, 64], np.int32)
+    log = []
+    for name, design in (("lds", fsmp.FSMP_DESIGN_GROUP_LDS), ("dm", fsmp.FSMP_DESIGN_GROUP_DEVMEM)):
+        d = tmp_path / name
+        d.mkdir()
+        log.append(_run_emu(str(d), wl, b["wave"], b["offsets"], b["lam"], km, 100, 40, 1, 9, [design] * 8,
+                            record_flags=fsmp.FSMP_REC_LOG)["log"])
+    for f in ("move", "flags", "j", "g", "t0", "dnu", "log_alpha"):
+        np.testing.assert_array_equal(log[0][f], log[1][f], err_msg=f)
