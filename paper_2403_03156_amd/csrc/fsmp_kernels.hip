@@ -723,6 +723,31 @@ __device__ inline void gram_set(const ModelDev &md, const double *vt, const doub
   if (lane == 0) Gm[(i * LD + i) * HS] = overlap(md, vt, ov, g, g, Lw) + rho_g;
 }
 
+// A lane's part of a sum of products over the PEs of a chain.  SPLIT: 4 lanes in the order of 16 with
+// an element each (group_sum<16>): products rounded, elements l and l + 8, l + 4 and l + 12 of lane l
+// (its first and third, second and fourth), then the two; the parts change places at each element.
+template <bool SPLIT>
+struct LaneSum {
+  double a = 0.0, b = 0.0;
+  __device__ inline void term(double x) {
+    const double t = a + x;
+    a = SPLIT ? b : t;
+    if (SPLIT) b = t;
+  }
+  __device__ inline void mac(double x, double y) {
+    if constexpr (SPLIT) {
+      const double p = x * y;
+      term(p);
+    } else {
+      a = fma(x, y, a);
+    }
+  }
+  template <int LPC>
+  __device__ inline double sum() const {
+    return group_sum<LPC>(SPLIT ? a + b : a);
+  }
+};
+
 template <int W>
 __device__ inline double group_max(double v) {
 #pragma unroll
@@ -735,7 +760,7 @@ __device__ inline double group_max(double v) {
 // the birth update of the inverse of the leading block, its columns owned by the group's
 // lanes: false if a Schur complement is not positive.  ek: the PEs' mixture components (their
 // own ridge rho_e on the diagonal), or null for the single charge law.  s1, s2: scratch.
-template <int LPC, int LD, int HS>
+template <int LPC, int LD, int HS, bool SPLIT = false>
 __device__ bool grp_build(const ModelDev &md, const double *vt, const double *ov, int Lw, double *M, double *s1,
                           double *s2, const int *zg, int N, int lane, const int *ek = nullptr) {
   for (int k = 0; k < N; ++k) {
@@ -743,14 +768,13 @@ __device__ bool grp_build(const ModelDev &md, const double *vt, const double *ov
     for (int i = lane; i < k; i += LPC) s1[i] = overlap(md, vt, ov, gk, zg[i], Lw);
     const double d = overlap(md, vt, ov, gk, gk, Lw) + (ek ? md.mix_rho[ek[k]] : md.rho);
     WAVE_SYNC();
-    double q = 0.0;
+    LaneSum<SPLIT> q;
     for (int i = lane; i < k; i += LPC) {
       const double e = grp_col_dot<LD, HS>(M, s1, i, k);
       s2[i] = e;
-      q = fma(s1[i], e, q);
+      q.mac(s1[i], e);
     }
-    q = group_sum<LPC>(q);
-    const double delta2 = d - q;
+    const double delta2 = d - q.template sum<LPC>();
     if (!(delta2 > 0.0)) return false;
     const double inv = 1.0 / delta2;
     WAVE_SYNC();
@@ -769,11 +793,11 @@ __device__ bool grp_build(const ModelDev &md, const double *vt, const double *ov
 // Precision form: rebuild G^-1 of the current PE list in FP64 into W, recompute x = G^-1 b in
 // FP64 and round W into the FP32 H.  False if a Schur complement is not positive.  `drift` =
 // the largest change of a charge mean, relative to max(1, |x|).  s1, s2 are scratch.
-template <int LPC, int LD, int HS, typename HT>
+template <int LPC, int LD, int HS, bool SPLIT, typename HT>
 __device__ bool grp_refresh(const ModelDev &md, const double *vt, const double *ov, int Lw, double *W, HT *H,
                             double *xv, const double *bv, double *s1, double *s2, const int *zg, int N, int lane,
                             double &drift) {
-  if (!grp_build<LPC, LD, HS>(md, vt, ov, Lw, W, s1, s2, zg, N, lane)) return false;
+  if (!grp_build<LPC, LD, HS, SPLIT>(md, vt, ov, Lw, W, s1, s2, zg, N, lane)) return false;
   double dr = 0.0;
   for (int i = lane; i < N; i += LPC) {
     const double xi = grp_col_dot<LD, HS>(W, bv, i, N);
@@ -799,6 +823,12 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
   static_assert(!MCP || (!FORCE && !F32), "the mixture form runs FP64 and does not replay");
   static_assert(KCAP % 16 == 0, "the column loads go in chunks of 16 rows below the capacity");
   using HT = typename std::conditional<F32, float, double>::type;
+  // The FP32 form runs capacity 16 in groups of 16 lanes or, with many chains, of 4: the 4 lanes take
+  // their sums in the order of the 16, and the 16 their t0 products by the classes of the 4, so that a
+  // chain is the same bits in either.  (In the 4 lanes 64,000 chains x 400 sweeps take 22.4 ms, 21.8 in
+  // an order of their own.)
+  constexpr bool SPLIT = F32 && KCAP == 16 && LPC == 4;
+  constexpr int TRO = F32 && LPC == 16 ? 4 : LPC;
   constexpr int CPW = kWave / LPC;
   using CL = ChainLayout<KCAP, F32, MCP>;
   constexpr int LD = CL::LD;
@@ -910,7 +940,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       for (int k = lane; k < n0; k += LPC) zg[k] = z0[k];
       WAVE_SYNC();
       double *M = F32 ? W : (double *)H;
-      if (grp_build<LPC, LD, HS>(md, vt, ov, Lw, M, s1, s2, zg, n0, lane)) {
+      if (grp_build<LPC, LD, HS, SPLIT>(md, vt, ov, Lw, M, s1, s2, zg, n0, lane)) {
         for (int k = lane; k < n0; k += LPC) s1[k] = mf[zg[k] - glo] + md.rhom;  // b
         WAVE_SYNC();
         for (int i = lane; i < n0; i += LPC) {
@@ -950,7 +980,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       if constexpr (F32) {
         // precision form: FP64 rebuild of G^{-1} every refresh_M sweeps
         double drift;
-        if (!grp_refresh<LPC, LD, HS>(md, vt, ov, Lw, W, H, xv, bv, s1, s2, zg, N, lane, drift)) st |= FSMP_ST_FACTOR;
+        if (!grp_refresh<LPC, LD, HS, SPLIT>(md, vt, ov, Lw, W, H, xv, bv, s1, s2, zg, N, lane, drift)) st |= FSMP_ST_FACTOR;
         else if (drift > a.drift_bound) st |= FSMP_ST_DRIFT;
       } else if constexpr (!CORR) {
         // FP64 form: G^-1 rebuilt in place by bordering and x = G^-1 b recomputed, against the
@@ -1074,7 +1104,11 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
               pc[0] *= c0;
             }
           }
-          S = group_sum<LPC>(log((pn[0] * pn[1]) / (pc[0] * pc[1])));
+          if constexpr (TRO < LPC) {
+            S = group_sum<TRO>(log(class_product<LPC, TRO>(pn[0] * pn[1]) / class_product<LPC, TRO>(pc[0] * pc[1])));
+          } else {
+            S = group_sum<LPC>(log((pn[0] * pn[1]) / (pc[0] * pc[1])));
+          }
         }
         if (glo <= ghi) t0_phi(md, tp);
         const double part = (double)N * (t0p - t0) * md.inv_tau2 + S;
@@ -1310,19 +1344,20 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
       }
       WAVE_SYNC();
       // pass 1 over H: eta = H gamma, h = row j; gamma^T eta, gamma^T x
-      double qa = 0.0, pa = 0.0;
+      LaneSum<SPLIT> sqa, spa;
       for (int i = lane; i < N; i += LPC) {
         if (wg) {
           const double e = grp_col_dot<LD, HS>(H, s2, i, N);
           s3[i] = e;
-          qa += s2[i] * e;
-          pa += s2[i] * xv[i];
+          sqa.mac(s2[i], e);
+          spa.mac(s2[i], xv[i]);
         }
         if (wj) s1[i] = (double)H[(j * LD + i) * HS];
       }
+      double qa = 0.0, pa = 0.0;
       if (wg) {
-        qa = group_sum<LPC>(qa);
-        pa = group_sum<LPC>(pa);
+        qa = sqa.template sum<LPC>();
+        pa = spa.template sum<LPC>();
       }
       WAVE_SYNC();
       // the residuals against G: r_eta = gamma - G eta (s5), r_h = e_j - G h (s4), s = b - G x (s6)
@@ -1335,58 +1370,57 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         x_j = xv[j];
       }
       // first correction terms
-      double qb = 0.0, pb = 0.0, jb = 0.0, ob = 0.0, xb = 0.0;
+      LaneSum<SPLIT> sqb, spb, sjb, sob, sxb;
       for (int i = lane; i < N; i += LPC) {
         if (wg) {
-          qb += s3[i] * s5[i];
-          pb += s3[i] * s6[i];
+          sqb.mac(s3[i], s5[i]);
+          spb.mac(s3[i], s6[i]);
         }
         if (wj) {
-          if (wg) jb += s1[i] * s5[i];
-          ob += s1[i] * s4[i];
-          xb += s1[i] * s6[i];
+          if (wg) sjb.mac(s1[i], s5[i]);
+          sob.mac(s1[i], s4[i]);
+          sxb.mac(s1[i], s6[i]);
         }
       }
+      double qb = 0.0, pb = 0.0, jb = 0.0, ob = 0.0, xb = 0.0;
       if (wg) {
-        qb = group_sum<LPC>(qb);
-        pb = group_sum<LPC>(pb);
+        qb = sqb.template sum<LPC>();
+        pb = spb.template sum<LPC>();
       }
       if (wj) {
-        if (wg) jb = group_sum<LPC>(jb);
-        ob = group_sum<LPC>(ob);
-        xb = group_sum<LPC>(xb);
+        if (wg) jb = sjb.template sum<LPC>();
+        ob = sob.template sum<LPC>();
+        xb = sxb.template sum<LPC>();
       }
       // pass 2 over H: H r_eta, H r_h; the second terms, then eta and h corrected in place
-      double qc = 0.0, pc = 0.0, jc = 0.0, oc = 0.0, xc = 0.0;
+      LaneSum<SPLIT> sqc, spc, sjc, soc, sxc;
       for (int i = lane; i < N; i += LPC) {
         double te = 0.0, th = 0.0;
         if (wg) {
           te = grp_col_dot<LD, HS>(H, s5, i, N);
-          qc += s5[i] * te;
-          pc += te * s6[i];
+          sqc.mac(s5[i], te);
+          spc.mac(te, s6[i]);
         }
         if (wj) {
           th = grp_col_dot<LD, HS>(H, s4, i, N);
-          if (wg) jc += s4[i] * te;
-          oc += s4[i] * th;
-          xc += th * s6[i];
+          if (wg) sjc.mac(s4[i], te);
+          soc.mac(s4[i], th);
+          sxc.mac(th, s6[i]);
         }
         if (wg) s3[i] += te;
         if (wj) s1[i] += th;
       }
       double Qgg = 0.0, Pg = 0.0, Qjg = 0.0, Bgg = 0.0, Bp = 0.0, Bjg = 0.0, Bom = 0.0, Bxj = 0.0;
       if (wg) {
-        qc = group_sum<LPC>(qc);
-        pc = group_sum<LPC>(pc);
+        const double qc = sqc.template sum<LPC>(), pc = spc.template sum<LPC>();
         Qgg = qa + qb + qc;
         Pg = pa + pb + pc;
         Bgg = fabs(qc);
         Bp = fabs(pc);
       }
       if (wj) {
-        if (wg) jc = group_sum<LPC>(jc);
-        oc = group_sum<LPC>(oc);
-        xc = group_sum<LPC>(xc);
+        const double jc = wg ? sjc.template sum<LPC>() : 0.0;
+        const double oc = soc.template sum<LPC>(), xc = sxc.template sum<LPC>();
         om = h_j + ob + oc;
         xj = x_j + xb + xc;
         Qjg = eta_j + jb + jc;
@@ -1434,15 +1468,14 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         const double d = overlap(md, vt, ov, gnew, gnew, Lw) + md.rho;
         beta = mf[gnew - glo] + md.rhom;
         WAVE_SYNC();
-        double q = 0.0, p = 0.0;
+        LaneSum<SPLIT> sq, sp;
         for (int i = lane; i < N; i += LPC) {
           const double e = grp_col_dot<LD, HS>(W, s2, i, N);
           s3[i] = e;
-          q += s2[i] * e;
-          p += s2[i] * xv[i];
+          sq.mac(s2[i], e);
+          sp.mac(s2[i], xv[i]);
         }
-        q = group_sum<LPC>(q);
-        p = group_sum<LPC>(p);
+        double q = sq.template sum<LPC>(), p = sp.template sum<LPC>();
         if (move == 3) {
           WAVE_SYNC();
           const double e = s3[j];
@@ -1471,7 +1504,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         // the FP64 rebuild
         if (inexact || (valid && (bnd > kF32Tol * fmax(1.0, fabs(dnu)) || fabs(logu - la) <= bnd))) {
           double drift;
-          if (N == 0 || grp_refresh<LPC, LD, HS>(md, vt, ov, Lw, W, H, xv, bv, s1, s2, zg, N, lane, drift)) {
+          if (N == 0 || grp_refresh<LPC, LD, HS, SPLIT>(md, vt, ov, Lw, W, H, xv, bv, s1, s2, zg, N, lane, drift)) {
             f64_eval_W();
           } else {
             valid = false;
@@ -1660,9 +1693,9 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
 
     // ---- record after burn-in
     if (step >= burn) {
-      double Q = 0.0;
-      for (int i = lane; i < N; i += LPC) Q += xv[i];
-      Q = group_sum<LPC>(Q);
+      LaneSum<SPLIT> sQ;
+      for (int i = lane; i < N; i += LPC) sQ.term(xv[i]);
+      const double Q = sQ.template sum<LPC>();
       const double v0 = (double)N, v1 = Q, v2 = t0;
       const int64_t i = step - burn;
       if (lane == 0) {
@@ -1710,7 +1743,7 @@ __global__ void __launch_bounds__(kWave *WPB) __attribute__((amdgpu_waves_per_eu
         bool ok = true;
         if constexpr (F32) {
           double drift;
-          if (N > 0 && !grp_refresh<LPC, LD, HS>(md, vt, ov, Lw, W, H, xv, bv, s1, s2, zg, N, lane, drift)) ok = false;
+          if (N > 0 && !grp_refresh<LPC, LD, HS, SPLIT>(md, vt, ov, Lw, W, H, xv, bv, s1, s2, zg, N, lane, drift)) ok = false;
         }
         for (int r = lane; r < N; r += LPC) {
           for (int k = 0; k <= r; ++k) {

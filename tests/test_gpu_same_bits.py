@@ -49,3 +49,48 @@ def test_every_kernel_gives_the_same_bits(preset, form):
         if isinstance(v, np.ndarray):
             np.testing.assert_array_equal(out[1][k], v, err_msg=k)
             np.testing.assert_array_equal(out[2][k], v, err_msg=k)
+
+
+@pytest.mark.parametrize("preset", ["batched", "plain"])
+def test_mixed_precision_does_not_depend_on_the_number_of_chains(preset):
+    # capacity 16 in 16-lane groups alone, in 4-lane groups among 9,000 chains, in the launch of
+    # capacity 32; with rebuilds from the bounds and every 64 sweeps, and from start lists
+    wl = synth.PRESETS[preset]
+    n, r = 100, 90
+    lam = np.linspace(0.1, 3.2, n)
+    b = synth.generate(wl, n_wave=n, seed=2, lam=lam)
+    km = np.full(n, 16, np.int32)
+    km[:3] = (1, 5, 9)
+    t0 = float(np.floor(wl.t0_min)) + 1.0
+    L = int(np.diff(b["offsets"])[0])
+    z = [np.unique(np.clip(np.rint(np.asarray(t) * 4), int(4 * t0) + 1, 4 * L - 1).astype(int))[:k].tolist()
+         if i % 2 else [] for i, (t, k) in enumerate(zip(b["times"], km))]
+    s = fsmp.Sampler(ser=wl.ser, phi_kind=wl.phi_kind, tau_rise=wl.tau_rise, tau_decay=wl.tau_decay,
+                     t0_min=wl.t0_min, t0_max=wl.t0_max, sigma_eps=wl.sigma_eps, mu_q=wl.mu_q, sigma_q=wl.sigma_q,
+                     n_steps=200, burn_in=60, seed=3, thin=20, k_max=32,
+                     record_flags=fsmp.FSMP_REC_TRACE | fsmp.FSMP_REC_LOG | fsmp.FSMP_REC_CHARGE,
+                     precision=fsmp.FSMP_FP32_REFRESH, refresh_M=64)
+
+    def run(rep, k, wide32=False):
+        # wide32: a waveform of capacity 32 besides, so that both share a launch
+        kk = np.tile(k, rep)
+        wid = np.tile(np.arange(n, dtype=np.uint64), rep)
+        if wide32:
+            kk[0] = 32
+        off = np.concatenate([[0], np.cumsum(np.full(n * rep, L, np.int64))])
+        s.set_timing(True)
+        out = s.sample(torch.from_numpy(np.tile(b["wave"], rep)).cuda(), off, np.tile(lam, rep), kmax=kk, kz=32,
+                       wave_id=wid, z_init=z * rep, t0_init=np.full(n * rep, t0))
+        lanes = {(t["kcap"], t["lanes"]) for t in s.last_timings() if t["kcap"] > 0}
+        o = to_host(out)
+        lg = o.pop("log").view(fsmp.LOGREC_DTYPE)
+        o.update({"log " + f: lg[f] for f in ("move", "flags", "j", "g", "t0", "dnu", "log_alpha")})
+        return lanes, {q: v[-n + 1:] for q, v in o.items() if isinstance(v, np.ndarray)}  # (the first one apart)
+
+    print(f"[case] mixed precision few and many, {preset}", flush=True)
+    few, many, joined = run(1, km), run(r, km), run(1, km, wide32=True)
+    assert few[0] == {(16, 16)} and many[0] == {(16, 4)} and joined[0] == {(32, 16)}
+    assert few[1]["n_pe"].max() > 3
+    for k, v in few[1].items():
+        np.testing.assert_array_equal(many[1][k], v, err_msg=k)
+        np.testing.assert_array_equal(joined[1][k], v, err_msg=k)
