@@ -300,12 +300,15 @@ fsmp_status fsmp_server_create(fsmp_server **out, const fsmp_ser *ser, const fsm
     // with its state in device memory needs many memory round trips per sweep.  The FP32
     // form has lane groups with G^-1 in device memory only: its wide groups (16 lanes per
     // chain at capacities 16 and 32, the narrow ones above, which are 32-64 lanes wide
-    // from capacity 64 up).
+    // from capacity 64 up).  Above capacity 64, where kernels round differently, the choice may
+    // not follow the number of channels that a micro-batch happens to hold: an event's result
+    // would depend on the events beside it.  The LDS chains, the faster ones for few.
     if (cfg->precision == FSMP_FP32_REFRESH) {
       (void)fsmp_set_design(sl->ctx, 0, FSMP_DESIGN_GROUP_DEVMEM);
       (void)fsmp_set_design(sl->ctx, 0, FSMP_DESIGN_GROUP_DEVMEM_WIDE);
     } else {
       (void)fsmp_set_design(sl->ctx, 0, FSMP_DESIGN_GROUP);
+      for (const int cap : {96, 128, 160, 192}) (void)fsmp_set_design(sl->ctx, cap, FSMP_DESIGN_GROUP_LDS);
     }
     (void)hipSetDevice(device);
     if (hipStreamCreateWithFlags(&sl->stream, hipStreamNonBlocking) != hipSuccess ||
