@@ -446,7 +446,8 @@ fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
  * so (not set by this call, the autotuner or FSMP_CHAIN_DESIGN) runs
  * the LDS kernels, which exist in the library for every capacity and the mixture law, in the
  * corrected form from 48 up, for as many chains as they are the faster ones for (14,000 at
- * capacity 16 to 3,800 at 160), and the narrow device-memory groups beyond; the FP32 form its
+ * capacity 16 to 3,800 at 160), and the narrow device-memory groups beyond (the LDS kernels again
+ * where the SER tables leave those no room); the FP32 form its
  * wide groups for few chains.  FSMP_DESIGN_GROUP_DEVMEM_WIDE stands for the kernels that shorten
  * a sweep: in FP64 it too runs the LDS kernels while the chains are few enough (always up to
  * capacity 64 and at 192, 5,500 chains at 96 to 2,000 at 160).  The kernels that these two choose

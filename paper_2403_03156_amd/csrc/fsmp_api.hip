@@ -325,7 +325,11 @@ int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
     return !wide && cnt <= kF32WideChains[q] && design_available(c, kCaps[q], FSMP_DESIGN_GROUP_DEVMEM_WIDE)
                ? (int)FSMP_DESIGN_GROUP_DEVMEM_WIDE
                : dz;
-  if (cnt <= (wide ? kLdsChainsWide : kLdsChains)[q] && design_available(c, kCaps[q], kDesignLds)) return kDesignLds;
+  // (a response whose tables leave the device-memory groups no LDS: the LDS kernels, whose tables stay
+  // in device memory, at any number of chains)
+  if ((cnt <= (wide ? kLdsChainsWide : kLdsChains)[q] || !design_available(c, kCaps[q], dz)) &&
+      design_available(c, kCaps[q], kDesignLds))
+    return kDesignLds;
   return dz;
 }
 

@@ -210,3 +210,25 @@ def test_mixed_precision_in_the_narrow_groups():
     o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, n_steps, burn, seed, kz, kmax=km)
     parted = compare_chains(g, o, tol=1e-7)
     check_partings(parted, p, b, b["lam"], km, 1, n_steps, burn, seed, kz, sampler)
+
+
+def test_long_responses_at_any_number_of_chains():
+    # a response whose overlap table takes the LDS of the device-memory groups: accepted for few chains
+    # and for more than the LDS kernels are otherwise chosen for, with the same results
+    wl = synth.Workload("long", 8, (600,), "uniform", 0.5, 6.0, ser=(8.0, 1.5, 45.0))
+    b = synth.generate(wl, n_wave=8, seed=3)
+    km = np.array([16, 32, 48, 64] * 2, np.int32)
+    r = 1800  # 3,600 chains per capacity: past the 3,500 of capacity 64
+    s = gpu_sampler(wl, 20, 10, 1, 2, sub=8, support=512)
+    with pytest.raises(RuntimeError):
+        s.set_design(64, fsmp.FSMP_DESIGN_GROUP_DEVMEM)
+    print("[case] long response", flush=True)
+    few = to_host(s.sample(torch.from_numpy(b["wave"]).cuda(), b["offsets"], b["lam"], kmax=km, kz=64))
+    off = np.arange(8 * r + 1, dtype=np.int64) * 600
+    many = to_host(s.sample(torch.from_numpy(np.tile(b["wave"], r)).cuda(), off, np.tile(b["lam"], r),
+                            kmax=np.tile(km, r), kz=64, wave_id=np.tile(np.arange(8, dtype=np.uint64), r)))
+    for k in KEYS:
+        np.testing.assert_array_equal(many[k][-8:], few[k], err_msg=k)
+    p = oracle_params(wl, sub=8, support=512)
+    o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, 20, 10, 2, 64, kmax=km)
+    assert len(compare_chains(few, o)) == 0
