@@ -303,20 +303,64 @@ int effective_design(const fsmp_ctx *c, int kcap, int design) {
 // that latency above.  At 32, 48, 64 and 192 sampling has no wide groups: one chain of 16 with 8x the
 // sweeps of the others, LDS / wide 32: 16,000 4.5 / 11.5, 32,000 8.4 / 11.9;  48: 16,000 9.5 / 12.2;
 // 64: 4,000 5.0 / 8.2, 16,000 15.1 / 14.8;  192: 1,000 10 / 41, 16,000 134 / 187.
+// These hold on lists of kNFull PEs and more.  A sweep of the LDS kernels takes nearly as long on short
+// lists (its latency, and the LDS is sized by the capacity), one of the device-memory groups a fraction:
+// a short run from no PEs, or a K_max far above the intensity, is better off there with fewer chains.
+// LDS / narrow at capacity 160: N = 20 500 chains 9.6 / 7.2, 2,000 37.6 / 9.2;  N = 40 500 12.4 / 14.5,
+// 2,000 46 / 19;  N = 80 2,000 60 / 48;  N = 120 3,500 116 / 154;  128: N = 20 500 5.6 / 7.5, 2,000
+// 20.0 / 9.5;  N = 80 4,500 67 / 116;  96: N = 8 1,000 8.1 / 8.5, 5,500 32 / 11;  N = 40 5,500 43 / 53;
+// 64: N = 8 3,500 14.5 / 7.9;  48: N = 2 5,500 14.4 / 9.2;  32: N = 2 8,000 12.0 / 9.8;  192: N = 20
+// 500 10.3 / 7.6, 8,000 154 / 27;  N = 80 2,000 64 / 47;  N = 120 8,000 283 / 345.  Between the lists of
+// kNShort PEs, where kLdsChainsShort is the crossing, and kNFull the crossing grows about evenly by
+// factors (160 at N = 40: 660 by the rule, 700 between the measured counts).
 constexpr int64_t kAnyChains = INT64_MAX;
 static const int64_t kLdsChains[kNumCaps] = {14000, 32000, 5500, 3500, 6000, 5000, 3800, kAnyChains};
 static const int64_t kLdsChainsWide[kNumCaps] = {kAnyChains, kAnyChains, kAnyChains, kAnyChains,
                                                  5500, 4000, 2000, kAnyChains};
+static const double kLdsChainsShort[kNumCaps] = {14000, 6300, 2200, 1800, 1100, 800, 370, 370};
+static const double kNShort[kNumCaps] = {0, 2, 4, 8, 8, 20, 20, 20};
+static const double kNFull[kNumCaps] = {0, 7, 14, 22, 38, 62, 100, 110};
+constexpr double kLds192 = 2600;  // where the crossing at capacity 192 tends to below kNFull
+
+// the LDS kernels' last number of chains on lists of n_mean PEs
+double lds_chains(int q, bool wide, double n_mean) {
+  const int64_t full = (wide ? kLdsChainsWide : kLdsChains)[q];
+  if (n_mean >= kNFull[q] || (full == kAnyChains && kCaps[q] != 192)) return (double)full;
+  const double to = full == kAnyChains ? kLds192 : (double)full, from = std::min(kLdsChainsShort[q], to);
+  const double x = std::max(0.0, n_mean - kNShort[q]) / (kNFull[q] - kNShort[q]);
+  return from * std::pow(to / from, x);
+}
+
+// A chain's mean number of PEs over its sweeps, before it has run: from the n0 of its start list a PE
+// more every four sweeps (births are a quarter of the proposals) up to the intensity.
+double expected_list(double lambda, int kmax, int steps, double n0) {
+  const double d = std::max(0.0, std::min(lambda, (double)kmax) - n0);
+  return n0 + (steps <= 4.0 * d ? steps / 8.0 : d * (1.0 - 2.0 * d / steps));
+}
+
+// the sum of expected_list over the chains of waveform i of a batch
+double expected_lists(const fsmp_ctx *c, const fsmp_batch *b, int64_t i) {
+  const int C = c->cfg.n_chains, steps = b->n_steps ? b->n_steps[i] : c->cfg.n_steps;
+  const int kmax = b->kmax ? b->kmax[i] : c->cfg.k_max;
+  const double lambda = b->lambda ? b->lambda[i] : (double)kmax;
+  if (!b->z_init_offsets) return C * expected_list(lambda, kmax, steps, 0.0);
+  double s = 0.0;
+  for (int64_t ch = i * C; ch < (i + 1) * C; ++ch)
+    s += expected_list(lambda, kmax, steps, (double)(b->z_init_offsets[ch + 1] - b->z_init_offsets[ch]));
+  return s;
+}
+
 // FP32-refresh form, up to this many chains the wide groups (16 lanes per chain) at capacities 16
 // and 32: 4,000 chains x 100 sweeps 1.08 against 1.43 ms and 1.40 against 2.69; 16,000 at
 // capacity 16 2.45 against 1.69, at 32 wide also at 64,000 (10.9 against 18.6).
 static const int64_t kF32WideChains[kNumCaps] = {8000, kAnyChains};
 
-// The kernels a bucket of `cnt` chains runs: the design the caller (or the autotuner) has set;
-// where none is set, and for the wide device-memory groups, by the number of chains.  Past the
-// LDS kernels' range a capacity that is not set runs the narrow groups (at capacity 16, 64,000
-// chains x 200 sweeps: 4.2 ms against 6.9 ms with a lane per chain).
-int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
+// The kernels a bucket of `cnt` chains with n_mean PEs runs: the design the caller (or the autotuner)
+// has set; where none is set, and for the wide device-memory groups, by the number of chains.  Past
+// the LDS kernels' range a capacity that is not set runs the narrow groups (at capacity 16, 64,000
+// chains x 200 sweeps: 4.2 ms against 6.9 ms with a lane per chain), and so does the wide design where
+// it has no groups of its own for sampling.
+int routed_design(const fsmp_ctx *c, int q, int64_t cnt, double n_mean) {
   const int dz = effective_design(c, kCaps[q], c->design[q]);
   const bool wide = dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE;
   if (dz == kWideOnly) return FSMP_DESIGN_GROUP_DEVMEM_WIDE;
@@ -327,10 +371,10 @@ int routed_design(const fsmp_ctx *c, int q, int64_t cnt) {
                : dz;
   // (a response whose tables leave the device-memory groups no LDS: the LDS kernels, whose tables stay
   // in device memory, at any number of chains)
-  if ((cnt <= (wide ? kLdsChainsWide : kLdsChains)[q] || !design_available(c, kCaps[q], dz)) &&
+  if (((double)cnt <= lds_chains(q, wide, n_mean) || !design_available(c, kCaps[q], dz)) &&
       design_available(c, kCaps[q], kDesignLds))
     return kDesignLds;
-  return dz;
+  return wide && !design_available(c, kCaps[q], kWideOnly) ? (int)FSMP_DESIGN_GROUP_DEVMEM : dz;
 }
 
 // Whether the mixed-precision form's capacity-16 chains run in the launch of capacity 32 (no design
@@ -650,6 +694,7 @@ size_t fsmp_workspace_bytes(const fsmp_ctx *c, const fsmp_batch *b) {
   const bool fp32 = cf.precision == FSMP_FP32_REFRESH;
   const int sub = cf.grid_sub;
   int64_t cnt[kNumCaps] = {0};
+  double nsum[kNumCaps] = {0.0};
   size_t grid = 0;
   int64_t tmax = 0;
   for (int64_t i = 0; i < n; ++i) {
@@ -661,7 +706,10 @@ size_t fsmp_workspace_bytes(const fsmp_ctx *c, const fsmp_batch *b) {
     int kc = chain_kcap_for(b->kmax ? b->kmax[i] : cf.k_max);
     if (fp32 && kc == 48) kc = 64;
     for (int q = 0; q < kNumCaps; ++q)
-      if (kCaps[q] == kc) cnt[q] += cf.n_chains;
+      if (kCaps[q] == kc) {
+        cnt[q] += cf.n_chains;
+        nsum[q] += expected_lists(c, b, i);
+      }
   }
   if (f32_joined(c, cnt[0], cnt[1])) {
     cnt[1] += cnt[0];
@@ -672,7 +720,7 @@ size_t fsmp_workspace_bytes(const fsmp_ctx *c, const fsmp_batch *b) {
   // chain state of each bucket in its design; charge-draw scratch; partial-sum table
   for (int q = 0; q < kNumCaps; ++q) {
     if (!cnt[q]) continue;
-    const int dz = routed_design(c, q, cnt[q]);
+    const int dz = routed_design(c, q, cnt[q], nsum[q] / (double)cnt[q]);
     bytes += design_ws_doubles(kCaps[q], dz, cnt[q], fp32) * 8;
     if (dz == FSMP_DESIGN_LANE) bytes += lane_ws_ints(kCaps[q], cnt[q]) * 4;
     if (cf.record_flags & FSMP_REC_CHARGE) bytes += (size_t)((cnt[q] + 63) / 64 * 64) * kCaps[q] * (kCaps[q] + 1) * 8;
@@ -839,6 +887,10 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
   const int *caps = kCaps;
   int64_t n_order = 0;
   int64_t bucket_start[kNumCaps + 1] = {0};
+  double bucket_lists[kNumCaps] = {0.0};  // sum of the chains' expected PEs
+  for (int64_t i = 0; i < n; ++i)
+    for (int q = 0; q < kNumCaps; ++q)
+      if (kCaps[q] == chain_kcap_for(kmx[i])) bucket_lists[q] += expected_lists(c, b, i);
   const bool fp32 = cf.precision == FSMP_FP32_REFRESH;
   auto design_of = [&](int bi) -> int {
     // a replay runs the device-memory groups: the wide ones where the context has chosen them
@@ -848,7 +900,8 @@ fsmp_status sample_impl(fsmp_ctx *c, const fsmp_batch *b, const fsmp_samples *o,
       const bool wide = (dz == FSMP_DESIGN_GROUP_DEVMEM_WIDE || dz == kWideOnly) && caps[bi] >= 64;
       return wide ? FSMP_DESIGN_GROUP_DEVMEM_WIDE : FSMP_DESIGN_GROUP_DEVMEM;
     }
-    return routed_design(c, bi, bucket_start[bi + 1] - bucket_start[bi]);
+    const int64_t cnt = bucket_start[bi + 1] - bucket_start[bi];
+    return routed_design(c, bi, cnt, cnt > 0 ? bucket_lists[bi] / (double)cnt : 0.0);
   };
   // within a bucket, waveforms with per-waveform sweep counts in 16 bins of the batch's
   // largest count, the longest first, so that the chains of a workgroup end together and the
@@ -1380,17 +1433,22 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
   c->cfg.burn_in = 0;
   c->cfg.record_flags = 0;
   c->timing = true;
-  // chains per capacity, and the kernels that each design runs for that many
+  // chains per capacity and their expected PEs in the full run, and the kernels that each design
+  // runs for those: a trial runs these (its own sweeps are fewer, its lists shorter)
   int64_t cnt[kNumCaps] = {0};
+  double nsum[kNumCaps] = {0.0};
   for (int64_t i = 0; i < n; ++i) {
     int kc = chain_kcap_for(b->kmax ? b->kmax[i] : c->cfg.k_max);
     if (c->cfg.precision == FSMP_FP32_REFRESH && kc == 48) kc = 64;
     for (int q = 0; q < kNumCaps; ++q)
-      if (kCaps[q] == kc) cnt[q] += c->cfg.n_chains;
+      if (kCaps[q] == kc) {
+        cnt[q] += c->cfg.n_chains;
+        nsum[q] += expected_lists(c, b, i);
+      }
   }
   auto kernels_of = [&](int q, int d) {
     c->design[q] = d;
-    const int r = routed_design(c, q, cnt[q]);
+    const int r = routed_design(c, q, cnt[q], cnt[q] > 0 ? nsum[q] / (double)cnt[q] : 0.0);
     c->design[q] = saved_design[q];
     return r == FSMP_DESIGN_GROUP && kCaps[q] < 48 ? kDesignLds : r;
   };
@@ -1420,7 +1478,10 @@ fsmp_status fsmp_autotune(fsmp_ctx *c, const fsmp_batch *b, int32_t trial_steps,
     bool any = false;
     for (int q = 0; q < kNumCaps; ++q) {
       any = any || tried[d][q];
-      c->design[q] = tried[d][q] ? kTrials[d] : saved_design[q];
+      c->design[q] = saved_design[q];
+      if (!tried[d][q]) continue;
+      const int r = kernels_of(q, kTrials[d]);
+      c->design[q] = r == FSMP_DESIGN_GROUP_DEVMEM_WIDE ? kWideOnly : r;
     }
     if (!any) continue;
     st = fsmp_sample(c, &bt, &o, hip_stream);

@@ -232,3 +232,61 @@ def test_long_responses_at_any_number_of_chains():
     p = oracle_params(wl, sub=8, support=512)
     o = oracle.run(p, b["wave"], b["offsets"], b["lam"], 1, 20, 10, 2, 64, kmax=km)
     assert len(compare_chains(few, o)) == 0
+
+
+def _kernels(smp, cap, n, lam, lists=0):
+    """the kernel name and the outputs of n chains of one capacity"""
+    wl = synth.PRESETS["batched"]
+    m = 40
+    b = synth.generate(wl, n_wave=m, seed=6, lam=np.full(m, 20.0), lengths=np.full(m, 300))
+    r = n // m
+    kw = {}
+    if lists:
+        z = [np.arange(4 * 80, 4 * 80 + 3 * lists, 3).tolist()] * (m * r)
+        kw.update(z_init=z, t0_init=np.full(m * r, 75.0))
+    km, la = np.full(m * r, cap, np.int32), np.full(m * r, float(lam))
+    smp.set_timing(True)
+    out = smp.sample(torch.from_numpy(np.tile(b["wave"], r)).cuda(), np.arange(m * r + 1, dtype=np.int64) * 300, la,
+                     kmax=km, kz=cap, **kw)
+    t = [x["name"] for x in smp.last_timings() if x["kcap"] == cap]
+    return t[0], to_host(out), b, m
+
+
+# capacity, chains, intensity, sweeps, length of the start lists: the kernels of lists that stay short
+# against those of lists near the capacity.  Both sides as measured, microseconds a sweep LDS / narrow.
+@pytest.mark.parametrize("cap,n,lam,steps,lists,lds", [
+    (192, 4000, 2.0, 200, 0, False),    # K_max far above the intensity: 65 / 12
+    (192, 4000, 130.0, 20, 120, True),  # 145 / 200
+    (160, 2000, 90.0, 100, 0, False),   # a short run from no PEs: 33 / 7
+    (160, 2000, 120.0, 20, 110, True),  # 66 / 99
+    (160, 320, 90.0, 100, 0, True),
+    (128, 4000, 80.0, 20, 75, True),    # 60 / 100
+    (128, 2000, 5.0, 200, 0, False),    # 17 / 7
+    (96, 3000, 4.0, 200, 0, False),     # 17 / 9
+    (96, 5000, 60.0, 2000, 0, True),
+    (64, 3400, 4.0, 200, 0, False),     # 14 / 8
+    (48, 5000, 2.0, 200, 0, False),     # 14 / 9
+    (32, 10000, 1.0, 200, 0, False),
+    (32, 10000, 8.0, 200, 0, True),
+])
+def test_routes_follow_the_length_of_the_lists(cap, n, lam, steps, lists, lds):
+    smp = gpu_sampler(synth.PRESETS["batched"], steps, steps // 2, 1, 4, k_max=cap)
+    print(f"[case] route {cap} {n} {lam} {steps} {lists}", flush=True)
+    name, g, b, m = _kernels(smp, cap, n, lam, lists)
+    assert name.startswith("chain_group_dm") == (not lds), name
+    if lists == 0 and steps <= 200:
+        p = oracle_params(synth.PRESETS["batched"])
+        o = oracle.run(p, b["wave"], b["offsets"], np.full(m, lam), 1, steps, steps // 2, 4, cap,
+                       kmax=np.full(m, cap, np.int32))
+        part = {k: (v[:m] if isinstance(v, np.ndarray) else v) for k, v in g.items()}
+        assert len(compare_chains(part, o)) == 0
+
+
+def test_workspace_follows_the_route():
+    # the predicted workspace is that of the kernels that run: K^2 per chain in LDS, 2 K^2 beside it
+    wl = synth.PRESETS["batched"]
+    for lam, words in ((2.0, 2), (190.0, 1)):
+        smp = gpu_sampler(wl, 4000, 10, 1, 4, k_max=192)
+        off = np.arange(4001, dtype=np.int64) * 300
+        big = smp.workspace_bytes(off, np.full(4000, lam), kmax=np.full(4000, 192, np.int32))
+        assert abs(big - 4000 * words * 192 * 192 * 8) < 100e6
