@@ -661,7 +661,18 @@ __device__ inline void grp_col_update(MT *H, int i, int N, double ai, const doub
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const double v = TWO ? edit_two(h[u], ai, av[u], cA, bi, bw[u], cB, u == 0) : edit_build(h[u], ai, av[u], cA);
+      double v;
+      if constexpr (!TWO) {
+        v = edit_build(h[u], ai, av[u], cA);
+      } else if constexpr (HS > 1) {
+        v = edit_two(h[u], ai, av[u], cA, bi, bw[u], cB, u == 0);
+      } else {
+        // one chain per wavefront: no other kernel repeats its rounding, which is left to the code
+        // generator (168 and 232 ms for the launches of 128 and 160 in a batch of 250,000 tuned windows,
+        // 174 and 240 with the products fused as in edit_two)
+#pragma clang fp contract(fast)
+        v = h[u] + (ai * av[u] * cA + bi * bw[u] * cB);
+      }
       if (k0 + u < N) H[((k0 + u) * LD + i) * HS] = (MT)v;
     }
   }
