@@ -24,9 +24,11 @@
  *   - every chain draws its random numbers from Philox4x32-10 (Salmon et al., SC'11)
  *     with key (seed lo, seed hi) and counter (step, block, uid lo, uid hi),
  *     uid = wave_id * n_chains + chain: a chain's result does not depend on the batch
- *     it runs in, on the launch shape or on the other chains (from PE capacity 96 up the
- *     kernel, and with it the rounding of the charges' last bits, follows the number of
- *     chains; up to 64 both kernels round alike.  fsmp_set_design fixes it).
+ *     it runs in, on the launch shape or on the other chains.  (Where the library chooses the
+ *     kernels, FSMP_DESIGN_AUTO and _GROUP_DEVMEM_WIDE, it goes by the call: up to PE capacity
+ *     64 and in the FP32-refresh form the kernels it chooses from round alike, in FP64 from 96
+ *     up they differ in the last bits of charges and logs, and an acceptance within those of
+ *     its threshold can turn.  Every other design fixes the kernel, and fsmp_server_* does.)
  *   - pointers marked "device" are HIP device memory of the context's device; pointers
  *     marked "host" are ordinary host memory read during the call.  The caller owns every
  *     buffer it passes; the context owns its tables and workspace.
@@ -443,18 +445,19 @@ fsmp_status fsmp_set_timing(fsmp_ctx *ctx, int32_t enable);
  * set the launch's duration.  Capacities are 16, 32, 48, 64, 96, 128, 160, 192; a waveform
  * runs in the smallest one >= its kmax.  capacity 0 = every capacity that has the design.
  * FSMP_DESIGN_AUTO, which a context starts with, leaves the choice to the library.  A capacity
- * so (not set by this call, the autotuner or FSMP_CHAIN_DESIGN) runs
- * the LDS kernels, which exist in the library for every capacity and the mixture law, in the
- * corrected form from 48 up, for as many chains as they are the faster ones for (14,000 at
- * capacity 16 to 3,800 at 160), and the narrow device-memory groups beyond (the LDS kernels again
- * where the SER tables leave those no room); the FP32 form its
+ * so (not set by this call, the autotuner or FSMP_CHAIN_DESIGN) runs the LDS kernels, which exist
+ * in the library for every capacity and the mixture law, in the corrected form from 48 up, for as
+ * many chains as they are the faster ones for, and the narrow device-memory groups beyond (the
+ * LDS kernels again where the SER tables leave those no room).  On lists near their capacity
+ * that is 14,000 chains at 16 to 3,800 at 160 and any number at 192; fewer on shorter lists, as
+ * the call's intensities, sweeps and start lists lead to expect them.  The FP32 form runs its
  * wide groups for few chains.  FSMP_DESIGN_GROUP_DEVMEM_WIDE stands for the kernels that shorten
  * a sweep: in FP64 it too runs the LDS kernels while the chains are few enough (always up to
- * capacity 64 and at 192, 5,500 chains at 96 to 2,000 at 160).  The kernels that these two choose
- * from at any number of chains: FSMP_DESIGN_GROUP_LDS (every capacity, FP64 and the mixture law),
- * FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY (capacities 96 to 160 in FP64; where the FP32 form has wide
- * groups), FSMP_DESIGN_GROUP_DEVMEM.  Small calls run the LDS chains of all capacities up
- * to 64 in one launch, unless timings are on.
+ * capacity 64; on long lists any number at 192, 5,500 chains at 96 to 2,000 at 160).  The kernels
+ * that these two choose from at any number of chains: FSMP_DESIGN_GROUP_LDS (every capacity,
+ * FP64 and the mixture law), FSMP_DESIGN_GROUP_DEVMEM_WIDE_ONLY (capacities 96 to 160 in FP64;
+ * where the FP32 form has wide groups), FSMP_DESIGN_GROUP_DEVMEM.  Small calls run the LDS chains
+ * of all capacities up to 64 in one launch, unless timings are on.
  * FSMP_ENOTSUP if the requested pair does not exist.  The FP32-refresh form runs
  * FSMP_DESIGN_GROUP_DEVMEM and its wide groups (capacity 48 at 64); the mixture charge law
  * FSMP_DESIGN_GROUP_LDS and FSMP_DESIGN_GROUP_DEVMEM; replays run FSMP_DESIGN_GROUP_DEVMEM, or the

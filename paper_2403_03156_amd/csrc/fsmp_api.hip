@@ -287,7 +287,7 @@ int effective_design(const fsmp_ctx *c, int kcap, int design) {
 }
 
 // Up to this many chains per capacity the LDS kernels end before the device-memory groups.  Few
-// chains: the latency of a sweep decides (LDS 4-12 us, device memory 8-98 us); many: the LDS
+// chains: the latency of a sweep decides (the figures for 1,000 chains below); many: the LDS
 // holds fewer chains per CU than the device-memory groups run.  Both sides on windows of 512
 // samples with the lists at their length, microseconds per sweep of the whole launch, LDS /
 // narrow groups:

@@ -1855,7 +1855,9 @@ struct LdsLayout {
   // does not depend on which of the two its launch is given.
   static constexpr int kRO = KCAP <= 32 ? 4 : KCAP == 48 ? 16 : 32;
   // matrix, two scratch vectors, x (b and the residual too in the corrected form), the PE list (and
-  // the components)
+  // the components).  With the logs a workgroup takes 10 KB at 16 (four chains), 18 at 32 (two), 21 at 48,
+  // 36 at 64, 44 at 96 (three on a CU), 75 at 128 (two), 115 at 160 and 162 at 192 (one), and the rise
+  // table beside it, which has no room at 192: every PE takes an expm1 in a t0 step there.
   static constexpr int kDoubles = kMat + 2 * kVec + (CORR ? 3 : 1) * KCAP + (KCAP + 1) / 2 * (MCP ? 2 : 1);
 };
 
